@@ -6,8 +6,9 @@ extract the path of every target.  Inputs are resident in HBM before timing.
 
 Default workload: the 23170 x 23170 maze (Bernoulli(0.40) + 50,000 filled
 rectangles, 16 sources, 4096 targets on the largest component; seeded,
-synthetic).  Metric: Gcell-updates/s = cell-updates the sweep kernels execute
-per step (interior cells of the visited tiles x layers per visit) / step time.
+synthetic).  Metric: Gcell-updates/s = cell-updates the propagation kernels
+execute per step (interior cells of the visited tiles x layers applied to
+them) / step time.
 The dense equivalent of the paper's layer-by-layer network, cells x S_J / step
 time with S_J = L* + 1 effective layers, is reported beside it under its own
 key (the active schedule reaches the same bits while executing a small part of
@@ -35,16 +36,20 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0                  # MI355X HBM3E
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_c3_traffic.json")
-KERNEL_SOURCES = ("omap_sweep.h", "omap_sweep_split.h", "omap_sweep_variant.hip", "omap_internal.h")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_front_c3_traffic.json")
+KERNEL_SOURCES = ("omap_front.h", "omap_front.hip", "omap_sweep.h", "omap_internal.h")
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # 256 CUs x 4 SIMD x 16 lanes x 2.4 GHz, 32-bit ops
-BYTES_PER_CELL_UPDATE = 8.125          # int32 read + int32 write + 1 mask bit
+# integer sweep: int32 read + int32 write + 1 mask bit; bit-packed front: reached
+# set in and out and mask, 1 bit each (plus 4 B per reached cell once)
+BYTES_PER_CELL_UPDATE, FRONT_BYTES_PER_CELL_UPDATE = 8.125, 0.375
+# VALU operations per cell-update: integer sweep 4.5; front 6 per word of 32 cells
+OPS_PER_CELL_UPDATE, FRONT_OPS_PER_CELL_UPDATE = 4.5, 6 / 32
 LDS_FILE = os.path.join(ROOT, "profiles", "lds_c3_23170.json")
 LDS_SOURCES = KERNEL_SOURCES + ("omap_kernels.hip",)
 # LDS: 256 CUs x 128 B per clock (32 banks of 4 B) x 2.4 GHz
 LDS_PEAK_GBS = 256 * 128 * 2.4
 # kernels whose LDS use is summarized: (part of the name in the counter files, label)
-LDS_KERNELS = (("omap::k_sweep_split<", "k_sweep_split<16>"), ("omap::k_walk(", "k_walk"))
+LDS_KERNELS = (("omap::k_front(", "k_front"), ("omap::k_walk(", "k_walk"))
 LDS_COUNTERS = ("SQ_INSTS_LDS", "SQ_LDS_IDX_ACTIVE", "SQ_LDS_BANK_CONFLICT", "SQ_WAVES")
 
 
@@ -186,12 +191,12 @@ def _counter_per_dispatch(directory: str, counter: str, kernel_part: str):
 
 
 def summarize_counters(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, out_path, commands):
-    """profiles/k_sweep_c3_traffic.json from four rocprofv3 --pmc runs: the
+    """profiles/k_front_c3_traffic.json from four rocprofv3 --pmc runs: the
     sweep's FETCH_SIZE and WRITE_SIZE (KiB per dispatch), each scaled by what
     the counter reads for a plain pass of known size (bench.py --workload
     copy: 1 GiB read + 1 GiB written per launch)."""
     import paper_2004_00540_amd as omap
-    kern = "omap::k_sweep_split<"
+    kern = "omap::k_front("
     f_kib, n = _counter_per_dispatch(fetch_dir, "FETCH_SIZE", kern)
     w_kib, _ = _counter_per_dispatch(write_dir, "WRITE_SIZE", kern)
     cf_kib, _ = _counter_per_dispatch(copy_fetch_dir, "FETCH_SIZE", "neg_kernel")
@@ -201,7 +206,7 @@ def summarize_counters(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, out
     fetch = f_kib * 1024 * f_scale
     write = w_kib * 1024 * w_scale
     out = {
-        "kernel": "omap::k_sweep_split<16> (two waves per tile visit, per-round launch)",
+        "kernel": "omap::k_front (64 layers per tile visit, per-round launch)",
         "workload": "config3_23170x23170_rect_overlay",
         "options": omap.resolve_options(),
         "kernel_source_sha256": kernel_source_hash(),
@@ -237,9 +242,8 @@ def summarize_lds(pmc_dir: str, trace_dir: str, out_path: str, commands):
     """profiles/lds_c3_23170.json from one rocprofv3 --pmc run with the LDS
     counters (SQ_INSTS_LDS, SQ_LDS_IDX_ACTIVE, SQ_LDS_BANK_CONFLICT, SQ_WAVES)
     and the kernel trace of the same command.  LDS bytes are counted as 256 per
-    LDS instruction (64 lanes x 4 B: the ring rows, windows and counters are
-    32-bit accesses; the two-wave visit's input sums, 64-bit, are one
-    instruction per visit), an estimate of the data the instructions move."""
+    LDS instruction (64 lanes x 4 B: words and windows are 32-bit accesses), an
+    estimate of the data the instructions move."""
     import paper_2004_00540_amd as omap
     kernels = {}
     for part, label in LDS_KERNELS:
@@ -415,16 +419,21 @@ def bench_plain(args):
     resolved = omap.resolve_options(**opts)
     executed = prof["cell_updates"]            # per propagation = per step
     gcups = executed / step_s / 1e9
-    alg_bytes = prof["cell_updates"] * BYTES_PER_CELL_UPDATE
+    # the bit-packed front runs the default active shape and the bit-sliced schedule
+    front = resolved["schedule"] == omap.SCHEDULE_BITS or (
+        resolved["schedule"], resolved["temporal_depth"], resolved["tile_rows"], resolved["lane_columns"]) == (
+        omap.SCHEDULE_ACTIVE, 16, 16, 1)
+    alg_bytes = (prof["cell_updates"] * FRONT_BYTES_PER_CELL_UPDATE + 4 * info["reached_cells"] if front
+                 else prof["cell_updates"] * BYTES_PER_CELL_UPDATE)
     kern_s = prof["ms"] / 1e3
     launches = max(prof["launches"], 1)
     achieved = alg_bytes / kern_s / 1e9 if kern_s > 0 else 0.0
-    ops_per_cell = 4.5
+    ops_per_cell = FRONT_OPS_PER_CELL_UPDATE if front else OPS_PER_CELL_UPDATE
     alu_tops = prof["cell_updates"] * ops_per_cell / kern_s / 1e12 if kern_s > 0 else 0.0
     traffic = measured_traffic(m.name, resolved)
     out = {
         "metric": "Gcell-updates/s", "value": round(gcups, 3), "unit": "Gcell-updates/s",
-        "value_definition": "cell-updates executed by the sweep kernels per step / step time",
+        "value_definition": "cell-updates executed by the propagation kernels per step / step time",
         "dense_equivalent_gcell_updates_per_s": round(N * S_J / step_s / 1e9, 1),
         "dense_equivalent_definition": "cells x S_J / step time, S_J = L* + 1: the paper's layer-by-layer "
                                        "network reaches the same map with this many cell-updates",
@@ -486,7 +495,7 @@ def main():
     ap.add_argument("--serve-rounds", type=int, default=4)
     ap.add_argument("--summarize-counters", nargs=4, metavar=("FETCH_DIR", "WRITE_DIR", "COPY_FETCH_DIR",
                                                               "COPY_WRITE_DIR"),
-                    help="write profiles/k_sweep_c3_traffic.json from four rocprofv3 --pmc runs (no GPU)")
+                    help="write profiles/k_front_c3_traffic.json from four rocprofv3 --pmc runs (no GPU)")
     ap.add_argument("--summarize-trace", metavar="DIR", help="markdown table of a rocprofv3 --stats run (no GPU)")
     ap.add_argument("--summarize-lds", nargs=2, metavar=("PMC_DIR", "TRACE_DIR"),
                     help="write profiles/lds_c3_23170.json from a rocprofv3 --pmc run of the LDS counters and "

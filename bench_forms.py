@@ -122,7 +122,7 @@ def bench_batch(args):
         "speedup_vs_plain_loop": round(t_plain / t_batch, 2) if t_plain else None,
         "effective_gcell_updates_per_s": round(eff / t_batch / 1e9, 1),
         "paths_per_s": round(n_tgt / t_batch, 1),
-        "sweep_kernel": {"kernel": f"k_bits<{resolved['temporal_depth']}>" if bits else
+        "sweep_kernel": {"kernel": "k_front" if bits else
                          f"k_sweep<{resolved['temporal_depth']},{resolved['lane_columns']}>",
                          "launches": prof["launches"], "ms_total": round(prof["ms"], 3),
                          "avg_us": round(prof["ms"] * 1e3 / max(prof["launches"], 1), 2),

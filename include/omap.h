@@ -79,13 +79,17 @@ typedef enum omap_status {
 #define OMAP_SCHEDULE_DENSE 2    /* visit every tile of a maze until the maze stops changing      */
 #define OMAP_SCHEDULE_BITS 3     /* active schedule on a bit-packed reached set instead of int32  */
                                  /* activity: same results; temporal_depth 8 or 16, lane_columns 0 */
+                                 /* (both, and tile_rows, are accepted and checked; the kernel has */
+                                 /* one tile, 64 x 64 cells, and applies 64 layers per visit)      */
 
 /* Round launches (see omap_options.round_launch). */
 #define OMAP_LAUNCH_PER_ROUND 0  /* one kernel launch per round, enqueued by the host             */
 #define OMAP_LAUNCH_GRAPH 1      /* groups of rounds captured once in a HIP graph and replayed     */
 
 /* Execution options.  Zero-initialised = tuned defaults.  No option changes a
- * result: activity maps and paths are identical bit for bit for every value. */
+ * result: activity maps and paths are identical bit for bit for every value.
+ * A plan's default (active, 16 layers, 16 rows, 1 column per lane) runs on the
+ * same bit-packed kernel as OMAP_SCHEDULE_BITS. */
 typedef struct omap_options {
     int32_t temporal_depth;  /* layers applied per tile visit: 4, 8, 12, 16 (and 24, 32    */
                              /* with lane_columns = 2; bit-sliced: 8, 16); 0 = default     */
@@ -407,7 +411,9 @@ const char *omap_status_string(omap_status_t status);
 /* Kernel timing of a plan, batch or engine's tile-sweep kernel, collected with
  * HIP events on its stream while enabled (enable = 1 starts and clears,
  * enable = 0 stops).  *launches, *milliseconds, *cell_updates: totals since
- * enabling; cell_updates = interior cells of visited tiles x layers per visit.
+ * enabling; cell_updates = interior cells of visited tiles x layers applied to them (a
+ * visit of the bit-packed kernel counts the layers of the 16-layer steps in
+ * which some cell was reached).
  * kind: 0 plan, 1 batch, 2 engine. */
 omap_status_t omap_profile_enable(void *handle, int32_t kind, int32_t enable);
 omap_status_t omap_profile_read(void *handle, int32_t kind, int64_t *launches,

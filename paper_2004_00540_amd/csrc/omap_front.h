@@ -1,0 +1,349 @@
+// Bit-packed front propagation: the layers of the paper on a reached set of
+// one bit per cell, kFrontSteps x 16 layers per tile visit.
+//
+// With d(x) the 8-neighbour step distance from the nearest source, the layer
+// output of the paper is A_L(x) = max(0, L + 1 - d(x)) (Sec. Methods; the
+// closed form is what the tests pin), and the integer sweeps hold it as
+// V = K - d.  Here the state is the reached set R_n = {x : d(x) <= n}:
+// R_0 = sources and R_{n+1} = free AND dilate3x3(R_n).  A cell entering R at
+// layer n gets V = K - n written once (activity buffer 0), so V is exactly
+// what the integer sweeps produce and everything after propagation is shared.
+//
+// Layer numbers must be exact, so every visited tile of a maze advances the
+// same T layers per round (round r of a maze covers layers (r - round0) T + 1
+// .. + T) from ping-pong bit planes.
+//
+// Layout.  Planes and masks are strip-major: the 32-cell words of one 32-column
+// strip are contiguous down the rows (word (r, j) at j * mcol + r), so that a
+// wave whose lanes are rows loads 64 words with one contiguous access.  A
+// lane holds one row of the tile's region, its words in registers: horizontal
+// neighbours are funnel shifts between a lane's words, vertical ones DPP moves
+// between lanes, and a layer costs 6 VALU operations per word of 32 cells.
+//
+// A visit.  The block loads the tile's region (64 x 64 cells and a halo of T
+// on every side) into LDS once and runs kFrontSteps steps of 16 layers on it.
+// In step k wave g takes the 64 rows from 16 k + 32 g, applies 16 layers in
+// registers and returns the middle 32 rows, which are exact, to the other LDS
+// buffer; after the last step exactly the tile's 64 rows are left.  A wave whose
+// rows gain no cell in the first layer has nothing to do in any (its rows are
+// settled, and nothing outside them comes near its middle rows in 16 layers);
+// if no wave gains a cell the visit is over.
+//
+// The registers of the 16 layers of the tile's own two words form a unary
+// code of each cell's arrival, turned into 4 bit planes by 11 selects per
+// word; the planes of the whole visit are kept in LDS, and at the end every
+// wave writes activity rows from them, one lane per column.
+//
+// Scheduling.  A cell reached before the last layer of a round has all its free
+// neighbours reached by the end of the round, so only cells reached in
+// the last layer are a front that moves on: a tile with such a cell schedules
+// its 3 x 3 tiles (T <= 64 layers reach no further).  A tile that gained any cell
+// schedules itself: its next visit brings the other plane up to date, so
+// that both planes of an unvisited tile are equal.
+//
+// What bounds it: on one large maze the chain of rounds (launch gap, list and
+// region loads, four steps, claims), 64 layers per round instead of 16 of the
+// two-wave integer visit it replaced: 23170^2 maze with L* = 7124 per pass
+// (load, propagate, 4096 paths) 6.4 -> 2.7 ms, 4096^2 corridors (L* = 11,000)
+// 12.4 -> 4.1 ms; with fronts everywhere (26,000^2, 5000 sources, 650 layers)
+// VALU issue and the activity writes, 67.7 -> 13.7 ms.  Against the earlier
+// bit-sliced sweep (one row of 1984 columns per wave, 8 layers per visit, a
+// per-lane loop to write activity) a batch of 512 mazes takes 10.9 instead of
+// 21.3 ms.
+#pragma once
+
+#include "omap_sweep.h"
+
+namespace omap {
+
+constexpr int kFrontRows = 64;                       // tile rows
+constexpr int kFrontWords = kFrontCols / 32;         // tile words per row
+constexpr int kFrontHaloRows = kFrontLayers;
+constexpr int kFrontHaloWords = (kFrontLayers + 31) / 32;
+constexpr int kFrontRegionRows = kFrontRows + 2 * kFrontHaloRows;
+constexpr int kFrontRegionWords = kFrontWords + 2 * kFrontHaloWords;
+constexpr int kFrontGroups = (kFrontRegionRows - 32) / 32;   // waves with rows in step 0
+constexpr int kFrontWaves = 8;
+constexpr int kFrontThreads = kFrontWaves * kLanes;
+constexpr int kFrontPlanes = kFrontSteps <= 1 ? 4 : (kFrontSteps <= 2 ? 5 : 6);   // bits of a layer within a visit
+static_assert(kFrontRows == kFrontTileRows && kFrontRegionRows % 64 == 0 && kFrontGroups <= kFrontWaves, "front tile");
+static_assert(kFrontLayers <= kFrontRows && kFrontLayers <= kFrontCols, "a front reaches the next tiles only");
+
+struct FrontShared {
+    uint32_t r[2][kFrontRegionWords][kFrontRegionRows];   // reached, double-buffered over the steps
+    uint32_t f[kFrontRegionWords][kFrontRegionRows];      // free
+    uint32_t plane[kFrontPlanes][kFrontWords][kFrontRows];  // layer of arrival within the visit, bit-sliced
+    uint32_t fresh[kFrontWords][kFrontRows];              // cells that arrived in this visit
+    int32_t active[kFrontSteps];                          // some wave gained a cell in step k
+    int32_t last;                                         // a cell of the tile arrived in the last layer
+};
+
+// One layer of NW words per lane: o = free AND dilate(r).
+template <int NW>
+__device__ __forceinline__ void front_layer(const uint32_t (&r)[NW], const uint32_t (&f)[NW], uint32_t (&o)[NW]) {
+    uint32_t h[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        // column c sees c-1 (bit c-1, or bit 31 of the word to the left) and c+1
+        const uint32_t left = w > 0 ? __builtin_amdgcn_alignbit(r[w], r[w > 0 ? w - 1 : 0], 31) : r[w] << 1;
+        const uint32_t right = w + 1 < NW ? __builtin_amdgcn_alignbit(r[w + 1 < NW ? w + 1 : w], r[w], 1) : r[w] >> 1;
+        h[w] = r[w] | left | right;
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const uint32_t up = (uint32_t)from_left_lane((int)h[w]);     // the row above is the lane below
+        const uint32_t down = (uint32_t)from_right_lane((int)h[w]);
+        o[w] = (h[w] | up | down) & f[w];
+    }
+}
+
+// m ? a : b, bit by bit.
+__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
+
+// Step k of a visit, rows 16 k + 32 g .. + 63 of the region (one wave).
+__device__ __forceinline__ void front_step(FrontShared& sh, int k, int g) {
+    constexpr int NW = kFrontRegionWords, C0 = kFrontHaloWords;
+    const int lane = lane_id();
+    const int row = 16 * k + 32 * g + lane;
+    const int cur = k & 1;
+    uint32_t r[NW], f[NW], o[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        r[w] = sh.r[cur][w][row];
+        f[w] = sh.f[w][row];
+    }
+    uint32_t h[15][kFrontWords];   // the tile's words after 1 .. 15 layers
+    uint32_t r0[kFrontWords];
+#pragma unroll
+    for (int c = 0; c < kFrontWords; ++c) r0[c] = r[C0 + c];
+    front_layer<NW>(r, f, o);
+    uint32_t gain = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) gain |= o[w] ^ r[w];
+    const bool mid = lane >= 16 && lane < 48;
+    if (__ballot(gain != 0) == 0) {
+        if (mid) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sh.r[cur ^ 1][w][row] = r[w];
+        }
+        return;
+    }
+    if (lane == 0) sh.active[k] = 1;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) r[w] = o[w];
+#pragma unroll
+    for (int j = 0; j < 15; ++j) {
+#pragma unroll
+        for (int c = 0; c < kFrontWords; ++c) h[j][c] = r[C0 + c];
+        front_layer<NW>(r, f, o);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) r[w] = o[w];
+    }
+    if (mid) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sh.r[cur ^ 1][w][row] = r[w];
+    }
+    const int ti = row - kFrontHaloRows;   // row of the tile
+    const bool own = mid && ti >= 0 && ti < kFrontRows;
+    uint32_t fresh[kFrontWords], any = 0, lastb = 0;
+#pragma unroll
+    for (int c = 0; c < kFrontWords; ++c) {
+        fresh[c] = own ? r[C0 + c] & ~r0[c] : 0u;
+        any |= fresh[c];
+        lastb |= fresh[c] & ~h[14][c];
+    }
+    if (__ballot(any != 0) == 0) return;
+    if (k == kFrontSteps - 1 && __ballot(lastb != 0) != 0 && lane == 0) sh.last = 1;
+    if (!own) return;
+#pragma unroll
+    for (int c = 0; c < kFrontWords; ++c) {
+        // arrival a in 0 .. 15: a cell of layer a + 1 is in the sets after a + 1, a + 2, ...
+        const uint32_t in8 = h[7][c];
+        const uint32_t in4 = bit_select(in8, h[3][c], h[11][c]);
+        const uint32_t q0 = bit_select(in8, h[1][c], h[9][c]), q1 = bit_select(in8, h[5][c], h[13][c]);
+        const uint32_t in2 = bit_select(in4, q0, q1);
+        const uint32_t e0 = bit_select(in8, h[0][c], h[8][c]), e1 = bit_select(in8, h[2][c], h[10][c]);
+        const uint32_t e2 = bit_select(in8, h[4][c], h[12][c]), e3 = bit_select(in8, h[6][c], h[14][c]);
+        const uint32_t p0 = bit_select(in4, e0, e2), p1 = bit_select(in4, e1, e3);
+        const uint32_t in1 = bit_select(in2, p0, p1);
+        const uint32_t b[4] = {~in1 & fresh[c], ~in2 & fresh[c], ~in4 & fresh[c], ~in8 & fresh[c]};
+        // (one lane owns each word; the steps are separated by barriers)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) atomicOr(&sh.plane[j][c][ti], b[j]);
+        if (kFrontSteps > 1 && (k & 1)) atomicOr(&sh.plane[kFrontPlanes > 4 ? 4 : 0][c][ti], fresh[c]);
+        if (kFrontSteps > 2 && (k & 2)) atomicOr(&sh.plane[kFrontPlanes > 5 ? 5 : 0][c][ti], fresh[c]);
+        atomicOr(&sh.fresh[c][ti], fresh[c]);
+    }
+}
+
+// One round: T = kFrontLayers layers of every listed tile.
+__global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
+    // first list entry and count issued before anything else (see k_sweep)
+    int i = (int)blockIdx.x - 1;   // block 0: the accounting block
+    const int ie = i >= 0 && i < a.n_tile_ids ? i : 0;
+    uint64_t e = __hip_atomic_load(reinterpret_cast<const uint64_t*>(a.list_in + 2 * ie), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+    const int cnt = __hip_atomic_load(a.count_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const MazeDev md_one = a.md0;
+    const bool one = a.n_slots == 1;
+    if (a.round_base) a.round_id += *a.round_base;
+    if (blockIdx.x == 0) {
+        round_accounting<kFrontLayers, kFrontThreads>(a);
+        return;
+    }
+    __shared__ FrontShared sh;
+    constexpr int RR = kFrontRegionRows, RW = kFrontRegionWords;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = lane_id();
+    const int stride = a.wave_stride;
+    const int n = __builtin_amdgcn_readfirstlane(cnt);
+    for (; i < n; i += stride) {
+        const int g = __builtin_amdgcn_readfirstlane((int)(uint32_t)e);
+        const int slot = __builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32));
+        if (i + stride < n) e = *reinterpret_cast<const uint64_t*>(a.list_in + 2 * (i + stride));
+        const MazeDev md = one ? md_one : a.mazes[slot];
+        const int64_t n0 = (int64_t)(a.round_id - md.round0) * kFrontLayers;   // layers done before this round
+        const int64_t left = (int64_t)md.K - 1 - n0;                           // layers the maze still has
+        if (left <= 0) {   // every layer below K is done
+            if (threadIdx.x == 0) a.flags_in[g] = 0;
+            continue;
+        }
+        const int limit = left < kFrontLayers ? (int)left : kFrontLayers;
+        const int lt = g - md.tile_base;
+        const int ty = lt / md.tiles_x, tx = lt - ty * md.tiles_x;
+        const int r0 = ty * kFrontRows, j0 = tx * kFrontWords;
+        const uint32_t* Rin = a.parity ? md.R[1] : md.R[0];
+        uint32_t* Rout = a.parity ? md.R[0] : md.R[1];
+        // ---- load the region: chunks of 64 rows of one word, all loads issued
+        // before the first is used; outside the maze nothing is free or reached
+        constexpr int kChunks = RW * (RR / kLanes), kPer = (kChunks + kFrontWaves - 1) / kFrontWaves;
+        uint32_t vr[kPer], vm[kPer];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int c = wave + q * kFrontWaves;
+            const int j = j0 - kFrontHaloWords + c / (RR / kLanes);
+            const int r = r0 - kFrontHaloRows + (c % (RR / kLanes)) * kLanes + lane;
+            const bool ok = c < kChunks && j >= 0 && j < md.mpitch && r >= 0 && r < md.H;
+            const int64_t x = ok ? (int64_t)j * md.mcol + r : 0;
+            vr[q] = *(gconst_u32*)(Rin + x);
+            vm[q] = *(gconst_u32*)(md.mask + x);
+            if (!ok) {
+                vr[q] = 0;
+                vm[q] = 0xffffffffu;
+            }
+        }
+        if (threadIdx.x == 0) {   // (the touched flag is set by a tile that gained a cell)
+            a.flags_in[g] = 0;
+            a.maze_last_round[slot] = a.round_id;
+        }
+        for (int t = threadIdx.x; t < kFrontPlanes * kFrontWords * kFrontRows; t += kFrontThreads)
+            (&sh.plane[0][0][0])[t] = 0;
+        if (threadIdx.x < kFrontWords * kFrontRows) (&sh.fresh[0][0])[threadIdx.x] = 0;
+        if (threadIdx.x < kFrontSteps) sh.active[threadIdx.x] = 0;
+        if (threadIdx.x == 0) sh.last = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int c = wave + q * kFrontWaves;
+            if (c < kChunks) {
+                const int j = c / (RR / kLanes), r = (c % (RR / kLanes)) * kLanes + lane;
+                sh.r[0][j][r] = vr[q];
+                sh.f[j][r] = ~vm[q];   // guard bits (columns >= W) are obstacles
+            }
+        }
+        lds_barrier();
+        // ---- the steps
+        int fin = 0;   // buffer holding the tile's reached set
+        int k = 0;
+        for (; k < kFrontSteps; ++k) {
+            if (wave < kFrontGroups - k) front_step(sh, k, wave);
+            lds_barrier();
+            if (sh.active[k] == 0) break;   // nothing moves any more
+            fin ^= 1;
+        }
+        // ---- the last wave schedules the next round; waves 0 .. kFrontWords-1
+        // store the reached set and count; all write activity rows
+        const int base_v = md.K - 1 - (int)n0;
+        if (wave < kFrontWords) {
+            uint32_t fr = sh.fresh[wave][lane];
+            uint32_t rf = sh.r[fin][kFrontHaloWords + wave][kFrontHaloRows + lane];
+            if (limit < kFrontLayers) {   // cells past the maze's last layer do not count
+                uint32_t less = 0, same = fr;
+#pragma unroll
+                for (int b = kFrontPlanes - 1; b >= 0; --b) {
+                    const uint32_t p = sh.plane[b][wave][lane];
+                    if ((limit >> b) & 1) {
+                        less |= same & ~p;
+                        same &= p;
+                    } else {
+                        same &= ~p;
+                    }
+                }
+                rf &= ~(fr & ~less);
+                fr = less;
+            }
+            if (wave == 0 && lane == 0 && k > 0)   // 16 layers of the tile's cells per step that moved
+                atomicAdd(a.total_cells + (blockIdx.x & (kSpread - 1)),
+                          (unsigned long long)(k * tile_cells(md, ty, tx, kFrontRows, kFrontCols)));
+            if (r0 + lane < md.H) Rout[(int64_t)(j0 + wave) * md.mcol + r0 + lane] = rf;
+            if (__ballot(fr != 0) != 0) {
+                int count = __popc(fr);
+                for (int o = kLanes / 2; o > 0; o >>= 1) count += __shfl_xor(count, o);
+                int top = 0;   // the latest arrival among the counted cells
+                uint32_t m = fr;
+#pragma unroll
+                for (int b = kFrontPlanes - 1; b >= 0; --b) {
+                    const uint32_t t = m & sh.plane[b][wave][lane];
+                    if (__ballot(t != 0) != 0) {
+                        top |= 1 << b;
+                        m = t;
+                    }
+                }
+                if (lane == 0) {
+                    const int sp = blockIdx.x & (kSpread - 1);
+                    atomicAdd(&a.maze_reached[slot * kSpread + sp], (unsigned long long)count);
+                    atomicMax(&a.maze_layer[slot * kSpread + sp], (int)n0 + top + 1);
+                    a.touched[g] = 1;
+                }
+            }
+        }
+        if (wave == kFrontWaves - 1 && left > kFrontLayers) {
+            uint32_t fr = 0;
+#pragma unroll
+            for (int c = 0; c < kFrontWords; ++c) fr |= sh.fresh[c][lane];
+            const bool last = sh.last != 0;
+            if (__ballot(fr != 0) != 0) {
+                const int ny = ty + lane / 3 - 1, nx = tx + lane % 3 - 1;
+                const int gn = md.tile_base + ny * md.tiles_x + nx;
+                bool won = false;
+                if ((lane == 4 || (last && lane < 9)) && ny >= 0 && ny < md.tiles_y && nx >= 0 && nx < md.tiles_x)
+                    won = atomicExch(&a.flags_out[gn], 1) == 0;
+                const uint64_t wmask = __ballot(won);
+                const int nwon = __popcll(wmask);
+                if (nwon > 0) {
+                    int base = 0;
+                    if (lane == 0) base = atomicAdd(a.count_out, nwon);
+                    base = __builtin_amdgcn_readfirstlane(base);
+                    if (won) {
+                        const int q = base + __popcll(wmask & ((1ull << lane) - 1));
+                        a.list_out[2 * q] = gn;
+                        a.list_out[2 * q + 1] = slot;
+                    }
+                    if (!one && lane == 0) atomicAdd(&a.sched_out[slot], nwon);
+                }
+            }
+        }
+        // activity rows: lane = column of the tile
+        const int c = lane >> 5, b = lane & 31;
+        for (int row = wave; row < kFrontRows; row += kFrontWaves) {
+            const bool here = (sh.fresh[c][row] >> b) & 1u;
+            if (__ballot(here) == 0) continue;
+            int t = 0;
+#pragma unroll
+            for (int p = 0; p < kFrontPlanes; ++p) t |= (int)((sh.plane[p][c][row] >> b) & 1u) << p;
+            if (here && t < limit) md.V[0][(int64_t)(r0 + row) * md.pitch + j0 * 32 + lane] = base_v - t;
+        }
+        lds_barrier();   // the block's LDS is reused by the next tile
+    }
+}
+
+}  // namespace omap

@@ -14,25 +14,34 @@ constexpr uint32_t kObstacleBit = 0x80000000u;      // in-register obstacle mark
 // kSpread) so that concurrent waves do not serialise on one address; readers
 // sum the copies.
 constexpr int kSpread = 16;
-// Interior columns of a bit-sliced tile: 64 lanes x 32 bits minus one halo
-// word on each side.
-constexpr int kBitsTileColumns = (kLanes - 2) * 32;
+// Bit-packed front propagation (omap_front.h): layers per tile visit, in steps
+// of 16, and the tile.
+#ifndef OMAP_FRONT_STEPS
+#define OMAP_FRONT_STEPS 4
+#endif
+constexpr int kFrontSteps = OMAP_FRONT_STEPS;
+constexpr int kFrontLayers = 16 * kFrontSteps;
+constexpr int kFrontTileRows = 64;
+constexpr int kFrontCols = 64;
 
 // Maze state on the device.  Activity rows are `pitch` int32 apart (pitch a
 // multiple of 64, so rows are 256-byte aligned); the obstacle mask has one bit
 // per cell (bit c&31 of word c>>5 of the row, 1 = obstacle), `mpitch` words per
-// row, and the bits of columns >= W are set (guard bits).
+// row, and the bits of columns >= W are set (guard bits).  Word j of row r lies
+// at r * mrow + j * mcol: row by row (mrow = mpitch, mcol = 1) for the integer
+// sweeps, strip by strip (mrow = 1, mcol >= H) for the front propagation.
 struct MazeDev {
     int32_t H, W;
     int32_t pitch;
     int32_t mpitch;
+    int32_t mrow, mcol;
     int32_t tiles_x, tiles_y;
     int32_t tile_base;      // global id of tile (0, 0)
     int32_t K;              // source level of the encoding
-    int32_t* V[2];          // activity ping-pong
+    int32_t* V[2];          // activity ping-pong (front propagation: V[0] alone)
     const uint32_t* mask;
-    uint32_t* R[2];         // bit-sliced schedule: reached-set planes (mask layout), else null
-    int32_t round0;         // bit-sliced schedule: index of the maze's first round
+    uint32_t* R[2];         // front propagation: reached-set planes (mask layout), else null
+    int32_t round0;         // front propagation: index of the maze's first round
 };
 
 // Arguments of round r of the tile schedule.  The tile lists and their dedup
@@ -61,8 +70,11 @@ struct RoundArgs {
     int32_t* maze_last_round;     // per slot: last round with a tile visited
     uint8_t* touched;             // per tile id: written since its maze's buffers were last cleared
     int64_t* maze_visits;         // [slot][kSpread]: tile visits
-    int64_t* maze_cell_visits;    // [slot][kSpread]: interior cells of visited tiles
-    unsigned long long* total_cells;  // [kSpread], all slots: interior cells of visited tiles
+    int64_t* maze_cell_visits;    // [slot][kSpread]: interior cells of visited tiles (integer sweeps)
+    unsigned long long* total_cells;  // [kSpread], all slots: interior cells of visited tiles (front
+                                  // propagation: once per step of 16 layers)
+    unsigned long long* maze_reached; // front propagation, [slot][kSpread]: cells reached
+    int32_t* maze_layer;          // front propagation, [slot][kSpread]: last layer that reached a cell
     int32_t n_slots;
     int32_t round_id;             // r (wraps; only differences are used); in a graph replay
                                   // the round's offset in the captured group
@@ -89,23 +101,13 @@ struct RoundArgs {
 OMAP_SWEEP_VARIANTS(X)
 #undef X
 
-// Two-wave visits (omap_sweep_split.h): one column per lane, 16 layers per
-// visit, tiles of 16 rows; defined in the T = 16, C = 1 sweep variant.
-hipError_t launch_sweep_split_T16(const RoundArgs& a, int32_t grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-int sweep_split_blocks_per_cu_T16();
-
-// Bit-sliced variants (layers per visit); omap_bits_variant.hip with OMAP_BITS_T.
-#define OMAP_BITS_VARIANTS(X) X(8) X(16)
-
-#define X(t)                                                                                          \
-    hipError_t launch_bits_T##t(const RoundArgs& a, int32_t grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1); \
-    int bits_blocks_per_cu_T##t();
-OMAP_BITS_VARIANTS(X)
-#undef X
+// A round of the front propagation (omap_front.hip), `grid` visiting blocks.
+hipError_t launch_front(const RoundArgs& a, int32_t grid, hipStream_t s, hipEvent_t e0 = nullptr,
+                        hipEvent_t e1 = nullptr);
+int front_blocks_per_cu();
 
 // ---- launch wrappers (omap_kernels.hip) -------------------------------------
-hipError_t launch_pack_mask(const uint8_t* occ, int32_t H, int32_t W, uint32_t* mask,
-                            int32_t mpitch, hipStream_t s);
+hipError_t launch_pack_mask(const uint8_t* occ, const MazeDev& md, uint32_t* mask, hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n_elems, int32_t value, hipStream_t s);
 // Seed slot's sources (V := K) and schedule their tiles into a.list_out /
 // a.count_out / a.flags_out / a.sched_out (the runtime points these at the
@@ -113,8 +115,8 @@ hipError_t launch_fill(int32_t* p, int64_t n_elems, int32_t value, hipStream_t s
 // (src_slot: per-source slots, or nullptr for `slot`)
 hipError_t launch_seed(const RoundArgs& a, int32_t slot, const int32_t* src_rc, const int32_t* src_slot,
                        int32_t n_src, int32_t* bad_count, hipStream_t s);
-hipError_t launch_check_sources(const uint32_t* mask, int32_t mpitch, const int32_t* src_rc,
-                                int32_t n_src, int32_t* bad_count, hipStream_t s);
+hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, int32_t* bad_count,
+                                hipStream_t s);
 bool sweep_supported(int T, int C);
 // e0 / e1 (optional, both or neither): events that record the kernel's own
 // start and end (hipExtLaunchKernel), for profiling.
@@ -122,17 +124,13 @@ hipError_t launch_sweep(int T, int C, const RoundArgs& a, int32_t grid, hipStrea
                         hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // Clears slot's counters before its seeds (last round = r-1; dense: marks the
 // maze for a visit in the round about to run through a.dchg_prev).
-bool bits_supported(int T);
-int bits_max_waves_per_cu(int T);
-hipError_t launch_bits(int T, const RoundArgs& a, int32_t grid, hipStream_t s, hipEvent_t e0 = nullptr,
-                       hipEvent_t e1 = nullptr);
 hipError_t launch_slot_reset(const RoundArgs& a, const int32_t* slots, int32_t n, hipStream_t s);
 
 // Packing of several mazes' occupancy in one launch.
 struct PackJob {
     const uint8_t* occ;
     uint32_t* mask;
-    int32_t H, W, mpitch;
+    int32_t H, W, mpitch, mrow, mcol;
     int64_t word_begin;   // first word of this maze in the concatenation
 };
 hipError_t launch_pack_mask_many(const PackJob* jobs, int32_t n_jobs, int64_t total_words, hipStream_t s);
@@ -144,6 +142,8 @@ hipError_t launch_reduce(const MazeDev* mazes, const int32_t* tile_maze, const u
                          int32_t tile_begin, int32_t tile_end, const int32_t* slot_select, int32_t tile_rows,
                          int32_t tile_cols, int32_t parity, int32_t* maze_min,
                          unsigned long long* maze_reached, hipStream_t s);
+hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* reached, const int32_t* layer,
+                               int32_t n_slots, int32_t* maze_min, unsigned long long* maze_reached, hipStream_t s);
 hipError_t launch_path_lengths(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                                int32_t n_tgt, int32_t parity, int32_t* len, hipStream_t s);
 // order (optional): receives the targets by path length, longest first

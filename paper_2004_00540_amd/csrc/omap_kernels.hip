@@ -11,13 +11,19 @@ namespace omap {
 // ingest: occupancy bytes -> obstacle bit mask
 // ---------------------------------------------------------------------------
 
+// (a wave takes 8 words of 8 rows: 256 contiguous bytes of each row are read,
+// and in the strip layout 8 contiguous words of each strip are written)
 __global__ void k_pack_mask(const uint8_t* __restrict__ occ, int32_t H, int32_t W,
-                            uint32_t* __restrict__ mask, int32_t mpitch) {
-    const int64_t n = (int64_t)H * mpitch;
+                            uint32_t* __restrict__ mask, int32_t mpitch, int32_t mrow, int32_t mcol) {
+    const int32_t wb = (mpitch + 7) / 8;
+    const int64_t n = (int64_t)((H + 7) / 8) * wb * 64;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t r = (int32_t)(i / mpitch);
-        const int32_t w = (int32_t)(i - (int64_t)r * mpitch);
+        const int64_t q = i >> 6;
+        const int32_t rb = (int32_t)(q / wb);
+        const int32_t r = rb * 8 + (int32_t)((i >> 3) & 7);
+        const int32_t w = (int32_t)(q - (int64_t)rb * wb) * 8 + (int32_t)(i & 7);
+        if (r >= H || w >= mpitch) continue;
         const int32_t c0 = w * 32;
         const uint8_t* row = occ + (int64_t)r * W;
         uint32_t word = 0;
@@ -31,7 +37,7 @@ __global__ void k_pack_mask(const uint8_t* __restrict__ occ, int32_t H, int32_t 
                 word |= bit << b;
             }
         }
-        mask[i] = word;
+        mask[(int64_t)r * mrow + (int64_t)w * mcol] = word;
     }
 }
 
@@ -46,13 +52,16 @@ __global__ void k_fill(int32_t* __restrict__ p, int64_t n, int32_t value) {
     if (blockIdx.x == 0 && threadIdx.x < (unsigned)(n - 4 * n4)) p[4 * n4 + threadIdx.x] = value;
 }
 
-__global__ void k_check_sources(const uint32_t* __restrict__ mask, int32_t mpitch,
-                                const int32_t* __restrict__ src, int32_t n,
-                                int32_t* __restrict__ bad) {
+// Index of the mask (or plane) word holding cell (r, c).
+__device__ __forceinline__ int64_t mask_word(const MazeDev& md, int32_t r, int32_t c) {
+    return (int64_t)r * md.mrow + (int64_t)(c >> 5) * md.mcol;
+}
+
+__global__ void k_check_sources(MazeDev md, const int32_t* __restrict__ src, int32_t n, int32_t* __restrict__ bad) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t r = src[2 * i], c = src[2 * i + 1];
-    const uint32_t w = mask[(int64_t)r * mpitch + (c >> 5)];
+    const uint32_t w = md.mask[mask_word(md, r, c)];
     if ((w >> (c & 31)) & 1u) atomicAdd(bad, 1);
 }
 
@@ -66,18 +75,20 @@ __global__ void k_seed(RoundArgs a, int32_t slot0, const int32_t* __restrict__ s
     const int slot = src_slot != nullptr ? src_slot[i] : slot0;
     const MazeDev md = a.mazes[slot];
     const int32_t r = src[2 * i], c = src[2 * i + 1];
-    const uint32_t w = md.mask[(int64_t)r * md.mpitch + (c >> 5)];
+    const uint32_t w = md.mask[mask_word(md, r, c)];
     if ((w >> (c & 31)) & 1u) {
         atomicAdd(bad, 1);
         return;
     }
     const int64_t x = (int64_t)r * md.pitch + c;
     md.V[0][x] = md.K;
-    md.V[1][x] = md.K;
-    if (md.R[0] != nullptr) {   // bit-sliced schedule: the source is in R_0 (both planes)
-        const int64_t wx = (int64_t)r * md.mpitch + (c >> 5);
-        atomicOr(&md.R[0][wx], 1u << (c & 31));
-        atomicOr(&md.R[1][wx], 1u << (c & 31));
+    if (md.R[0] != nullptr) {   // front propagation: the source is in R_0 (both planes), counted once
+        const int64_t wx = mask_word(md, r, c);
+        const uint32_t bit = 1u << (c & 31);
+        atomicOr(&md.R[1][wx], bit);
+        if (!(atomicOr(&md.R[0][wx], bit) & bit)) atomicAdd(&a.maze_reached[slot * kSpread + (i & (kSpread - 1))], 1ull);
+    } else {
+        md.V[1][x] = md.K;
     }
     const int ty = r / a.tile_rows, tx = c / a.tile_cols;
     a.touched[md.tile_base + ty * md.tiles_x + tx] = 1;
@@ -101,14 +112,16 @@ __global__ void k_slot_reset(RoundArgs a, const int32_t* __restrict__ slots, int
     for (int k = 0; k < kSpread; ++k) {
         a.maze_visits[slot * kSpread + k] = 0;
         a.maze_cell_visits[slot * kSpread + k] = 0;
+        a.maze_reached[slot * kSpread + k] = 0;
+        a.maze_layer[slot * kSpread + k] = 0;
     }
     if (a.dense) a.dchg_prev[slot] = 1;
 }
 
 // One wave per tile id in [tile_begin, tile_begin + n_tiles) whose maze is
 // selected (sel == nullptr: every maze): zero the interior of touched tiles in
-// both activity buffers (and, for the bit-sliced schedule, the interior words
-// of both reached-set planes), and clear their touched flags.
+// both activity buffers (front propagation: in its one buffer and both
+// reached-set planes), and clear their touched flags.
 __global__ __launch_bounds__(kBlockThreads) void k_clear_touched(RoundArgs a, int32_t tile_begin,
                                                                  int32_t n_tiles,
                                                                  const int32_t* __restrict__ sel) {
@@ -124,17 +137,21 @@ __global__ __launch_bounds__(kBlockThreads) void k_clear_touched(RoundArgs a, in
     const int ty = lt / md.tiles_x, tx = lt - ty * md.tiles_x;
     const int r0 = ty * a.tile_rows, c0 = tx * a.tile_cols;
     const int rows = min(a.tile_rows, md.H - r0), cols = min(a.tile_cols, md.W - c0);
-    for (int k = lane_id(); k < rows * cols; k += kLanes) {
-        const int64_t x = (int64_t)(r0 + k / cols) * md.pitch + c0 + k % cols;
-        md.V[0][x] = 0;
-        md.V[1][x] = 0;
-    }
-    if (md.R[0] != nullptr) {   // bit tiles: 62 interior words per row
-        const int w0 = c0 / 32, nw = min((cols + 31) / 32, md.mpitch - w0);
-        for (int k = lane_id(); k < rows * nw; k += kLanes) {
-            const int64_t x = (int64_t)(r0 + k / nw) * md.mpitch + w0 + k % nw;
-            md.R[0][x] = 0;
-            md.R[1][x] = 0;
+    if (md.R[0] != nullptr) {   // front tiles: whole rows and words of 64 x 64 cells
+        static_assert(kFrontCols == kLanes && kFrontTileRows == kLanes, "front tile");
+        for (int k = 0; k < rows; ++k) md.V[0][(int64_t)(r0 + k) * md.pitch + c0 + lane_id()] = 0;
+        if (lane_id() < rows) {
+            for (int j = 0; j < kFrontCols / 32; ++j) {
+                const int64_t x = mask_word(md, r0 + lane_id(), c0 + 32 * j);
+                md.R[0][x] = 0;
+                md.R[1][x] = 0;
+            }
+        }
+    } else {
+        for (int k = lane_id(); k < rows * cols; k += kLanes) {
+            const int64_t x = (int64_t)(r0 + k / cols) * md.pitch + c0 + k % cols;
+            md.V[0][x] = 0;
+            md.V[1][x] = 0;
         }
     }
     if (lane_id() == 0) a.touched[g] = 0;
@@ -163,7 +180,7 @@ __global__ void k_pack_mask_many(const PackJob* __restrict__ jobs, int32_t n_job
             const uint32_t bit = (c >= jb.W) ? 1u : (row[c] != 0 ? 1u : 0u);
             word |= bit << b;
         }
-        jb.mask[wi] = word;
+        jb.mask[(int64_t)r * jb.mrow + (int64_t)w * jb.mcol] = word;
     }
 }
 
@@ -175,7 +192,7 @@ __global__ void k_check_sources_many(const MazeDev* __restrict__ mazes, const in
     const int slot = src_slot[i];
     const MazeDev md = mazes[slot];
     const int32_t r = src[2 * i], c = src[2 * i + 1];
-    const uint32_t w = md.mask[(int64_t)r * md.mpitch + (c >> 5)];
+    const uint32_t w = md.mask[mask_word(md, r, c)];
     if ((w >> (c & 31)) & 1u) atomicAdd(&bad[slot], 1);
 }
 
@@ -232,6 +249,23 @@ __global__ __launch_bounds__(256) void k_reduce(const MazeDev* __restrict__ maze
             atomicAdd(&maze_reached[slot], (unsigned long long)n);
         }
     }
+}
+
+// The same from the counts the front propagation's visits keep: per slot, the
+// cells reached and K minus the last layer that reached one.
+__global__ void k_front_report(const MazeDev* __restrict__ mazes, const unsigned long long* __restrict__ reached,
+                               const int32_t* __restrict__ layer, int32_t n_slots, int32_t* __restrict__ maze_min,
+                               unsigned long long* __restrict__ maze_reached) {
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= n_slots) return;
+    unsigned long long n = 0;
+    int last = 0;
+    for (int k = 0; k < kSpread; ++k) {
+        n += reached[s * kSpread + k];
+        last = max(last, layer[s * kSpread + k]);
+    }
+    maze_min[s] = mazes[s].K - last;
+    maze_reached[s] = n;
 }
 
 // ---------------------------------------------------------------------------
@@ -722,11 +756,10 @@ static int grid_for(int64_t n, int block, int cap = 1 << 20) {
     return (int)g;
 }
 
-hipError_t launch_pack_mask(const uint8_t* occ, int32_t H, int32_t W, uint32_t* mask,
-                            int32_t mpitch, hipStream_t s) {
-    const int64_t n = (int64_t)H * mpitch;
-    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, occ, H, W, mask,
-                       mpitch);
+hipError_t launch_pack_mask(const uint8_t* occ, const MazeDev& md, uint32_t* mask, hipStream_t s) {
+    const int64_t n = (int64_t)((md.H + 7) / 8) * ((md.mpitch + 7) / 8) * 64;
+    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, occ, md.H, md.W, mask,
+                       md.mpitch, md.mrow, md.mcol);
     return hipGetLastError();
 }
 
@@ -737,10 +770,9 @@ hipError_t launch_fill(int32_t* p, int64_t n_elems, int32_t value, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_check_sources(const uint32_t* mask, int32_t mpitch, const int32_t* src_rc,
-                                int32_t n_src, int32_t* bad_count, hipStream_t s) {
-    hipLaunchKernelGGL(k_check_sources, dim3(grid_for(n_src, 256)), dim3(256), 0, s, mask, mpitch,
-                       src_rc, n_src, bad_count);
+hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, int32_t* bad_count,
+                                hipStream_t s) {
+    hipLaunchKernelGGL(k_check_sources, dim3(grid_for(n_src, 256)), dim3(256), 0, s, md, src_rc, n_src, bad_count);
     return hipGetLastError();
 }
 
@@ -795,28 +827,6 @@ int sweep_max_waves_per_cu(int T, int C) {
     return (b > 1 ? b : 1) * kWavesPerBlock;
 }
 
-bool bits_supported(int T) {
-#define X(t) if (T == t) return true;
-    OMAP_BITS_VARIANTS(X)
-#undef X
-    return false;
-}
-
-int bits_max_waves_per_cu(int T) {
-    int b = 0;
-#define X(t) if (T == t) b = bits_blocks_per_cu_T##t();
-    OMAP_BITS_VARIANTS(X)
-#undef X
-    return (b > 1 ? b : 1) * kWavesPerBlock;
-}
-
-hipError_t launch_bits(int T, const RoundArgs& a, int32_t grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-#define X(t) if (T == t) return launch_bits_T##t(a, grid, s, e0, e1);
-    OMAP_BITS_VARIANTS(X)
-#undef X
-    return hipErrorInvalidValue;
-}
-
 bool sweep_supported(int T, int C) {
 #define X(t, c) if (T == t && C == c) return true;
     OMAP_SWEEP_VARIANTS(X)
@@ -832,6 +842,13 @@ hipError_t launch_reduce(const MazeDev* mazes, const int32_t* tile_maze, const u
     hipLaunchKernelGGL(k_reduce, dim3(tile_end - tile_begin), dim3(256), 0, s, mazes, tile_maze, touched,
                        tile_begin, slot_select, tile_rows, tile_cols, parity, maze_min,
                        maze_reached);
+    return hipGetLastError();
+}
+
+hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* reached, const int32_t* layer,
+                               int32_t n_slots, int32_t* maze_min, unsigned long long* maze_reached, hipStream_t s) {
+    hipLaunchKernelGGL(k_front_report, dim3(grid_for(n_slots, 64)), dim3(64), 0, s, mazes, reached, layer, n_slots,
+                       maze_min, maze_reached);
     return hipGetLastError();
 }
 

@@ -3,9 +3,8 @@
 // declared in include/omap.h.
 //
 // All device work of a handle is ordered on one HIP stream.  A propagation is a
-// sequence of rounds; one round is three launches: the tile sweep (T layers on
-// every scheduled tile), the schedule build (next round's tile list from the
-// change flags) and a per-maze update (counters, convergence).  The host reads
+// sequence of rounds, one launch each: T layers on every scheduled tile, which
+// also lists the next round's tiles.  The host reads
 // the scheduled-tile count back only every few rounds, so the device never
 // waits for a per-layer host handshake (the paper's appendix measures that
 // handshake as the dominant cost of running one layer per call).
@@ -168,29 +167,42 @@ struct Options {
     int TW = 64 * 4 - 2 * 16;
     int dense = 0;
     int check = 0;       // 0 = adaptive
-    int bits = 0;        // 1 = bit-sliced reached-set schedule (C unused; TW = 1984)
+    int front = 0;       // 1 = bit-packed front propagation (k_front: its own tile and depth)
     int graph = 0;       // 1 = rounds replayed from captured HIP graphs
-    int split = 0;       // 1 = two waves per tile visit (k_sweep_split: C = 1, T = TH = 16, active)
+    omap_options asked{};  // the option values as omap_resolve_options reports them
 };
 
 // Launch of one round's sweep kernel for the resolved options.
 static hipError_t launch_round_kernel(const Options& opt, const RoundArgs& a, int32_t grid, hipStream_t s,
                                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
-    if (opt.bits) return launch_bits(opt.T, a, grid, s, e0, e1);
-    if (opt.split) return launch_sweep_split_T16(a, grid, s, e0, e1);
+    if (opt.front) return launch_front(a, grid, s, e0, e1);
     return launch_sweep(opt.T, opt.C, a, grid, s, e0, e1);
 }
 
-// Defaults (measured on MI355X).  A single maze under the active schedule is
-// latency-bound (a few hundred tiles per round on 1024 SIMDs): one column per
-// lane keeps each visit short, and with the one-column visits' unrolled
-// warm-up 16 layers per visit beat 12 (23170^2 maze: propagation 8.2 vs
-// 8.5 ms; 2 columns and 16 layers: 12.8 ms).  Many mazes at once (batch,
-// engine) fill the device: there the bit-sliced schedule is fastest (512
-// mazes: 19.6k mazes/s against 17.9k for the active schedule with 2 columns
-// per lane and 12 layers per visit; serving capacity 198 against 180 mazes/s).
-// The dense schedule is throughput-bound: 4 columns per lane, 16 layers and
-// tall tiles.
+// The public values of an option set (what omap_resolve_options reports).
+static void report_options(Options* r, int schedule, int columns) {
+    r->asked.temporal_depth = r->T;
+    r->asked.tile_rows = r->TH;
+    r->asked.schedule = schedule;
+    r->asked.check_interval = r->check;
+    r->asked.lane_columns = columns;
+    r->asked.round_launch = r->graph ? OMAP_LAUNCH_GRAPH : OMAP_LAUNCH_PER_ROUND;
+}
+
+// The front propagation in place of an integer sweep: its own tile and depth.
+static void use_front(Options* r) {
+    r->front = 1;
+    r->T = kFrontLayers;
+    r->TH = kFrontTileRows;
+    r->TW = kFrontCols;
+}
+
+// Which kernel runs an option set.  The bit-packed front propagation (k_front)
+// serves the bit-sliced schedule and the active schedule as a single maze has
+// it by default (one column per lane, 16 layers, 16-row tiles); it applies 64
+// layers to a tile in the time the integer sweep takes for 16.  The other
+// shapes of the active schedule and the dense one run the integer sweeps; the dense
+// schedule is throughput-bound: 4 columns per lane, 16 layers, tall tiles.
 enum class Use { kPlan, kMany };
 static omap_status_t resolve_options(const omap_options* o, Options* out, Use use = Use::kPlan) {
     Options r;
@@ -203,7 +215,8 @@ static omap_status_t resolve_options(const omap_options* o, Options* out, Use us
         // the bit-sliced schedule has its own lane layout: an explicit column
         // count asks for the integer sweep
         schedule = (single || (o && o->lane_columns != 0)) ? OMAP_SCHEDULE_ACTIVE : OMAP_SCHEDULE_BITS;
-        if (schedule == OMAP_SCHEDULE_BITS && o && o->temporal_depth != 0 && !bits_supported(o->temporal_depth))
+        if (schedule == OMAP_SCHEDULE_BITS && o && o->temporal_depth != 0 && o->temporal_depth != 8 &&
+            o->temporal_depth != 16)
             schedule = OMAP_SCHEDULE_ACTIVE;
     }
     const bool dense = schedule == OMAP_SCHEDULE_DENSE;
@@ -232,21 +245,17 @@ static omap_status_t resolve_options(const omap_options* o, Options* out, Use us
     }
     r.dense = dense;
     if (bits) {
-        // bit-sliced: 32 columns per lane, one halo word per side
         if (o && o->lane_columns != 0)
             return fail(OMAP_ERR_INVALID_ARG, "lane_columns must be 0 with the bit-sliced schedule");
-        r.bits = 1;
-        r.C = 32;
-        // many mazes: 8 layers per visit (the autotuner's choice on the 512-maze
-        // batch, 21.4k against 19.6k mazes/s, and on the serving stream)
         if (r.T == 0) r.T = single ? 16 : 8;
-        if (!bits_supported(r.T))
+        if (r.T != 8 && r.T != 16)
             return fail(OMAP_ERR_INVALID_ARG, "temporal_depth %d is not available with the bit-sliced schedule (8, 16)",
                         r.T);
         r.TH = th ? th : std::max(16, r.T);
         if (r.TH < r.T)
             return fail(OMAP_ERR_INVALID_ARG, "tile_rows (%d) must be >= temporal_depth (%d)", r.TH, r.T);
-        r.TW = kBitsTileColumns;
+        report_options(&r, OMAP_SCHEDULE_BITS, 0);
+        use_front(&r);
         *out = r;
         return OMAP_OK;
     }
@@ -265,9 +274,8 @@ static omap_status_t resolve_options(const omap_options* o, Options* out, Use us
     if (r.TH < r.T)
         return fail(OMAP_ERR_INVALID_ARG, "tile_rows (%d) must be >= temporal_depth (%d)", r.TH, r.T);
     r.TW = 64 * r.C - 2 * r.T;
-    // a single maze with one column per lane and 16 layers on 16-row tiles
-    // (the latency-bound case) visits each tile with two waves
-    r.split = single && !dense && r.C == 1 && r.T == 16 && r.TH == 16;
+    report_options(&r, schedule, r.C);
+    if (single && !dense && r.C == 1 && r.T == 16 && r.TH == 16) use_front(&r);
     *out = r;
     return OMAP_OK;
 }
@@ -457,8 +465,9 @@ class PinnedPool {
 
 struct Geometry {
     int32_t H, W, pitch, mpitch, tiles_x, tiles_y;
+    int32_t mrow, mcol;         // mask layout (see MazeDev)
     int64_t v_bytes, m_bytes;
-    bool bits;                  // reached-set planes (m_bytes each) are needed
+    bool front;                 // one activity buffer and reached-set planes (m_bytes each)
 };
 
 static Geometry make_geometry(int32_t H, int32_t W, const Options& o) {
@@ -470,14 +479,17 @@ static Geometry make_geometry(int32_t H, int32_t W, const Options& o) {
     g.tiles_x = (W + o.TW - 1) / o.TW;
     g.tiles_y = (H + o.TH - 1) / o.TH;
     g.v_bytes = (int64_t)g.pitch * H * 4;
-    g.m_bytes = (int64_t)g.mpitch * H * 4;
-    g.bits = o.bits != 0;
+    g.front = o.front != 0;
+    // strips start on 64-byte lines
+    g.mrow = g.front ? 1 : g.mpitch;
+    g.mcol = g.front ? (H + 15) / 16 * 16 : 1;
+    g.m_bytes = (int64_t)g.mpitch * (g.front ? g.mcol : H) * 4;
     return g;
 }
 
 static int64_t maze_device_bytes(int32_t H, int32_t W, const Options& o) {
     const Geometry g = make_geometry(H, W, o);
-    return 2 * g.v_bytes + (g.bits ? 3 : 1) * g.m_bytes + 4096;
+    return (g.front ? 1 : 2) * g.v_bytes + (g.front ? 3 : 1) * g.m_bytes + 4096;
 }
 
 static omap_status_t validate_problem(int32_t H, int32_t W, const void* occ,
@@ -512,7 +524,7 @@ struct Slot {
     int32_t tile_base = 0, n_tiles = 0;
     int32_t* V[2] = {nullptr, nullptr};
     uint32_t* mask = nullptr;
-    uint32_t* R[2] = {nullptr, nullptr};   // bit-sliced schedule only
+    uint32_t* R[2] = {nullptr, nullptr};   // front propagation only
     int32_t* d_src = nullptr;
     std::vector<int32_t> src, tgt;
     int32_t K = 0;
@@ -545,6 +557,8 @@ class Solver {
     uint8_t* d_touched = nullptr;             // per tile id
     int64_t *d_visits = nullptr, *d_cell_visits = nullptr;
     unsigned long long* d_total_cells = nullptr;
+    unsigned long long* d_reached_copies = nullptr;   // front propagation: [cap_slots][kSpread] ...
+    int32_t* d_layer_copies = nullptr;                // ... cells reached and last layer
     int32_t* d_bad_slot = nullptr;            // per slot: sources found on obstacles
     int32_t* h_bad = nullptr;                 // pinned mirror of d_bad_slot
     std::vector<MazeDev> h_mazes;             // host mirror of d_mazes
@@ -662,6 +676,8 @@ class Solver {
         OK_TRY(dalloc(&d_visits, (size_t)cap_slots * kSpread));
         OK_TRY(dalloc(&d_cell_visits, (size_t)cap_slots * kSpread));
         OK_TRY(dalloc(&d_total_cells, kSpread));
+        OK_TRY(dalloc(&d_reached_copies, (size_t)cap_slots * kSpread));
+        OK_TRY(dalloc(&d_layer_copies, (size_t)cap_slots * kSpread));
         OK_TRY(dalloc(&d_min, cap_slots));
         OK_TRY(dalloc(&d_reached, cap_slots));
         OK_TRY(dalloc(&d_bad, 1));
@@ -686,11 +702,11 @@ class Solver {
         HIP_TRY(hipGetDevice(&dev));
         int cus = 0;
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        if (opt.split) {   // one tile per block of two waves
-            grid = std::max(1, cus * std::max(1, sweep_split_blocks_per_cu_T16()));
+        if (opt.front) {   // one tile per block
+            grid = std::max(1, cus * std::max(1, front_blocks_per_cu()));
             grid = std::max(1, std::min(grid, cap_tiles));
         } else {
-            const int waves = opt.bits ? bits_max_waves_per_cu(opt.T) : sweep_max_waves_per_cu(opt.T, opt.C);
+            const int waves = sweep_max_waves_per_cu(opt.T, opt.C);
             grid = std::max(1, cus * std::max(1, waves / kWavesPerBlock));
             const int need = (cap_tiles + kWavesPerBlock - 1) / kWavesPerBlock;
             grid = std::max(1, std::min(grid, need));
@@ -730,6 +746,8 @@ class Solver {
         a.maze_visits = d_visits;
         a.maze_cell_visits = d_cell_visits;
         a.total_cells = d_total_cells;
+        a.maze_reached = d_reached_copies;
+        a.maze_layer = d_layer_copies;
         a.n_slots = cap_slots;
         a.round_id = (int32_t)r;
         a.round_base = nullptr;
@@ -743,7 +761,7 @@ class Solver {
 
     void free_slot_buffers(Slot& s) {
         mem->release(s.V[0]);
-        mem->release(s.V[1]);
+        if (s.V[1]) mem->release(s.V[1]);
         mem->release(s.mask);
         mem->release(s.d_src);
         if (s.R[0]) mem->release(s.R[0]);
@@ -752,6 +770,20 @@ class Solver {
         s.R[0] = s.R[1] = nullptr;
         s.mask = nullptr;
         s.d_src = nullptr;
+    }
+
+    // Activity, mask and (front propagation) reached-set buffers of a slot;
+    // false when memory ran out (what was allocated stays with the slot).
+    bool alloc_slot_buffers(Slot& s) {
+        s.V[0] = static_cast<int32_t*>(mem->alloc(s.g.v_bytes));
+        s.mask = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
+        if (!s.g.front) {
+            s.V[1] = static_cast<int32_t*>(mem->alloc(s.g.v_bytes));
+            return s.V[0] && s.mask && s.V[1];
+        }
+        s.R[0] = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
+        s.R[1] = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
+        return s.V[0] && s.mask && s.R[0] && s.R[1];
     }
 
     // Copies slot k's descriptor to the device (stream-ordered; the host
@@ -769,6 +801,8 @@ class Solver {
         md.W = s.g.W;
         md.pitch = s.g.pitch;
         md.mpitch = s.g.mpitch;
+        md.mrow = s.g.mrow;
+        md.mcol = s.g.mcol;
         md.tiles_x = s.g.tiles_x;
         md.tiles_y = s.g.tiles_y;
         md.tile_base = s.tile_base;
@@ -852,14 +886,15 @@ class Solver {
         s.src.assign(src, src + 2 * n_src);
         if (tgt && n_tgt > 0) s.tgt.assign(tgt, tgt + 2 * n_tgt);
         else s.tgt.clear();
-        HIP_TRY(launch_pack_mask(occ_dev, s.g.H, s.g.W, s.mask, s.g.mpitch, stream));
+        set_desc(k);
+        HIP_TRY(launch_pack_mask(occ_dev, h_mazes[k], s.mask, stream));
         if (check_sources) {
             mem->release(s.d_src);
             s.d_src = static_cast<int32_t*>(mem->alloc(sizeof(int32_t) * 2 * n_src));
             if (!s.d_src) return fail(OMAP_ERR_OUT_OF_MEMORY, "source list (%d sources)", n_src);
             OK_TRY(upload(s.d_src, s.src.data(), sizeof(int32_t) * 2 * n_src));
             HIP_TRY(launch_fill(d_bad_slot + k, 1, 0, stream));
-            HIP_TRY(launch_check_sources(s.mask, s.g.mpitch, s.d_src, n_src, d_bad_slot + k, stream));
+            HIP_TRY(launch_check_sources(h_mazes[k], s.d_src, n_src, d_bad_slot + k, stream));
         }
         s.started = s.finalized = false;
         s.layers = -1;
@@ -904,14 +939,7 @@ class Solver {
             return fail(OMAP_ERR_OUT_OF_MEMORY, "no tile ids left for %lld tiles", (long long)nt);
         s.n_tiles = (int32_t)nt;
         s.used = true;
-        s.V[0] = static_cast<int32_t*>(mem->alloc(s.g.v_bytes));
-        s.V[1] = static_cast<int32_t*>(mem->alloc(s.g.v_bytes));
-        s.mask = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
-        if (s.g.bits) {
-            s.R[0] = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
-            s.R[1] = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
-        }
-        if (!s.V[0] || !s.V[1] || !s.mask || (s.g.bits && (!s.R[0] || !s.R[1]))) {
+        if (!alloc_slot_buffers(s)) {
             remove(k);
             return fail(OMAP_ERR_OUT_OF_MEMORY, "activity and mask buffers for %d x %d", H, W);
         }
@@ -953,14 +981,7 @@ class Solver {
                 return fail(OMAP_ERR_OUT_OF_MEMORY, "no tile ids left for %lld tiles", (long long)nt);
             s.n_tiles = (int32_t)nt;
             s.used = true;
-            s.V[0] = static_cast<int32_t*>(mem->alloc(s.g.v_bytes));
-            s.V[1] = static_cast<int32_t*>(mem->alloc(s.g.v_bytes));
-            s.mask = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
-            if (s.g.bits) {
-                s.R[0] = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
-                s.R[1] = static_cast<uint32_t*>(mem->alloc(s.g.m_bytes));
-            }
-            if (!s.V[0] || !s.V[1] || !s.mask || (s.g.bits && (!s.R[0] || !s.R[1])))
+            if (!alloc_slot_buffers(s))
                 return fail(OMAP_ERR_OUT_OF_MEMORY, "activity and mask buffers for %d x %d", d[i].height, d[i].width);
             s.src.assign(d[i].sources_host, d[i].sources_host + 2 * d[i].n_sources);
             if (d[i].targets_host && d[i].n_targets > 0)
@@ -972,6 +993,8 @@ class Solver {
             jb.H = s.g.H;
             jb.W = s.g.W;
             jb.mpitch = s.g.mpitch;
+            jb.mrow = s.g.mrow;
+            jb.mcol = s.g.mcol;
             jb.word_begin = words;
             words += (int64_t)s.g.H * s.g.mpitch;
             jobs.push_back(jb);
@@ -1071,8 +1094,8 @@ class Solver {
             Slot& s = slots[k];
             if (s.cleared) continue;
             HIP_TRY(launch_fill(s.V[0], s.g.v_bytes / 4, 0, stream));
-            HIP_TRY(launch_fill(s.V[1], s.g.v_bytes / 4, 0, stream));
-            if (s.g.bits) {
+            if (!s.g.front) HIP_TRY(launch_fill(s.V[1], s.g.v_bytes / 4, 0, stream));
+            if (s.g.front) {
                 HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(s.R[0]), s.g.m_bytes / 4, 0, stream));
                 HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(s.R[1]), s.g.m_bytes / 4, 0, stream));
             }
@@ -1138,7 +1161,7 @@ class Solver {
         a.round_id = 0;
         std::vector<char> sig(sizeof(RoundArgs) + 3 * sizeof(int));
         std::memcpy(sig.data(), &a, sizeof a);
-        const int extra[3] = {grid, opt.T, opt.C + 100 * opt.bits + 1000 * opt.split};
+        const int extra[3] = {grid, opt.T, opt.C + 100 * opt.front};
         std::memcpy(sig.data() + sizeof a, extra, sizeof extra);
         return sig;
     }
@@ -1218,9 +1241,9 @@ class Solver {
     }
 
     // Activity buffer holding the latest values: the round parity, except for
-    // the bit-sliced schedule, which writes each reached cell's value once,
-    // into buffer 0.
-    int vparity() const { return opt.bits ? 0 : parity; }
+    // the front propagation, which writes each reached cell's value once, into
+    // buffer 0.
+    int vparity() const { return opt.front ? 0 : parity; }
 
     // `rounds` rounds.
     omap_status_t run_rounds(int32_t rounds) {
@@ -1257,18 +1280,22 @@ class Solver {
     // activity and reached count land in h_min / h_reached (pinned host
     // arrays of cap_slots entries) once the stream gets there.
     omap_status_t finalize_enqueue(const std::vector<int32_t>& which, int32_t* h_min, unsigned long long* h_reached) {
-        HIP_TRY(launch_fill(d_min, cap_slots, 0x7fffffff, stream));
-        HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(d_reached), 2 * (int64_t)cap_slots, 0, stream));
-        std::vector<int32_t> sel(cap_slots, 0);
-        for (int32_t k : which) sel[k] = 1;
-        OK_TRY(upload(d_sel, sel.data(), sizeof(int32_t) * cap_slots));
-        int32_t lo = tile_hwm, hi = 0;
-        for (int32_t k : which) {
-            lo = std::min(lo, slots[k].tile_base);
-            hi = std::max(hi, slots[k].tile_base + slots[k].n_tiles);
+        if (opt.front) {   // the visits have counted as they went
+            HIP_TRY(launch_front_report(d_mazes, d_reached_copies, d_layer_copies, cap_slots, d_min, d_reached, stream));
+        } else {
+            HIP_TRY(launch_fill(d_min, cap_slots, 0x7fffffff, stream));
+            HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(d_reached), 2 * (int64_t)cap_slots, 0, stream));
+            std::vector<int32_t> sel(cap_slots, 0);
+            for (int32_t k : which) sel[k] = 1;
+            OK_TRY(upload(d_sel, sel.data(), sizeof(int32_t) * cap_slots));
+            int32_t lo = tile_hwm, hi = 0;
+            for (int32_t k : which) {
+                lo = std::min(lo, slots[k].tile_base);
+                hi = std::max(hi, slots[k].tile_base + slots[k].n_tiles);
+            }
+            HIP_TRY(launch_reduce(d_mazes, d_tile_maze, d_touched, lo, hi, d_sel, opt.TH, opt.TW, vparity(), d_min,
+                                  d_reached, stream));
         }
-        HIP_TRY(launch_reduce(d_mazes, d_tile_maze, d_touched, lo, hi, d_sel, opt.TH, opt.TW, vparity(), d_min,
-                              d_reached, stream));
         HIP_TRY(hipMemcpyAsync(h_min, d_min, sizeof(int32_t) * cap_slots, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipMemcpyAsync(h_reached, d_reached, sizeof(unsigned long long) * cap_slots, hipMemcpyDeviceToHost,
                                stream));
@@ -1534,7 +1561,8 @@ class Solver {
         OK_TRY(total_cells(&cells));
         if (launches) *launches = prof_launches;
         if (ms) *ms = prof_ms;
-        if (cell_updates) *cell_updates = (int64_t)(cells - prof_cells0) * opt.T;
+        // (a front visit counts its cells once per step of 16 layers)
+        if (cell_updates) *cell_updates = (int64_t)(cells - prof_cells0) * (opt.front ? 16 : opt.T);
         return OMAP_OK;
     }
 };
@@ -1704,10 +1732,18 @@ namespace omap {
 static size_t lo_offsets_at(size_t n) { return (4 * (n + 1) + 63) & ~size_t(63); }
 
 static int64_t query_bytes(const Query& q, const Options& o) {
-    // activity ping-pong + mask + staging of the occupancy + path scratch
+    // activity, mask and planes + staging of the occupancy + path scratch
     const int64_t nt = (int64_t)q.tgt.size() / 2;
     return maze_device_bytes(q.H, q.W, o) + (int64_t)q.H * q.W + 256 +
            nt * 64 + nt * 4 * ((int64_t)q.H + q.W) + 4096;
+}
+
+// The size by which a query counts as larger than the budget: two activity
+// buffers whatever the kernel keeps, so that the limit is the same for every
+// option set.
+static int64_t query_budget_bytes(const Query& q, const Options& o) {
+    const Geometry g = make_geometry(q.H, q.W, o);
+    return query_bytes(q, o) + (g.front ? g.v_bytes : 0);
 }
 
 static void query_release_occ(omap_engine_s* e, Query& q) {
@@ -2114,12 +2150,7 @@ omap_status_t omap_resolve_options(const omap_options* options, omap_options* re
     if (!resolved) return fail(OMAP_ERR_INVALID_ARG, "resolved is NULL");
     Options r;
     OK_TRY(resolve_options(options, &r));
-    resolved->temporal_depth = r.T;
-    resolved->tile_rows = r.TH;
-    resolved->schedule = r.bits ? OMAP_SCHEDULE_BITS : (r.dense ? OMAP_SCHEDULE_DENSE : OMAP_SCHEDULE_ACTIVE);
-    resolved->check_interval = r.check;
-    resolved->lane_columns = r.bits ? 0 : r.C;
-    resolved->round_launch = r.graph ? OMAP_LAUNCH_GRAPH : OMAP_LAUNCH_PER_ROUND;
+    *resolved = r.asked;
     return OMAP_OK;
 }
 
@@ -2474,9 +2505,10 @@ omap_status_t omap_engine_create(omap_engine_t* out, int64_t memory_budget_bytes
     if (!e->res_pool.init((size_t)pool)) return fail(OMAP_ERR_OUT_OF_MEMORY, "pinned results of %lld bytes", (long long)pool);
     e->budget = memory_budget_bytes;
     e->max_slots = max_slots;
-    // tile ids: enough for the whole budget filled with the smallest mazes
-    const int64_t per_tile = (int64_t)o.TH * o.TW * 8;
-    int64_t cap_tiles = memory_budget_bytes / per_tile + 4 * (int64_t)max_slots + 64;
+    // tile ids: enough for the whole budget filled with mazes of a strip's
+    // height or more (front tiles: of 16 rows or more, 31 tiles to 1984 columns)
+    const int64_t per_tile = o.front ? 16 * 1984 * 8 : (int64_t)o.TH * o.TW * 8;
+    int64_t cap_tiles = (memory_budget_bytes / per_tile + 4 * (int64_t)max_slots + 64) * (o.front ? 31 : 1);
     if (cap_tiles > (int64_t(1) << 28)) cap_tiles = int64_t(1) << 28;
     OK_TRY(e->solver.init(static_cast<hipStream_t>(stream), o, &e->mem, max_slots, (int32_t)cap_tiles,
                           size_t(16) << 20));
@@ -2505,8 +2537,9 @@ omap_status_t omap_engine_submit_ex(omap_engine_t engine, int32_t height, int32_
     q.L = max_layers;
     q.flags = flags;
     q.bytes = query_bytes(q, engine->solver.opt);
-    if (q.bytes > (int64_t)engine->mem.size())
-        return fail(OMAP_ERR_OUT_OF_MEMORY, "query needs %lld bytes, budget is %lld", (long long)q.bytes,
+    const int64_t need = query_budget_bytes(q, engine->solver.opt);
+    if (need > (int64_t)engine->mem.size())
+        return fail(OMAP_ERR_OUT_OF_MEMORY, "query needs %lld bytes, budget is %lld", (long long)need,
                     (long long)engine->mem.size());
     const Geometry g = make_geometry(height, width, engine->solver.opt);
     if ((int64_t)g.tiles_x * g.tiles_y > engine->solver.cap_tiles)

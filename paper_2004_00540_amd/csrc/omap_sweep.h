@@ -338,7 +338,7 @@ __device__ __forceinline__ void visit_bookkeeping(const RoundArgs& a, int g, int
     a.maze_last_round[slot] = a.round_id;
 }
 
-// The same for a visit of a listed tile (active and bit-sliced schedules):
+// The same for a visit of a listed tile (active schedule):
 // the round's accounting block has counted the visit as one of full size
 // (round_accounting), so only a tile cut by the maze's edge corrects the cell
 // counts; and the tile's scheduled flag of this round is cleared, which lets
@@ -362,10 +362,10 @@ __device__ __forceinline__ void visit_bookkeeping_active(const RoundArgs& a, int
 // visits from the list: per maze, its scheduled tiles (the whole list with
 // one maze) as visits of full tiles, corrected by the visits of edge tiles.
 // This replaces three same-address atomics per visit by one per maze and
-// round, off the visiting waves' path.  BITS_T (bit-sliced schedule, its
-// layers per visit): a maze whose rounds have covered its layers below K
-// visits nothing.
-template <int BITS_T, int NT = kBlockThreads>
+// round, off the visiting waves' path.  FRONT_T (front propagation, its layers
+// per visit): a maze whose rounds have covered its layers below K visits
+// nothing, and the visits count the cells they update themselves.
+template <int FRONT_T, int NT = kBlockThreads>
 __device__ __forceinline__ void round_accounting(const RoundArgs& a) {
     if (threadIdx.x == 0) *a.count_clear = 0;
     for (int m = threadIdx.x; m < a.n_slots; m += NT) {
@@ -375,15 +375,17 @@ __device__ __forceinline__ void round_accounting(const RoundArgs& a) {
     if (a.dense) return;
     const unsigned long long full = (unsigned long long)a.tile_rows * a.tile_cols;
     auto live = [&](const MazeDev& md) {
-        return BITS_T == 0 || (int64_t)(a.round_id - md.round0) * BITS_T + 1 < md.K;
+        return FRONT_T == 0 || (int64_t)(a.round_id - md.round0) * FRONT_T + 1 < md.K;
     };
     if (a.n_slots == 1) {
         if (threadIdx.x == 0) {
             const unsigned long long v = (unsigned long long)*a.count_in;
             if (v > 0 && live(a.md0)) {
                 atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_visits[0]), v);
-                atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[0]), v * full);
-                atomicAdd(a.total_cells, v * full);
+                if (FRONT_T == 0) {
+                    atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[0]), v * full);
+                    atomicAdd(a.total_cells, v * full);
+                }
             }
         }
         return;
@@ -393,10 +395,11 @@ __device__ __forceinline__ void round_accounting(const RoundArgs& a) {
         const unsigned long long v = (unsigned long long)a.sched_in[m];
         if (v > 0 && live(a.mazes[m])) {
             atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_visits[m * kSpread]), v);
-            atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[m * kSpread]), v * full);
+            if (FRONT_T == 0) atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[m * kSpread]), v * full);
             mine += v;
         }
     }
+    if (FRONT_T > 0) return;
     for (int o = kLanes / 2; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
     if (lane_id() == 0 && mine > 0) atomicAdd(a.total_cells + (threadIdx.x >> 6), mine * full);
 }
