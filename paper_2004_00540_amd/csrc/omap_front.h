@@ -31,8 +31,8 @@
 //
 // The registers of the 16 layers of the tile's own two words form a unary
 // code of each cell's arrival, turned into 4 bit planes by 11 selects per
-// word; the planes of the whole visit are kept in LDS, and at the end every
-// wave writes activity rows from them, one lane per column.
+// word; each step's planes and arrivals are kept in LDS, and at the end the
+// waves write activity rows from them, one lane per column.
 //
 // Scheduling.  A cell reached before the last layer of a round has all its free
 // neighbours reached by the end of the round, so only cells reached in
@@ -44,9 +44,11 @@
 // What bounds it: on one large maze the chain of rounds (launch gap, list and
 // region loads, four steps, claims), 64 layers per round instead of 16 of the
 // two-wave integer visit it replaced: 23170^2 maze with L* = 7124 per pass
-// (load, propagate, 4096 paths) 6.4 -> 2.7 ms, 4096^2 corridors (L* = 11,000)
-// 12.4 -> 4.1 ms; with fronts everywhere (26,000^2, 5000 sources, 650 layers)
-// VALU issue and the activity writes, 67.7 -> 13.7 ms.  Against the earlier
+// (load, propagate, 4096 paths) 6.4 -> 2.5 ms, 4096^2 corridors (L* = 11,000)
+// 12.4 -> 3.7 ms; with fronts everywhere (26,000^2, 5000 sources, 650 layers)
+// VALU issue and the activity writes, 67.7 -> 12.3 ms.  A lone visit takes 10 us:
+// list entry 0.9, region 0.6, steps 2.1 + 1.7 + 1.3 + 1.2, claims and activity
+// rows 1.5, and 1.6 us pass before the next round's first wave.  Against the earlier
 // bit-sliced sweep (one row of 1984 columns per wave, 8 layers per visit, a
 // per-lane loop to write activity) a batch of 512 mazes takes 10.9 instead of
 // 21.3 ms.
@@ -63,100 +65,111 @@ constexpr int kFrontHaloWords = (kFrontLayers + 31) / 32;
 constexpr int kFrontRegionRows = kFrontRows + 2 * kFrontHaloRows;
 constexpr int kFrontRegionWords = kFrontWords + 2 * kFrontHaloWords;
 constexpr int kFrontGroups = (kFrontRegionRows - 32) / 32;   // waves with rows in step 0
+// (4096^2 corridors, propagation: 8 waves 2.55 ms, 6: 2.77, 5: 3.03)
 constexpr int kFrontWaves = 8;
 constexpr int kFrontThreads = kFrontWaves * kLanes;
-constexpr int kFrontPlanes = kFrontSteps <= 1 ? 4 : (kFrontSteps <= 2 ? 5 : 6);   // bits of a layer within a visit
 static_assert(kFrontRows == kFrontTileRows && kFrontRegionRows % 64 == 0 && kFrontGroups <= kFrontWaves, "front tile");
 static_assert(kFrontLayers <= kFrontRows && kFrontLayers <= kFrontCols, "a front reaches the next tiles only");
 
 struct FrontShared {
     uint32_t r[2][kFrontRegionWords][kFrontRegionRows];   // reached, double-buffered over the steps
     uint32_t f[kFrontRegionWords][kFrontRegionRows];      // free
-    uint32_t plane[kFrontPlanes][kFrontWords][kFrontRows];  // layer of arrival within the visit, bit-sliced
-    uint32_t fresh[kFrontWords][kFrontRows];              // cells that arrived in this visit
+    uint4 code[kFrontSteps][kFrontWords][kFrontRows];     // layer of arrival within a step, 4 bit planes
+    uint32_t fresh[kFrontSteps][kFrontWords][kFrontRows]; // the tile's cells that arrived in a step
     int32_t active[kFrontSteps];                          // some wave gained a cell in step k
     int32_t last;                                         // a cell of the tile arrived in the last layer
 };
 
-// One layer of NW words per lane: o = free AND dilate(r).
+// Keeps the compiler's scheduler from moving instructions across this point.
+// A dependent VALU instruction issues 8 cycles after the one before it, an
+// independent one after 4 (measured, one wave on its SIMD), so a layer is
+// written as runs of independent instructions and kept that way: left to
+// itself the scheduler puts each funnel shift next to the OR that uses it.
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
+
+// One layer of NW words per lane: r = free AND dilate(r).
 template <int NW>
-__device__ __forceinline__ void front_layer(const uint32_t (&r)[NW], const uint32_t (&f)[NW], uint32_t (&o)[NW]) {
-    uint32_t h[NW];
+__device__ __forceinline__ void front_layer(uint32_t (&r)[NW], const uint32_t (&f)[NW]) {
+    uint32_t left[NW], right[NW], up[NW], h[NW];
+    keep_order();
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         // column c sees c-1 (bit c-1, or bit 31 of the word to the left) and c+1
-        const uint32_t left = w > 0 ? __builtin_amdgcn_alignbit(r[w], r[w > 0 ? w - 1 : 0], 31) : r[w] << 1;
-        const uint32_t right = w + 1 < NW ? __builtin_amdgcn_alignbit(r[w + 1 < NW ? w + 1 : w], r[w], 1) : r[w] >> 1;
-        h[w] = r[w] | left | right;
+        left[w] = w > 0 ? __builtin_amdgcn_alignbit(r[w], r[w > 0 ? w - 1 : 0], 31) : r[w] << 1;
+        right[w] = w + 1 < NW ? __builtin_amdgcn_alignbit(r[w + 1 < NW ? w + 1 : w], r[w], 1) : r[w] >> 1;
     }
+    keep_order();
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const uint32_t up = (uint32_t)from_left_lane((int)h[w]);     // the row above is the lane below
-        const uint32_t down = (uint32_t)from_right_lane((int)h[w]);
-        o[w] = (h[w] | up | down) & f[w];
-    }
+    for (int w = 0; w < NW; ++w) h[w] = r[w] | left[w] | right[w];
+    keep_order();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) up[w] = (uint32_t)from_left_lane((int)h[w]);   // the row above is the lane below
+    keep_order();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) up[w] |= (uint32_t)from_right_lane((int)h[w]);
+    keep_order();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) r[w] = (h[w] | up[w]) & f[w];
+    keep_order();
 }
 
 // m ? a : b, bit by bit.
 __device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
 
-// Step k of a visit, rows 16 k + 32 g .. + 63 of the region (one wave).
+// Step k of a visit, rows 16 k + 32 g .. + 63 and words W0 .. W0 + NW - 1 of
+// the region (one wave).  Of the tile's words it takes OWN from T0 on (their
+// arrivals, and in the last step their sets alone).
+template <int W0, int NW, int T0, int OWN, bool LAST>
 __device__ __forceinline__ void front_step(FrontShared& sh, int k, int g) {
-    constexpr int NW = kFrontRegionWords, C0 = kFrontHaloWords;
+    constexpr int C0 = kFrontHaloWords + T0 - W0;   // the first of them among the lane's
+    constexpr int S0 = LAST ? C0 : 0, S1 = LAST ? C0 + OWN : NW;   // words stored
     const int lane = lane_id();
     const int row = 16 * k + 32 * g + lane;
     const int cur = k & 1;
-    uint32_t r[NW], f[NW], o[NW];
+    uint32_t r[NW], f[NW], first[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        r[w] = sh.r[cur][w][row];
-        f[w] = sh.f[w][row];
+        first[w] = r[w] = sh.r[cur][W0 + w][row];
+        f[w] = sh.f[W0 + w][row];
     }
-    uint32_t h[15][kFrontWords];   // the tile's words after 1 .. 15 layers
-    uint32_t r0[kFrontWords];
-#pragma unroll
-    for (int c = 0; c < kFrontWords; ++c) r0[c] = r[C0 + c];
-    front_layer<NW>(r, f, o);
+    uint32_t h[15][OWN];   // the tile's words after 1 .. 15 layers
+    front_layer<NW>(r, f);
     uint32_t gain = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) gain |= o[w] ^ r[w];
+    for (int w = 0; w < NW; ++w) gain |= r[w] ^ first[w];
     const bool mid = lane >= 16 && lane < 48;
     if (__ballot(gain != 0) == 0) {
         if (mid) {
 #pragma unroll
-            for (int w = 0; w < NW; ++w) sh.r[cur ^ 1][w][row] = r[w];
+            for (int w = S0; w < S1; ++w) sh.r[cur ^ 1][W0 + w][row] = r[w];
         }
         return;
     }
     if (lane == 0) sh.active[k] = 1;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) r[w] = o[w];
-#pragma unroll
     for (int j = 0; j < 15; ++j) {
 #pragma unroll
-        for (int c = 0; c < kFrontWords; ++c) h[j][c] = r[C0 + c];
-        front_layer<NW>(r, f, o);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) r[w] = o[w];
+        for (int c = 0; c < OWN; ++c) h[j][c] = r[C0 + c];
+        front_layer<NW>(r, f);
     }
     if (mid) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) sh.r[cur ^ 1][w][row] = r[w];
+        for (int w = S0; w < S1; ++w) sh.r[cur ^ 1][W0 + w][row] = r[w];
     }
     const int ti = row - kFrontHaloRows;   // row of the tile
     const bool own = mid && ti >= 0 && ti < kFrontRows;
-    uint32_t fresh[kFrontWords], any = 0, lastb = 0;
+    uint32_t fresh[OWN], any = 0, lastb = 0;
 #pragma unroll
-    for (int c = 0; c < kFrontWords; ++c) {
-        fresh[c] = own ? r[C0 + c] & ~r0[c] : 0u;
+    for (int c = 0; c < OWN; ++c) {
+        fresh[c] = own ? r[C0 + c] & ~first[C0 + c] : 0u;
         any |= fresh[c];
         lastb |= fresh[c] & ~h[14][c];
     }
     if (__ballot(any != 0) == 0) return;
-    if (k == kFrontSteps - 1 && __ballot(lastb != 0) != 0 && lane == 0) sh.last = 1;
+    if (LAST && __ballot(lastb != 0) != 0 && lane == 0) sh.last = 1;
     if (!own) return;
 #pragma unroll
-    for (int c = 0; c < kFrontWords; ++c) {
+    for (int c = 0; c < OWN; ++c) {
         // arrival a in 0 .. 15: a cell of layer a + 1 is in the sets after a + 1, a + 2, ...
         const uint32_t in8 = h[7][c];
         const uint32_t in4 = bit_select(in8, h[3][c], h[11][c]);
@@ -166,17 +179,22 @@ __device__ __forceinline__ void front_step(FrontShared& sh, int k, int g) {
         const uint32_t e2 = bit_select(in8, h[4][c], h[12][c]), e3 = bit_select(in8, h[6][c], h[14][c]);
         const uint32_t p0 = bit_select(in4, e0, e2), p1 = bit_select(in4, e1, e3);
         const uint32_t in1 = bit_select(in2, p0, p1);
-        const uint32_t b[4] = {~in1 & fresh[c], ~in2 & fresh[c], ~in4 & fresh[c], ~in8 & fresh[c]};
-        // (one lane owns each word; the steps are separated by barriers)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) atomicOr(&sh.plane[j][c][ti], b[j]);
-        if (kFrontSteps > 1 && (k & 1)) atomicOr(&sh.plane[kFrontPlanes > 4 ? 4 : 0][c][ti], fresh[c]);
-        if (kFrontSteps > 2 && (k & 2)) atomicOr(&sh.plane[kFrontPlanes > 5 ? 5 : 0][c][ti], fresh[c]);
-        atomicOr(&sh.fresh[c][ti], fresh[c]);
+        sh.code[k][T0 + c][ti] = make_uint4(~in1, ~in2, ~in4, ~in8);
+        sh.fresh[k][T0 + c][ti] = fresh[c];
     }
 }
 
-// One round: T = kFrontLayers layers of every listed tile.
+// lt / tiles_x for 0 <= lt < 2^31: the product with the rounded-down reciprocal
+// is the quotient or one less.
+__device__ __forceinline__ int front_tile_row(const MazeDev& md, int lt) {
+    const int q = (int)(((uint64_t)(uint32_t)lt * md.tiles_x_inv) >> 32);
+    return q + (lt - q * md.tiles_x >= md.tiles_x);
+}
+
+// One round: T = kFrontLayers layers of every listed tile.  ONE: a single maze,
+// described in the arguments (copying either description into one variable
+// kept both in scalar registers, and their spills cost 0.9 us of a round).
+template <bool ONE>
 __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
     // first list entry and count issued before anything else (see k_sweep)
     int i = (int)blockIdx.x - 1;   // block 0: the accounting block
@@ -184,8 +202,18 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
     uint64_t e = __hip_atomic_load(reinterpret_cast<const uint64_t*>(a.list_in + 2 * ie), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
     const int cnt = __hip_atomic_load(a.count_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    const MazeDev md_one = a.md0;
-    const bool one = a.n_slots == 1;
+    // the arguments are read while those loads are in flight, all together (left
+    // to the compiler, their loads are issued and waited for in four groups
+    // after the list entry arrived: 0.7 us)
+    if (ONE)
+        asm volatile("" ::"s"(a.md0.mask), "s"(a.md0.R[0]), "s"(a.md0.R[1]), "s"(a.md0.H), "s"(a.md0.mpitch),
+                     "s"(a.md0.mcol), "s"(a.md0.tiles_x), "s"(a.md0.tiles_x_inv), "s"(a.md0.tile_base), "s"(a.md0.K),
+                     "s"(a.md0.round0), "s"(a.parity), "s"(a.round_id), "s"(a.flags_in), "s"(a.maze_last_round),
+                     "s"(a.wave_stride), "s"(a.md0.V[0]), "s"(a.md0.pitch), "s"(a.md0.W), "s"(a.total_cells),
+                     "s"(a.maze_reached), "s"(a.maze_layer), "s"(a.touched));
+    else
+        asm volatile("" ::"s"(a.mazes), "s"(a.parity), "s"(a.round_id), "s"(a.flags_in), "s"(a.maze_last_round),
+                     "s"(a.wave_stride));
     if (a.round_base) a.round_id += *a.round_base;
     if (blockIdx.x == 0) {
         round_accounting<kFrontLayers, kFrontThreads>(a);
@@ -193,15 +221,17 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
     }
     __shared__ FrontShared sh;
     constexpr int RR = kFrontRegionRows, RW = kFrontRegionWords;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = lane_id();
     const int stride = a.wave_stride;
     const int n = __builtin_amdgcn_readfirstlane(cnt);
     for (; i < n; i += stride) {
+        // (opaque to the compiler, which would otherwise compute everything that
+        // depends on the lane alone before the loop, ahead of the first visit's loads)
+        int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
+        asm volatile("" : "+s"(wave), "+v"(lane));
         const int g = __builtin_amdgcn_readfirstlane((int)(uint32_t)e);
         const int slot = __builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32));
         if (i + stride < n) e = *reinterpret_cast<const uint64_t*>(a.list_in + 2 * (i + stride));
-        const MazeDev md = one ? md_one : a.mazes[slot];
+        const MazeDev& md = ONE ? a.md0 : a.mazes[slot];
         const int64_t n0 = (int64_t)(a.round_id - md.round0) * kFrontLayers;   // layers done before this round
         const int64_t left = (int64_t)md.K - 1 - n0;                           // layers the maze still has
         if (left <= 0) {   // every layer below K is done
@@ -210,7 +240,7 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
         }
         const int limit = left < kFrontLayers ? (int)left : kFrontLayers;
         const int lt = g - md.tile_base;
-        const int ty = lt / md.tiles_x, tx = lt - ty * md.tiles_x;
+        const int ty = front_tile_row(md, lt), tx = lt - ty * md.tiles_x;
         const int r0 = ty * kFrontRows, j0 = tx * kFrontWords;
         const uint32_t* Rin = a.parity ? md.R[1] : md.R[0];
         uint32_t* Rout = a.parity ? md.R[0] : md.R[1];
@@ -236,9 +266,8 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
             a.flags_in[g] = 0;
             a.maze_last_round[slot] = a.round_id;
         }
-        for (int t = threadIdx.x; t < kFrontPlanes * kFrontWords * kFrontRows; t += kFrontThreads)
-            (&sh.plane[0][0][0])[t] = 0;
-        if (threadIdx.x < kFrontWords * kFrontRows) (&sh.fresh[0][0])[threadIdx.x] = 0;
+        for (int t = threadIdx.x; t < kFrontSteps * kFrontWords * kFrontRows; t += kFrontThreads)
+            (&sh.fresh[0][0][0])[t] = 0;
         if (threadIdx.x < kFrontSteps) sh.active[threadIdx.x] = 0;
         if (threadIdx.x == 0) sh.last = 0;
 #pragma unroll
@@ -255,91 +284,123 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
         int fin = 0;   // buffer holding the tile's reached set
         int k = 0;
         for (; k < kFrontSteps; ++k) {
-            if (wave < kFrontGroups - k) front_step(sh, k, wave);
+            // the last 32 layers need the words next to the tile only; the last step
+            // is split by the tile's words too (its rows take two waves, the
+            // block's other SIMDs would idle)
+            constexpr int H = kFrontHaloWords;
+            static_assert(H == 2 && kFrontWords == 2 && kFrontSteps == 4, "words of a step");
+            if (k < kFrontSteps - 2) {
+                if (wave < kFrontGroups - k) front_step<0, RW, 0, 2, false>(sh, k, wave);
+            } else if (k < kFrontSteps - 1) {
+                if (wave < kFrontGroups - k) front_step<H - 1, 4, 0, 2, false>(sh, k, wave);
+            } else {
+                if (wave < 2) front_step<H - 1, 3, 0, 1, true>(sh, k, wave);
+                else if (wave < 4) front_step<H, 3, 1, 1, true>(sh, k, wave - 2);
+            }
             lds_barrier();
             if (sh.active[k] == 0) break;   // nothing moves any more
             fin ^= 1;
         }
-        // ---- the last wave schedules the next round; waves 0 .. kFrontWords-1
-        // store the reached set and count; all write activity rows
+        // ---- the last wave schedules the next round (a chain of two atomics, so
+        // that is all it does), waves 0 .. kFrontWords-1 store the reached set
+        // and count, and they and the others write activity rows
         const int base_v = md.K - 1 - (int)n0;
         if (wave < kFrontWords) {
-            uint32_t fr = sh.fresh[wave][lane];
-            uint32_t rf = sh.r[fin][kFrontHaloWords + wave][kFrontHaloRows + lane];
-            if (limit < kFrontLayers) {   // cells past the maze's last layer do not count
-                uint32_t less = 0, same = fr;
+            const uint32_t rf = sh.r[fin][kFrontHaloWords + wave][kFrontHaloRows + lane];
+            uint32_t late = 0;   // cells past the maze's last layer do not count
+            uint32_t count = 0;
+            int top = -1;        // the latest arrival among the counted cells
+            for (int j = 0; j < k; ++j) {
+                uint32_t fr = sh.fresh[j][wave][lane];
+                if (__ballot(fr != 0) == 0) continue;
+                const uint4 code = sh.code[j][wave][lane];
+                if (limit < 16 * (j + 1)) {
+                    const int lim = max(limit - 16 * j, 0);   // arrivals below lim count
+                    uint32_t less = 0, same = fr;
+                    const uint32_t plane[4] = {code.x, code.y, code.z, code.w};
 #pragma unroll
-                for (int b = kFrontPlanes - 1; b >= 0; --b) {
-                    const uint32_t p = sh.plane[b][wave][lane];
-                    if ((limit >> b) & 1) {
-                        less |= same & ~p;
-                        same &= p;
-                    } else {
-                        same &= ~p;
+                    for (int b = 3; b >= 0; --b) {
+                        if ((lim >> b) & 1) {
+                            less |= same & ~plane[b];
+                            same &= plane[b];
+                        } else {
+                            same &= ~plane[b];
+                        }
                     }
+                    late |= fr & ~less;
+                    fr = less;
                 }
-                rf &= ~(fr & ~less);
-                fr = less;
-            }
-            if (wave == 0 && lane == 0 && k > 0)   // 16 layers of the tile's cells per step that moved
-                atomicAdd(a.total_cells + (blockIdx.x & (kSpread - 1)),
-                          (unsigned long long)(k * tile_cells(md, ty, tx, kFrontRows, kFrontCols)));
-            if (r0 + lane < md.H) Rout[(int64_t)(j0 + wave) * md.mcol + r0 + lane] = rf;
-            if (__ballot(fr != 0) != 0) {
-                int count = __popc(fr);
-                for (int o = kLanes / 2; o > 0; o >>= 1) count += __shfl_xor(count, o);
-                int top = 0;   // the latest arrival among the counted cells
                 uint32_t m = fr;
-#pragma unroll
-                for (int b = kFrontPlanes - 1; b >= 0; --b) {
-                    const uint32_t t = m & sh.plane[b][wave][lane];
-                    if (__ballot(t != 0) != 0) {
-                        top |= 1 << b;
-                        m = t;
-                    }
-                }
+                if (__ballot(m != 0) == 0) continue;
+                int t = 0;
+                if (__ballot((m & code.w) != 0)) { t |= 8; m &= code.w; }
+                if (__ballot((m & code.z) != 0)) { t |= 4; m &= code.z; }
+                if (__ballot((m & code.y) != 0)) { t |= 2; m &= code.y; }
+                if (__ballot((m & code.x) != 0)) t |= 1;
+                top = 16 * j + t;
+                count += __popc(fr);
+            }
+            if (r0 + lane < md.H) Rout[(int64_t)(j0 + wave) * md.mcol + r0 + lane] = rf & ~late;
+            const int sp = blockIdx.x & (kSpread - 1);
+            if (wave == 0 && lane == 0 && k > 0)   // 16 layers of the tile's cells per step that moved
+                atomicAdd(a.total_cells + sp, (unsigned long long)(k * tile_cells(md, ty, tx, kFrontRows, kFrontCols)));
+            if (top >= 0) {
+                for (int o = kLanes / 2; o > 0; o >>= 1) count += __shfl_xor(count, o);
                 if (lane == 0) {
-                    const int sp = blockIdx.x & (kSpread - 1);
                     atomicAdd(&a.maze_reached[slot * kSpread + sp], (unsigned long long)count);
                     atomicMax(&a.maze_layer[slot * kSpread + sp], (int)n0 + top + 1);
                     a.touched[g] = 1;
                 }
             }
         }
-        if (wave == kFrontWaves - 1 && left > kFrontLayers) {
-            uint32_t fr = 0;
+        if (wave == kFrontWaves - 1) {
+            if (left > kFrontLayers) {
+                uint32_t fr = 0;
+                for (int j = 0; j < k; ++j)
 #pragma unroll
-            for (int c = 0; c < kFrontWords; ++c) fr |= sh.fresh[c][lane];
-            const bool last = sh.last != 0;
-            if (__ballot(fr != 0) != 0) {
-                const int ny = ty + lane / 3 - 1, nx = tx + lane % 3 - 1;
-                const int gn = md.tile_base + ny * md.tiles_x + nx;
-                bool won = false;
-                if ((lane == 4 || (last && lane < 9)) && ny >= 0 && ny < md.tiles_y && nx >= 0 && nx < md.tiles_x)
-                    won = atomicExch(&a.flags_out[gn], 1) == 0;
-                const uint64_t wmask = __ballot(won);
-                const int nwon = __popcll(wmask);
-                if (nwon > 0) {
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(a.count_out, nwon);
-                    base = __builtin_amdgcn_readfirstlane(base);
-                    if (won) {
-                        const int q = base + __popcll(wmask & ((1ull << lane) - 1));
-                        a.list_out[2 * q] = gn;
-                        a.list_out[2 * q + 1] = slot;
+                    for (int c = 0; c < kFrontWords; ++c) fr |= sh.fresh[j][c][lane];
+                const bool last = sh.last != 0;
+                if (__ballot(fr != 0) != 0) {
+                    const int ny = ty + lane / 3 - 1, nx = tx + lane % 3 - 1;
+                    const int gn = md.tile_base + ny * md.tiles_x + nx;
+                    bool won = false;
+                    if ((lane == 4 || (last && lane < 9)) && ny >= 0 && ny < md.tiles_y && nx >= 0 && nx < md.tiles_x)
+                        won = atomicExch(&a.flags_out[gn], 1) == 0;
+                    const uint64_t wmask = __ballot(won);
+                    const int nwon = __popcll(wmask);
+                    if (nwon > 0) {
+                        int base = 0;
+                        if (lane == 0) base = atomicAdd(a.count_out, nwon);
+                        base = __builtin_amdgcn_readfirstlane(base);
+                        if (won) {
+                            const int q = base + __popcll(wmask & ((1ull << lane) - 1));
+                            a.list_out[2 * q] = gn;
+                            a.list_out[2 * q + 1] = slot;
+                        }
+                        if (!ONE && lane == 0) atomicAdd(&a.sched_out[slot], nwon);
                     }
-                    if (!one && lane == 0) atomicAdd(&a.sched_out[slot], nwon);
                 }
             }
+            lds_barrier();   // the block's LDS is reused by the next tile
+            continue;
         }
         // activity rows: lane = column of the tile
         const int c = lane >> 5, b = lane & 31;
-        for (int row = wave; row < kFrontRows; row += kFrontWaves) {
-            const bool here = (sh.fresh[c][row] >> b) & 1u;
-            if (__ballot(here) == 0) continue;
-            int t = 0;
+        // (waves 0 .. kFrontWords-1 have had their part: they take the last rows)
+        constexpr int kHelp = kFrontWords, kWriters = kFrontWaves - 1 - kHelp, kRest = 9;
+        const bool helper = wave < kHelp;
+        int row = helper ? kFrontRows - kRest + wave : wave - kHelp;
+        const int row_end = helper ? kFrontRows : kFrontRows - kRest, row_step = helper ? kHelp : kWriters;
+        for (; row < row_end; row += row_step) {
+            uint32_t f[4] = {};
 #pragma unroll
-            for (int p = 0; p < kFrontPlanes; ++p) t |= (int)((sh.plane[p][c][row] >> b) & 1u) << p;
+            for (int j = 0; j < kFrontSteps; ++j) f[j] = sh.fresh[j][c][row];
+            const bool here = ((f[0] | f[1] | f[2] | f[3]) >> b) & 1u;
+            if (__ballot(here) == 0) continue;
+            const int j = (int)(((f[1] | f[3]) >> b) & 1u) | (int)(((f[2] | f[3]) >> b) & 1u) << 1;   // its step
+            const uint4 code = sh.code[j][c][row];
+            const int t = 16 * j + (int)(((code.x >> b) & 1u) | ((code.y >> b) & 1u) << 1 | ((code.z >> b) & 1u) << 2 |
+                                         ((code.w >> b) & 1u) << 3);
             if (here && t < limit) md.V[0][(int64_t)(r0 + row) * md.pitch + j0 * 32 + lane] = base_v - t;
         }
         lds_barrier();   // the block's LDS is reused by the next tile

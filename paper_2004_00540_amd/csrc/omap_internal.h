@@ -42,6 +42,7 @@ struct MazeDev {
     const uint32_t* mask;
     uint32_t* R[2];         // front propagation: reached-set planes (mask layout), else null
     int32_t round0;         // front propagation: index of the maze's first round
+    uint32_t tiles_x_inv;   // front propagation: min(2^32 / tiles_x, 2^32 - 1) (see front_tile_row)
 };
 
 // Arguments of round r of the tile schedule.  The tile lists and their dedup

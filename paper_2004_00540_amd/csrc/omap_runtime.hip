@@ -813,6 +813,7 @@ class Solver {
         md.R[0] = s.R[0];
         md.R[1] = s.R[1];
         md.round0 = (int32_t)s.first_round;
+        md.tiles_x_inv = s.g.tiles_x > 1 ? (uint32_t)((uint64_t(1) << 32) / (uint32_t)s.g.tiles_x) : 0xffffffffu;
     }
 
     // Grow-only device staging of start_many (synchronizes only to grow; the
