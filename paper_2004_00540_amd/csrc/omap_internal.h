@@ -14,6 +14,8 @@ constexpr uint32_t kObstacleBit = 0x80000000u;      // in-register obstacle mark
 // kSpread) so that concurrent waves do not serialise on one address; readers
 // sum the copies.
 constexpr int kSpread = 16;
+// Rounds whose scheduled counts the host can look at (a ring by round).
+constexpr int kPosted = 64;
 // Bit-packed front propagation (omap_front.h): layers per tile visit, in steps
 // of 16, and the tile.
 #ifndef OMAP_FRONT_STEPS
@@ -85,6 +87,7 @@ struct RoundArgs {
     int32_t tile_rows;            // interior rows per tile
     int32_t tile_cols;            // interior columns per tile (64*C - 2T)
     int32_t dense;                // 1 = dense schedule
+    uint64_t* posted;             // pinned host memory, [kPosted] by round: round << 32 | count (or null)
     int32_t wave_stride;          // waves in the launch (set by the launch wrapper)
     MazeDev md0;                  // copy of mazes[0] when n_slots == 1 (saves a dependent load)
 };
@@ -144,7 +147,9 @@ hipError_t launch_reduce(const MazeDev* mazes, const int32_t* tile_maze, const u
                          int32_t tile_cols, int32_t parity, int32_t* maze_min,
                          unsigned long long* maze_reached, hipStream_t s);
 hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* reached, const int32_t* layer,
-                               int32_t n_slots, int32_t* maze_min, unsigned long long* maze_reached, hipStream_t s);
+                               const int32_t* last_round, const int64_t* visits, int32_t n_slots, int32_t* maze_min,
+                               unsigned long long* maze_reached, int32_t* last_out, int64_t* visits_out,
+                               hipStream_t s);
 hipError_t launch_path_lengths(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                                int32_t n_tgt, int32_t parity, int32_t* len, hipStream_t s);
 // order (optional): receives the targets by path length, longest first

@@ -252,20 +252,29 @@ __global__ __launch_bounds__(256) void k_reduce(const MazeDev* __restrict__ maze
 }
 
 // The same from the counts the front propagation's visits keep: per slot, the
-// cells reached and K minus the last layer that reached one.
+// cells reached and K minus the last layer that reached one, and if asked for
+// the last round and the tile visits (the results may be in host memory).
 __global__ void k_front_report(const MazeDev* __restrict__ mazes, const unsigned long long* __restrict__ reached,
-                               const int32_t* __restrict__ layer, int32_t n_slots, int32_t* __restrict__ maze_min,
-                               unsigned long long* __restrict__ maze_reached) {
+                               const int32_t* __restrict__ layer, const int32_t* __restrict__ last_round,
+                               const int64_t* __restrict__ visits, int32_t n_slots, int32_t* __restrict__ maze_min,
+                               unsigned long long* __restrict__ maze_reached, int32_t* __restrict__ last_out,
+                               int64_t* __restrict__ visits_out) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n_slots) return;
     unsigned long long n = 0;
+    int64_t v = 0;
     int last = 0;
     for (int k = 0; k < kSpread; ++k) {
         n += reached[s * kSpread + k];
+        v += visits[s * kSpread + k];
         last = max(last, layer[s * kSpread + k]);
     }
     maze_min[s] = mazes[s].K - last;
     maze_reached[s] = n;
+    if (last_out != nullptr) {
+        last_out[s] = last_round[s];
+        visits_out[s] = v;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -846,9 +855,11 @@ hipError_t launch_reduce(const MazeDev* mazes, const int32_t* tile_maze, const u
 }
 
 hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* reached, const int32_t* layer,
-                               int32_t n_slots, int32_t* maze_min, unsigned long long* maze_reached, hipStream_t s) {
-    hipLaunchKernelGGL(k_front_report, dim3(grid_for(n_slots, 64)), dim3(64), 0, s, mazes, reached, layer, n_slots,
-                       maze_min, maze_reached);
+                               const int32_t* last_round, const int64_t* visits, int32_t n_slots, int32_t* maze_min,
+                               unsigned long long* maze_reached, int32_t* last_out, int64_t* visits_out,
+                               hipStream_t s) {
+    hipLaunchKernelGGL(k_front_report, dim3(grid_for(n_slots, 64)), dim3(64), 0, s, mazes, reached, layer, last_round,
+                       visits, n_slots, maze_min, maze_reached, last_out, visits_out);
     return hipGetLastError();
 }
 

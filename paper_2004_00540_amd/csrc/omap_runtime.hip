@@ -26,6 +26,8 @@
 #include <unordered_map>
 #include <vector>
 
+#include <immintrin.h>
+
 #include "omap.h"
 #include "omap_internal.h"
 
@@ -568,6 +570,8 @@ class Solver {
     int32_t* d_bad = nullptr;
     int32_t* d_sel = nullptr;
     int32_t* h_pinned = nullptr;              // 64 int32 of pinned host scratch
+    uint64_t* h_posted = nullptr;             // pinned, [kPosted]: counts posted by the rounds
+    bool posting = false;                     // rounds launched now post their counts
     void* d_scratch = nullptr;                // grow-only path scratch
     size_t scratch_bytes = 0;
     int32_t* d_start_ = nullptr;              // grow-only staging of start_many
@@ -603,6 +607,12 @@ class Solver {
         start_cap_ = 0;
         if (h_pinned) (void)hipHostFree(h_pinned);
         h_pinned = nullptr;
+        if (h_posted) (void)hipHostFree(h_posted);
+        h_posted = nullptr;
+        if (h_fin_last) (void)hipHostFree(h_fin_last);
+        h_fin_last = nullptr;
+        if (h_fin_visits) (void)hipHostFree(h_fin_visits);
+        h_fin_visits = nullptr;
         if (h_bad) (void)hipHostFree(h_bad);
         h_bad = nullptr;
         if (h_fin_min) (void)hipHostFree(h_fin_min);
@@ -683,6 +693,10 @@ class Solver {
         OK_TRY(dalloc(&d_bad, 1));
         OK_TRY(dalloc(&d_sel, cap_slots));
         HIP_TRY(hipHostMalloc((void**)&h_pinned, 64 * sizeof(int32_t), hipHostMallocDefault));
+        HIP_TRY(hipHostMalloc((void**)&h_posted, kPosted * sizeof(uint64_t), hipHostMallocDefault));
+        std::memset(h_posted, 0xff, kPosted * sizeof(uint64_t));
+        HIP_TRY(hipHostMalloc((void**)&h_fin_last, sizeof(int32_t) * cap_slots, hipHostMallocDefault));
+        HIP_TRY(hipHostMalloc((void**)&h_fin_visits, sizeof(int64_t) * cap_slots, hipHostMallocDefault));
         HIP_TRY(hipHostMalloc((void**)&h_fin_min, sizeof(int32_t) * cap_slots, hipHostMallocDefault));
         HIP_TRY(hipHostMalloc((void**)&h_fin_reached, sizeof(unsigned long long) * cap_slots, hipHostMallocDefault));
         if (!pin.init(pinned_bytes)) return fail(OMAP_ERR_OUT_OF_MEMORY, "pinned staging (%zu bytes)", pinned_bytes);
@@ -755,6 +769,7 @@ class Solver {
         a.tile_rows = opt.TH;
         a.tile_cols = opt.TW;
         a.dense = opt.dense;
+        a.posted = posting ? h_posted : nullptr;
         a.md0 = h_mazes.empty() ? MazeDev() : h_mazes[0];
         return a;
     }
@@ -1266,23 +1281,70 @@ class Solver {
                 reps = std::min(reps * 2, 4);
             }
         }
-        int g = opt.check > 0 ? opt.check : 2;
-        for (;;) {
-            for (int i = 0; i < g; ++i) OK_TRY(round());
-            int32_t n = 0;
-            OK_TRY(scheduled_count(&n));
-            if (n == 0) break;
-            if (opt.check == 0) g = std::min(g * 2, 64);
+        if (opt.check > 0) {
+            for (;;) {
+                for (int i = 0; i < opt.check; ++i) OK_TRY(round());
+                int32_t n = 0;
+                OK_TRY(scheduled_count(&n));
+                if (n == 0) return OMAP_OK;
+            }
         }
-        return OMAP_OK;
+        // kAhead rounds are kept in flight; each posts the count it starts with,
+        // and the first that starts with none ends the propagation.  (The dense
+        // schedule's first round has no count: its mazes are flagged.)
+        const int64_t first = next_round + (opt.dense ? 1 : 0);
+        posting = true;
+        omap_status_t st = OMAP_OK;
+        for (int64_t r = next_round;; ++r) {
+            while (st == OMAP_OK && next_round < r + kAhead) st = round();
+            int32_t n = 1;
+            if (st == OMAP_OK && r >= first) st = posted_count(r, &n);
+            if (st != OMAP_OK || n == 0) break;
+        }
+        posting = false;
+        return st;
+    }
+
+    // Rounds in flight ahead of the last posted count: a launch takes the host
+    // about 4 us and an empty round about 3, a round with tiles 10 or more.
+    #ifndef KA
+#define KA 3
+#endif
+    static constexpr int kAhead = KA;
+
+    // The count posted by round r, waiting for it.  A stream that has drained
+    // (or failed) without posting it is an error, not a wait.
+    omap_status_t posted_count(int64_t r, int32_t* n) {
+        const volatile uint64_t* p = &h_posted[(uint32_t)r % kPosted];
+        for (int64_t spin = 1;; ++spin) {
+            const uint64_t v = *p;
+            if ((uint32_t)(v >> 32) == (uint32_t)r) {
+                *n = (int32_t)(uint32_t)v;
+                return OMAP_OK;
+            }
+            _mm_pause();
+            if (spin % 50000 == 0) {
+                const hipError_t e = hipStreamQuery(stream);
+                if (e != hipErrorNotReady) {
+                    if (e != hipSuccess) HIP_TRY(e);
+                    if ((uint32_t)(*p >> 32) == (uint32_t)r) continue;
+                    return fail(OMAP_ERR_HIP, "round %lld ended without posting its count", (long long)r);
+                }
+                (void)hipGetLastError();
+            }
+        }
     }
 
     // Enqueues the reduction of the selected slots: their smallest positive
     // activity and reached count land in h_min / h_reached (pinned host
     // arrays of cap_slots entries) once the stream gets there.
     omap_status_t finalize_enqueue(const std::vector<int32_t>& which, int32_t* h_min, unsigned long long* h_reached) {
-        if (opt.front) {   // the visits have counted as they went
-            HIP_TRY(launch_front_report(d_mazes, d_reached_copies, d_layer_copies, cap_slots, d_min, d_reached, stream));
+        if (opt.front) {   // the visits have counted as they went; straight to the host arrays
+            const bool own = h_min == h_fin_min;
+            HIP_TRY(launch_front_report(d_mazes, d_reached_copies, d_layer_copies, d_last_round, d_visits, cap_slots,
+                                        h_min, h_reached, own ? h_fin_last : nullptr, own ? h_fin_visits : nullptr,
+                                        stream));
+            return OMAP_OK;
         } else {
             HIP_TRY(launch_fill(d_min, cap_slots, 0x7fffffff, stream));
             HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(d_reached), 2 * (int64_t)cap_slots, 0, stream));
@@ -1318,6 +1380,8 @@ class Solver {
     // Pinned host arrays of the synchronous finalize (cap_slots each).
     int32_t* h_fin_min = nullptr;
     unsigned long long* h_fin_reached = nullptr;
+    int32_t* h_fin_last = nullptr;            // front propagation: last round and visits, with the above
+    int64_t* h_fin_visits = nullptr;
 
     // Smallest positive activity and reached count of the selected slots,
     // then layers = L or K - min (synchronous).
@@ -1371,21 +1435,22 @@ class Solver {
     // are used instead of reading the device.
     omap_status_t info(int32_t k, omap_propagate_info* out, bool counters_read = false) {
         OK_TRY(ensure_finalized(k));
-        if (!counters_read) {
-            OK_TRY(read_counters());
-        }
-        int64_t v[3] = {0, 0, 0};
-        for (int j = 0; j < kSpread; ++j) {
-            v[1] += h_visits[(size_t)k * kSpread + j];
-            v[2] += h_cell_visits[(size_t)k * kSpread + j];
-        }
         const Slot& s = slots[k];
-        v[0] = (int64_t)(int32_t)(h_last_round[k] - (int32_t)s.first_round) + 1;   // rounds the maze was visited
-        if (v[0] < 0) v[0] = 0;
+        int32_t last_round = 0;
+        int64_t visits = 0;
+        if (opt.front && !counters_read) {   // (finalize brought the counters along)
+            last_round = h_fin_last[k];
+            visits = h_fin_visits[k];
+        } else {
+            if (!counters_read) OK_TRY(read_counters());
+            last_round = h_last_round[k];
+            for (int j = 0; j < kSpread; ++j) visits += h_visits[(size_t)k * kSpread + j];
+        }
+        const int64_t rounds = std::max<int64_t>(0, (int64_t)(int32_t)(last_round - (int32_t)s.first_round) + 1);
         out->layers = s.layers;
-        out->rounds = v[0];
-        out->sweeps_executed = v[0] * opt.T;
-        out->tile_visits = v[1];
+        out->rounds = rounds;
+        out->sweeps_executed = rounds * opt.T;
+        out->tile_visits = visits;
         out->reached_cells = s.reached;
         return OMAP_OK;
     }

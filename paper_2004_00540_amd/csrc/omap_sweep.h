@@ -367,7 +367,14 @@ __device__ __forceinline__ void visit_bookkeeping_active(const RoundArgs& a, int
 // nothing, and the visits count the cells they update themselves.
 template <int FRONT_T, int NT = kBlockThreads>
 __device__ __forceinline__ void round_accounting(const RoundArgs& a) {
-    if (threadIdx.x == 0) *a.count_clear = 0;
+    if (threadIdx.x == 0) {
+        *a.count_clear = 0;
+        // the host watches the counts go by instead of stopping the stream to read one
+        if (a.posted != nullptr)
+            __hip_atomic_store(&a.posted[(uint32_t)a.round_id % kPosted],
+                               (uint64_t)(uint32_t)a.round_id << 32 | (uint32_t)*a.count_in, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     for (int m = threadIdx.x; m < a.n_slots; m += NT) {
         a.sched_clear[m] = 0;
         a.dchg_clear[m] = 0;
