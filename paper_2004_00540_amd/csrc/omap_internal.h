@@ -161,7 +161,8 @@ hipError_t launch_walk(const MazeDev* mazes, const int32_t* tgt_slot, const int3
                        int32_t* cells, hipStream_t s, const int32_t* order = nullptr);
 hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                               const int32_t* tgt_local, int32_t n_tgt, int32_t parity, uint64_t seed,
-                              const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s);
+                              const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s,
+                              const int32_t* order);
 hipError_t launch_walk_euclid(bool write, const MazeDev* mazes, const int32_t* tgt_slot,
                               const int32_t* tgt_rc, int32_t n_tgt, int32_t parity, int32_t* len,
                               const int64_t* offsets, int32_t* cells, hipStream_t s);

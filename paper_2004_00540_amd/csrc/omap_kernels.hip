@@ -380,11 +380,6 @@ __global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ len, 
     }
 }
 
-__device__ __forceinline__ int dir_dr(int k) { return k < 3 ? -1 : (k < 5 ? 0 : 1); }
-__device__ __forceinline__ int dir_dc(int k) {
-    return (k == 0 || k == 3 || k == 5) ? -1 : ((k == 1 || k == 6) ? 0 : 1);
-}
-
 // The walk is a chain of dependent steps, so its time is the longest path
 // times the latency of one step.  One wave follows one target through the
 // activity map from a window of kWinRows x 64 cells held in LDS (one global
@@ -417,10 +412,77 @@ constexpr int kWalkWaves = 4;
 // neighbours of block cell 9 (row 1, column 1): cells 0, 1, 2, 8, 10, 16, 17, 18
 constexpr uint64_t kNbr = 0x70507ull;
 
+// Loads the window with corner (R0, C0), C0 a multiple of 4, into a wave's LDS;
+// cells outside the grid read -1.  Every chunk's load is issued before the
+// first is used, so the window costs one global round trip.
+__device__ __forceinline__ void walk_window(const MazeDev& md, const int32_t* V, int R0, int C0, int32_t* win) {
+    const int lane = lane_id();
+    v4i32 ld[kWinChunks / kLanes];
+#pragma unroll
+    for (int k = 0; k < kWinChunks / kLanes; ++k) {
+        const int q = lane + kLanes * k;
+        const int wr = q >> 4, wc = 4 * (q & 15);
+        const int R = R0 + wr, cs = C0 + wc;
+        const bool rok = R >= 0 && R < md.H;
+        const bool cok = cs >= 0 && cs < md.pitch;   // a chunk lies wholly inside or outside a row
+        ld[k] = *(const __attribute__((address_space(1))) v4i32*)(V + (int64_t)(rok ? R : 0) * md.pitch +
+                                                                  (cok ? cs : 0));
+    }
+#pragma unroll
+    for (int k = 0; k < kWinChunks / kLanes; ++k) {
+        const int q = lane + kLanes * k;
+        const int wr = q >> 4, wc = 4 * (q & 15);
+        const int R = R0 + wr, cs = C0 + wc;
+        const bool rok = R >= 0 && R < md.H;
+        v4i32 m;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] = (rok && cs + e >= 0 && cs + e < md.W) ? ld[k][e] : -1;
+        *(__attribute__((address_space(3))) v4i32*)(win + wr * kWinCols + wc) = m;
+    }
+    // the same wave reads what its lanes wrote: LDS operations of a wave
+    // complete in order; the wave barrier keeps the compiler from moving
+    // the reads above the writes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The next window overwrites this one only after every lane's reads.
+__device__ __forceinline__ void walk_window_done() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Row and column of the current cell in its next window: the most room in the
+// direction the path last went.
+__device__ __forceinline__ int walk_row(int dr) { return dr < 0 ? kWinRows - 5 : (dr > 0 ? 3 : kWinRows / 2); }
+__device__ __forceinline__ int walk_col(int dc) { return dc < 0 ? 56 : (dc > 0 ? 3 : 30); }
+
+// Moves left before the 8 x 8 block around (lr, lc) could leave the window.
+__device__ __forceinline__ int walk_room(int lr, int lc) {
+    return min(min(lr - 3, kWinRows - 5 - lr), min(lc - 3, kWinCols - 5 - lc));
+}
+
+// The random numbers of 64 consecutive moves, lane l those of move s + l: the
+// hash modulo 1 .. 8, three bits each (modulo c at bit 3 (c - 1)).
+__device__ __forceinline__ uint32_t tie_remainders(uint64_t seed, uint64_t target, uint64_t step);
+
+// Position of the j-th set bit of m.
+__device__ __forceinline__ int nth_bit(uint64_t m, int j) {
+    for (; j > 0; --j) m &= m - 1;
+    return __builtin_ctzll(m);
+}
+
+// RANDOM: among a cell's maximal neighbours, those holding v0 + 1, the one at
+// position hash mod count in the fixed order is taken, not the first; the
+// hashes of 64 moves are computed together, one per lane.
+template <bool RANDOM>
 __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
     const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot, const int32_t* __restrict__ trc,
     int32_t n, int32_t parity, const int32_t* __restrict__ len, const int64_t* __restrict__ off,
-    int32_t* __restrict__ cells, const int32_t* __restrict__ order) {
+    int32_t* __restrict__ cells, const int32_t* __restrict__ order, const int32_t* __restrict__ tlocal,
+    uint64_t seed) {
     __shared__ __attribute__((aligned(16))) int32_t win_all[kWalkWaves][kWinRows * kWinCols];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id();
@@ -441,6 +503,14 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
     int64_t o = off[i];
     if (lane == 0) cells[o] = r * md.W + c;
     ++o;
+    const uint64_t target = RANDOM ? (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(tlocal[i]) : 0;
+    // the set bit of m that the path's next move takes (k: moves since the
+    // remainders were computed)
+    auto choose = [&](uint64_t m, uint32_t ties, int k) {
+        if (!RANDOM) return __builtin_ctzll(m);
+        const uint32_t rem = (uint32_t)__builtin_amdgcn_readlane((int)ties, k);
+        return nth_bit(m, (int)((rem >> (3 * (__popcll(m) - 1))) & 7u));
+    };
     // the cells of a window's steps are logged one iteration (three steps)
     // per lane (lane k: iteration k of the window) as (window position of the
     // iteration's 8 x 8 block centre) << 18 | q1 << 12 | q2 << 6 | q3 (the
@@ -449,41 +519,8 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
     int dr_prev = 0, dc_prev = 0;   // displacement over the previous window
     int v0 = 0;
     for (int s = 0; s < steps;) {
-        // place the window: the current cell at row lr, column lc, with the
-        // most room in the direction the path last went
-        const int lr0 = dr_prev < 0 ? kWinRows - 5 : (dr_prev > 0 ? 3 : kWinRows / 2);
-        const int lc0 = dc_prev < 0 ? 56 : (dc_prev > 0 ? 3 : 30);
-        const int R0 = r - lr0, C0 = (c - lc0) & ~3;
-        // every chunk's load is issued before the first is used, so the
-        // window costs one global round trip
-        v4i32 ld[kWinChunks / kLanes];
-#pragma unroll
-        for (int k = 0; k < kWinChunks / kLanes; ++k) {
-            const int q = lane + kLanes * k;
-            const int wr = q >> 4, wc = 4 * (q & 15);
-            const int R = R0 + wr, cs = C0 + wc;
-            const bool rok = R >= 0 && R < md.H;
-            const bool cok = cs >= 0 && cs < md.pitch;   // a chunk lies wholly inside or outside a row
-            ld[k] = *(const __attribute__((address_space(1))) v4i32*)(V + (int64_t)(rok ? R : 0) * md.pitch +
-                                                                      (cok ? cs : 0));
-        }
-#pragma unroll
-        for (int k = 0; k < kWinChunks / kLanes; ++k) {
-            const int q = lane + kLanes * k;
-            const int wr = q >> 4, wc = 4 * (q & 15);
-            const int R = R0 + wr, cs = C0 + wc;
-            const bool rok = R >= 0 && R < md.H;
-            v4i32 m;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) m[e] = (rok && cs + e >= 0 && cs + e < md.W) ? ld[k][e] : -1;
-            *(__attribute__((address_space(3))) v4i32*)(win + wr * kWinCols + wc) = m;
-        }
-        // the same wave reads what its lanes wrote: LDS operations of a wave
-        // complete in order; the wave barrier keeps the compiler from moving
-        // the reads above the writes
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int R0 = r - walk_row(dr_prev), C0 = (c - walk_col(dc_prev)) & ~3;
+        walk_window(md, V, R0, C0, win);
         int lr = r - R0, lc = c - C0;
         if (s == 0) v0 = __builtin_amdgcn_readfirstlane(win[lr * kWinCols + lc]);
         const int s_start = s;
@@ -492,19 +529,21 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
         // iterations all start with their 8 x 8 block inside the window; the
         // bounds are checked once per such run.
         for (;;) {
-            const int room = min(min(lr - 3, kWinRows - 5 - lr), min(lc - 3, kWinCols - 5 - lc));
+            const int room = walk_room(lr, lc);
             int n = room < 0 ? 0 : room / 3 + 1;
             n = min(n, min((steps - s) / 3, kLanes - it));
+            if (RANDOM) n = min(n, kLanes / 3);
             if (n <= 0) break;
+            const uint32_t ties = RANDOM ? tie_remainders(seed, target, (uint64_t)s) : 0;
             for (int k = 0; k < n; ++k) {
                 const int pos = lr * kWinCols + lc;
                 const int d = win[pos + my_off] - v0;
                 const uint64_t m1 = __ballot(d == 1);
                 const uint64_t m2 = __ballot(d == 2);
                 const uint64_t m3 = __ballot(d == 3);
-                const int q1 = __builtin_ctzll(m1 & (kNbr << 18));   // neighbours of the centre, cell 27
-                const int q2 = __builtin_ctzll(m2 & (kNbr << (q1 - 9)));
-                const int q3 = __builtin_ctzll(m3 & (kNbr << (q2 - 9)));
+                const int q1 = choose(m1 & (kNbr << 18), ties, 3 * k);   // neighbours of the centre, cell 27
+                const int q2 = choose(m2 & (kNbr << (q1 - 9)), ties, 3 * k + 1);
+                const int q3 = choose(m3 & (kNbr << (q2 - 9)), ties, 3 * k + 2);
                 const int e = (pos << 18) | (q1 << 12) | (q2 << 6) | q3;
                 log = lane == it + k ? e : log;
                 lr += (q3 >> 3) - 3;
@@ -515,15 +554,15 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
             s += 3 * n;
         }
         // the path's last one or two steps, once their block fits
-        if (s < steps && steps - s < 3 && it < kLanes && lr >= 3 && lr <= kWinRows - 5 && lc >= 3 &&
-            lc <= kWinCols - 5) {
+        if (s < steps && steps - s < 3 && it < kLanes && walk_room(lr, lc) >= 0) {
+            const uint32_t ties = RANDOM ? tie_remainders(seed, target, (uint64_t)s) : 0;
             const int pos = lr * kWinCols + lc;
             const int d = win[pos + my_off] - v0;
             const uint64_t m1 = __ballot(d == 1);
             const uint64_t m2 = __ballot(d == 2);
             const int todo = steps - s;
-            const int q1 = __builtin_ctzll(m1 & (kNbr << 18));
-            const int q2 = todo > 1 ? __builtin_ctzll(m2 & (kNbr << (q1 - 9))) : 0;
+            const int q1 = choose(m1 & (kNbr << 18), ties, 0);
+            const int q2 = todo > 1 ? choose(m2 & (kNbr << (q1 - 9)), ties, 1) : 0;
             const int q = todo > 1 ? q2 : q1;
             log = lane == it ? (pos << 18) | (q1 << 12) | (q2 << 6) : log;
             ++it;
@@ -552,10 +591,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
         if (3 * abs(dc_prev) < nst) dc_prev = 0;
         r = R0 + lr;
         c = C0 + lc;
-        // the next window overwrites this one only after every lane's reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        walk_window_done();
     }
 }
 
@@ -571,48 +607,13 @@ __device__ __forceinline__ uint64_t tie_hash(uint64_t seed, uint64_t target, uin
     return z ^ (z >> 31);
 }
 
-__device__ __forceinline__ int read_or(const int32_t* V, const MazeDev& md, int r, int c, int outside) {
-    return (r >= 0 && r < md.H && c >= 0 && c < md.W) ? V[(int64_t)r * md.pitch + c] : outside;
-}
-
-// Simple reconstruction with random ties: at move s of target t (t = index in
-// its maze's target list) the maximal 8-neighbours are counted in the fixed
-// order and the one at position tie_hash(seed, t, s) mod count is taken.
-__global__ void k_walk_random(const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot,
-                              const int32_t* __restrict__ trc, const int32_t* __restrict__ tlocal,
-                              int32_t n, int32_t parity, uint64_t seed, const int32_t* __restrict__ len,
-                              const int64_t* __restrict__ off, int32_t* __restrict__ cells) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int steps = len[i];
-    if (steps < 0) return;
-    const MazeDev md = mazes[tslot[i]];
-    const int32_t* __restrict__ V = parity ? md.V[1] : md.V[0];
-    int r = trc[2 * i], c = trc[2 * i + 1];
-    int64_t o = off[i];
-    cells[o++] = r * md.W + c;
-    const uint64_t t = (uint64_t)tlocal[i];
-    for (int s = 0; s < steps; ++s) {
-        int nv[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) nv[k] = read_or(V, md, r + dir_dr(k), c + dir_dc(k), -1);
-        int bv = nv[0];
-#pragma unroll
-        for (int k = 1; k < 8; ++k) bv = max(bv, nv[k]);
-        int cnt = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) cnt += nv[k] == bv;
-        int j = (int)(tie_hash(seed, t, (uint64_t)s) % (uint64_t)cnt);
-        int pick = 0;
-#pragma unroll
-        for (int k = 7; k >= 0; --k)
-            if (nv[k] == bv) {      // walk maxima from the last: ends on the j-th in order
-                if (--cnt == j) pick = k;
-            }
-        r += dir_dr(pick);
-        c += dir_dc(pick);
-        cells[o++] = r * md.W + c;
-    }
+__device__ __forceinline__ uint32_t tie_remainders(uint64_t seed, uint64_t target, uint64_t step) {
+    const uint64_t z = tie_hash(seed, target, step + (uint64_t)lane_id());
+    const uint32_t lo = (uint32_t)z, hi = (uint32_t)(z >> 32);
+    // 2^32 is 1 modulo 3 and 5, and 4 modulo 7
+    const uint32_t m3 = (lo % 3 + hi % 3) % 3, m5 = (lo % 5 + hi % 5) % 5, m7 = (lo % 7 + 4 * (hi % 7)) % 7;
+    const uint32_t m6 = m3 + 3 * ((m3 ^ lo) & 1);   // m3 or m3 + 3, whichever has the parity of z
+    return (lo & 1) << 3 | m3 << 6 | (lo & 3) << 9 | m5 << 12 | m6 << 15 | m7 << 18 | (lo & 7) << 21;
 }
 
 // Euclidean reconstruction (Eq. 1 and straightening).  The walk climbs through
@@ -622,78 +623,105 @@ __global__ void k_walk_random(const MazeDev* __restrict__ mazes, const int32_t* 
 // whose predecessor and successor are diagonal neighbours) runs on the fly.
 // WRITE = false counts the final points (len = points - 1, -1 if no path);
 // WRITE = true writes them at off[i].
+//
+// One wave per target, from the same windows and 8 x 8 blocks as k_walk: a
+// block serves three moves, with ballots of the cells holding v .. v + 3 (a
+// cell's maximal 4-neighbour holds v + 1, v or less, its maximal 8-neighbour
+// v + 1).  Everything but the block's read and the ballots is scalar.  A
+// lane per target reading its neighbours from memory took 0.9 us per move.
+constexpr uint64_t kNbr4 = 0x20502ull;   // up, left, right, down of block cell 9: cells 1, 8, 10, 17
+
 template <bool WRITE>
-__global__ void k_walk_euclid(const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot,
-                              const int32_t* __restrict__ trc, int32_t n, int32_t parity,
-                              int32_t* __restrict__ len, const int64_t* __restrict__ off,
-                              int32_t* __restrict__ cells) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
+    const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot, const int32_t* __restrict__ trc, int32_t n,
+    int32_t parity, int32_t* __restrict__ len, const int64_t* __restrict__ off, int32_t* __restrict__ cells) {
+    __shared__ __attribute__((aligned(16))) int32_t win_all[kWalkWaves][kWinRows * kWinCols];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = lane_id();
+    const int i = blockIdx.x * kWalkWaves + wave;
     if (i >= n) return;
-    const MazeDev md = mazes[tslot[i]];
+    const int slot = __builtin_amdgcn_readfirstlane(tslot[i]);
+    const MazeDev md = mazes[slot];
     const int32_t* __restrict__ V = parity ? md.V[1] : md.V[0];
-    int r = trc[2 * i], c = trc[2 * i + 1];
-    int v = V[(int64_t)r * md.pitch + c];
+    int32_t* win = win_all[wave];
+    const int my_off = ((lane >> 3) - 3) * kWinCols + ((lane & 7) - 3);
+    int r = __builtin_amdgcn_readfirstlane(trc[2 * i]);
+    int c = __builtin_amdgcn_readfirstlane(trc[2 * i + 1]);
+    int v = __builtin_amdgcn_readfirstlane(V[(int64_t)r * md.pitch + c]);
     if (v <= 0) {
-        if (!WRITE) len[i] = -1;
+        if (!WRITE && lane == 0) len[i] = -1;
         return;
     }
-    if (WRITE && len[i] < 0) return;
     int64_t o = WRITE ? off[i] : 0;
-    int32_t count = 1;
-    if (WRITE) cells[o++] = r * md.W + c;
-    int kr = r, kc = c;            // last kept point
-    int pr = -1, pc = -1;          // pending point (not yet decided)
-    bool sideways_before = false;
-    while (v != md.K) {
-        // 4-neighbours: up, left, right, down
-        const int u = read_or(V, md, r - 1, c, -1), l = read_or(V, md, r, c - 1, -1);
-        const int rt = read_or(V, md, r, c + 1, -1), dn = read_or(V, md, r + 1, c, -1);
-        int b4 = u, dr = -1, dc = 0;
-        if (l > b4) { b4 = l; dr = 0; dc = -1; }
-        if (rt > b4) { b4 = rt; dr = 0; dc = 1; }
-        if (dn > b4) { b4 = dn; dr = 1; dc = 0; }
-        if (b4 > v) {
-            sideways_before = false;
-        } else if (b4 == v && !sideways_before) {
-            sideways_before = true;
-        } else {
-            int nv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) nv[k] = read_or(V, md, r + dir_dr(k), c + dir_dc(k), -1);
-            int best = 0, bv = nv[0];
-#pragma unroll
-            for (int k = 1; k < 8; ++k)
-                if (nv[k] > bv) {
-                    bv = nv[k];
-                    best = k;
-                }
-            b4 = bv;
-            dr = dir_dr(best);
-            dc = dir_dc(best);
-            sideways_before = false;
-        }
-        r += dr;
-        c += dc;
-        v = b4;
-        // straightening: the pending point is dropped when the last kept point
-        // and the new point are diagonal neighbours
-        if (pr >= 0) {
-            const int ar = kr > r ? kr - r : r - kr, ac = kc > c ? kc - c : c - kc;
-            if (!(ar == 1 && ac == 1)) {
-                if (WRITE) cells[o++] = pr * md.W + pc;
-                ++count;
-                kr = pr;
-                kc = pc;
+    // kept points: lane k holds the k-th of those not yet stored
+    int kept = 0, count = 0;
+    auto keep = [&](int pr, int pc) {
+        if (WRITE) {
+            kept = lane == (count & (kLanes - 1)) ? pr * md.W + pc : kept;
+            if ((count & (kLanes - 1)) == kLanes - 1) {
+                cells[o + lane] = kept;
+                o += kLanes;
             }
         }
-        pr = r;
-        pc = c;
-    }
-    if (pr >= 0) {
-        if (WRITE) cells[o++] = pr * md.W + pc;
         ++count;
+    };
+    keep(r, c);
+    int kr = r, kc = c;     // last kept point
+    int pr = -1, pc = -1;   // pending point (not yet decided)
+    bool sideways_before = false;
+    int dr_prev = 0, dc_prev = 0;
+    while (v != md.K) {
+        const int R0 = r - walk_row(dr_prev), C0 = (c - walk_col(dc_prev)) & ~3;
+        walk_window(md, V, R0, C0, win);
+        const int r_in = r, c_in = c;
+        int moves = 0;
+        while (v != md.K && walk_room(r - R0, c - C0) >= 0) {
+            const int d = win[(r - R0) * kWinCols + (c - C0) + my_off] - v;
+            uint64_t m0 = __ballot(d == 0), m1 = __ballot(d == 1), m2 = __ballot(d == 2), m3 = __ballot(d == 3);
+            const int br = r - 3, bc = c - 3;   // the block's corner
+            int q = 27;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const uint64_t up4 = m1 & (kNbr4 << (q - 9)), side = m0 & (kNbr4 << (q - 9));
+                const bool sideways = up4 == 0 && side != 0 && !sideways_before;
+                q = __builtin_ctzll(up4 != 0 ? up4 : (sideways ? side : m1 & (kNbr << (q - 9))));
+                sideways_before = sideways;
+                if (!sideways) {
+                    m0 = m1;
+                    m1 = m2;
+                    m2 = m3;
+                    ++v;
+                }
+                ++moves;
+                r = br + (q >> 3);
+                c = bc + (q & 7);
+                // straightening: the pending point is dropped when the last kept point
+                // and the new point are diagonal neighbours
+                if (pr >= 0) {
+                    const int ar = kr > r ? kr - r : r - kr, ac = kc > c ? kc - c : c - kc;
+                    if (!(ar == 1 && ac == 1)) {
+                        keep(pr, pc);
+                        kr = pr;
+                        kc = pc;
+                    }
+                }
+                pr = r;
+                pc = c;
+                if (v == md.K) break;
+            }
+        }
+        dr_prev = r - r_in;
+        dc_prev = c - c_in;
+        if (3 * abs(dr_prev) < moves) dr_prev = 0;
+        if (3 * abs(dc_prev) < moves) dc_prev = 0;
+        walk_window_done();
     }
-    if (!WRITE) len[i] = count - 1;
+    if (pr >= 0) keep(pr, pc);
+    if (WRITE) {
+        if (lane < (count & (kLanes - 1))) cells[o + lane] = kept;
+    } else if (lane == 0) {
+        len[i] = count - 1;
+    }
 }
 
 // Index (in its maze's source list) of the source each path ends on; -1 if no
@@ -880,17 +908,18 @@ hipError_t launch_walk(const MazeDev* mazes, const int32_t* tgt_slot, const int3
                        int32_t n_tgt, int32_t parity, const int32_t* len, const int64_t* offsets,
                        int32_t* cells, hipStream_t s, const int32_t* order) {
     if (n_tgt <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_walk, dim3((n_tgt + kWalkWaves - 1) / kWalkWaves), dim3(kLanes * kWalkWaves), 0, s,
-                       mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order);
+    hipLaunchKernelGGL(k_walk<false>, dim3((n_tgt + kWalkWaves - 1) / kWalkWaves), dim3(kLanes * kWalkWaves), 0, s,
+                       mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order, nullptr, 0);
     return hipGetLastError();
 }
 
 hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                               const int32_t* tgt_local, int32_t n_tgt, int32_t parity, uint64_t seed,
-                              const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s) {
+                              const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s,
+                              const int32_t* order) {
     if (n_tgt <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_walk_random, dim3(grid_for(n_tgt, 64)), dim3(64), 0, s, mazes, tgt_slot, tgt_rc,
-                       tgt_local, n_tgt, parity, seed, len, offsets, cells);
+    hipLaunchKernelGGL(k_walk<true>, dim3((n_tgt + kWalkWaves - 1) / kWalkWaves), dim3(kLanes * kWalkWaves), 0, s,
+                       mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order, tgt_local, seed);
     return hipGetLastError();
 }
 
@@ -898,12 +927,13 @@ hipError_t launch_walk_euclid(bool write, const MazeDev* mazes, const int32_t* t
                               const int32_t* tgt_rc, int32_t n_tgt, int32_t parity, int32_t* len,
                               const int64_t* offsets, int32_t* cells, hipStream_t s) {
     if (n_tgt <= 0) return hipSuccess;
+    const dim3 grid((n_tgt + kWalkWaves - 1) / kWalkWaves), block(kLanes * kWalkWaves);
     if (write)
-        hipLaunchKernelGGL(k_walk_euclid<true>, dim3(grid_for(n_tgt, 64)), dim3(64), 0, s, mazes, tgt_slot,
-                           tgt_rc, n_tgt, parity, len, offsets, cells);
+        hipLaunchKernelGGL(k_walk_euclid<true>, grid, block, 0, s, mazes, tgt_slot, tgt_rc, n_tgt, parity, len,
+                           offsets, cells);
     else
-        hipLaunchKernelGGL(k_walk_euclid<false>, dim3(grid_for(n_tgt, 64)), dim3(64), 0, s, mazes, tgt_slot,
-                           tgt_rc, n_tgt, parity, len, offsets, cells);
+        hipLaunchKernelGGL(k_walk_euclid<false>, grid, block, 0, s, mazes, tgt_slot, tgt_rc, n_tgt, parity, len,
+                           offsets, cells);
     return hipGetLastError();
 }
 

@@ -1530,7 +1530,7 @@ class Solver {
                 else
                     HIP_TRY(launch_path_lengths(d_mazes, d.tslot, d.trc, n, vparity(), d.len, stream));
             }
-            HIP_TRY(launch_scan_offsets(d.len, n, d.off, stream, mode == 0 ? d.order : nullptr));
+            HIP_TRY(launch_scan_offsets(d.len, n, d.off, stream, mode != 2 ? d.order : nullptr));
             return OMAP_OK;
         };
         OK_TRY(lengths(q));
@@ -1558,7 +1558,8 @@ class Solver {
         if (mode == 2)
             HIP_TRY(launch_walk_euclid(true, d_mazes, q.tslot, q.trc, n, vparity(), q.len, q.off, walk_dst, stream));
         else if (mode == 1)
-            HIP_TRY(launch_walk_random(d_mazes, q.tslot, q.trc, q.tlocal, n, vparity(), seed, q.len, q.off, walk_dst, stream));
+            HIP_TRY(launch_walk_random(d_mazes, q.tslot, q.trc, q.tlocal, n, vparity(), seed, q.len, q.off, walk_dst, stream,
+                                       q.order));
         else
             HIP_TRY(launch_walk(d_mazes, q.tslot, q.trc, n, vparity(), q.len, q.off, walk_dst, stream, q.order));
         const hipMemcpyKind kind = host_out ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
