@@ -88,8 +88,9 @@ typedef enum omap_status {
 
 /* Execution options.  Zero-initialised = tuned defaults.  No option changes a
  * result: activity maps and paths are identical bit for bit for every value.
- * A plan's default (active, 16 layers, 16 rows, 1 column per lane) runs on the
- * same bit-packed kernel as OMAP_SCHEDULE_BITS. */
+ * A plan's default (active, 16 layers, 16 rows, 1 column per lane) and the
+ * dense schedule's (16 layers, 256 rows, 4 columns per lane) run on the same
+ * bit-packed kernel as OMAP_SCHEDULE_BITS. */
 typedef struct omap_options {
     int32_t temporal_depth;  /* layers applied per tile visit: 4, 8, 12, 16 (and 24, 32    */
                              /* with lane_columns = 2; bit-sliced: 8, 16); 0 = default     */

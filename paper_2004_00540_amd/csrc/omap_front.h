@@ -34,6 +34,9 @@
 // word; each step's planes and arrivals are kept in LDS, and at the end the
 // waves write activity rows from them, one lane per column.
 //
+// Dense schedule: every tile of a maze that changed in the round before, no
+// lists and no claims; a tile that gained a cell flags its maze.
+//
 // Scheduling.  A cell reached before the last layer of a round has all its free
 // neighbours reached by the end of the round, so only cells reached in
 // the last layer are a front that moves on: a tile with such a cell schedules
@@ -194,7 +197,7 @@ __device__ __forceinline__ int front_tile_row(const MazeDev& md, int lt) {
 // One round: T = kFrontLayers layers of every listed tile.  ONE: a single maze,
 // described in the arguments (copying either description into one variable
 // kept both in scalar registers, and their spills cost 0.9 us of a round).
-template <bool ONE>
+template <bool ONE, bool DENSE>
 __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
     // first list entry and count issued before anything else (see k_sweep)
     int i = (int)blockIdx.x - 1;   // block 0: the accounting block
@@ -222,20 +225,25 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
     __shared__ FrontShared sh;
     constexpr int RR = kFrontRegionRows, RW = kFrontRegionWords;
     const int stride = a.wave_stride;
-    const int n = __builtin_amdgcn_readfirstlane(cnt);
+    const int n = DENSE ? a.n_tile_ids : __builtin_amdgcn_readfirstlane(cnt);
     for (; i < n; i += stride) {
+        if (DENSE) {
+            const int s = a.tile_maze[i];
+            if (s < 0 || __builtin_amdgcn_readfirstlane(a.dchg_prev[s]) == 0) continue;
+            e = (uint64_t)(uint32_t)s << 32 | (uint32_t)i;
+        }
         // (opaque to the compiler, which would otherwise compute everything that
         // depends on the lane alone before the loop, ahead of the first visit's loads)
         int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
         asm volatile("" : "+s"(wave), "+v"(lane));
         const int g = __builtin_amdgcn_readfirstlane((int)(uint32_t)e);
         const int slot = __builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32));
-        if (i + stride < n) e = *reinterpret_cast<const uint64_t*>(a.list_in + 2 * (i + stride));
+        if (!DENSE && i + stride < n) e = *reinterpret_cast<const uint64_t*>(a.list_in + 2 * (i + stride));
         const MazeDev& md = ONE ? a.md0 : a.mazes[slot];
         const int64_t n0 = (int64_t)(a.round_id - md.round0) * kFrontLayers;   // layers done before this round
         const int64_t left = (int64_t)md.K - 1 - n0;                           // layers the maze still has
         if (left <= 0) {   // every layer below K is done
-            if (threadIdx.x == 0) a.flags_in[g] = 0;
+            if (!DENSE && threadIdx.x == 0) a.flags_in[g] = 0;
             continue;
         }
         const int limit = left < kFrontLayers ? (int)left : kFrontLayers;
@@ -263,7 +271,11 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
             }
         }
         if (threadIdx.x == 0) {   // (the touched flag is set by a tile that gained a cell)
-            a.flags_in[g] = 0;
+            if (DENSE)
+                atomicAdd(reinterpret_cast<unsigned long long*>(
+                              &a.maze_visits[slot * kSpread + (blockIdx.x & (kSpread - 1))]), 1ull);
+            else
+                a.flags_in[g] = 0;
             a.maze_last_round[slot] = a.round_id;
         }
         for (int t = threadIdx.x; t < kFrontSteps * kFrontWords * kFrontRows; t += kFrontThreads)
@@ -360,7 +372,12 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
 #pragma unroll
                     for (int c = 0; c < kFrontWords; ++c) fr |= sh.fresh[j][c][lane];
                 const bool last = sh.last != 0;
-                if (__ballot(fr != 0) != 0) {
+                if (DENSE) {
+                    if (__ballot(fr != 0) != 0 && lane == 0) {
+                        a.dchg_cur[slot] = 1;
+                        *a.count_out = 1;
+                    }
+                } else if (__ballot(fr != 0) != 0) {
                     const int ny = ty + lane / 3 - 1, nx = tx + lane % 3 - 1;
                     const int gn = md.tile_base + ny * md.tiles_x + nx;
                     bool won = false;

@@ -200,11 +200,13 @@ static void use_front(Options* r) {
 }
 
 // Which kernel runs an option set.  The bit-packed front propagation (k_front)
-// serves the bit-sliced schedule and the active schedule as a single maze has
-// it by default (one column per lane, 16 layers, 16-row tiles); it applies 64
-// layers to a tile in the time the integer sweep takes for 16.  The other
-// shapes of the active schedule and the dense one run the integer sweeps; the dense
-// schedule is throughput-bound: 4 columns per lane, 16 layers, tall tiles.
+// serves the bit-sliced schedule and the default shapes of the active schedule
+// of a single maze (one column per lane, 16 layers, 16-row tiles) and of the
+// dense one (4 columns, 16 layers, 256 rows); it applies 64 layers to a tile in
+// the time the integer sweep takes for 16, and keeps a bit per cell where that
+// keeps 4 bytes (2000^2 x 2000 layers, dense: 22 ms with the integer sweep,
+// whose 72 tall tiles occupy 72 of 1024 SIMDs).  A shape asked for by other
+// values runs the integer sweep of that shape.
 enum class Use { kPlan, kMany };
 static omap_status_t resolve_options(const omap_options* o, Options* out, Use use = Use::kPlan) {
     Options r;
@@ -277,7 +279,7 @@ static omap_status_t resolve_options(const omap_options* o, Options* out, Use us
         return fail(OMAP_ERR_INVALID_ARG, "tile_rows (%d) must be >= temporal_depth (%d)", r.TH, r.T);
     r.TW = 64 * r.C - 2 * r.T;
     report_options(&r, schedule, r.C);
-    if (single && !dense && r.C == 1 && r.T == 16 && r.TH == 16) use_front(&r);
+    if (dense ? (r.C == 4 && r.T == 16 && r.TH == 256) : (single && r.C == 1 && r.T == 16 && r.TH == 16)) use_front(&r);
     *out = r;
     return OMAP_OK;
 }

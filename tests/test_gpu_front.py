@@ -25,6 +25,15 @@ def test_front_edges(shape, density):
         assert_same(m, run_plan(m, L), oracle_solution(m, L), f"front {shape} density={density} L={L}")
 
 
+@pytest.mark.parametrize("shape", [(1, 1), (64, 64), (65, 129), (191, 257), (40, 700)])
+def test_front_dense_schedule(shape):
+    """Every tile in every round until the maze stops changing."""
+    H, W = shape
+    m = workloads.random_maze(H, W, 0.3, 2, 12, 4300 + 3 * H + W)
+    for L in LAYERS:
+        assert_same(m, run_plan(m, L, schedule=2), oracle_solution(m, L), f"front dense {shape} L={L}")
+
+
 @pytest.mark.parametrize("corner", [(0, 0), (63, 63), (64, 64), (127, 64), (128, 129)])
 def test_front_straight_into_every_neighbour(corner):
     """One source at a tile's corner on an empty map: the front enters the
@@ -36,12 +45,13 @@ def test_front_straight_into_every_neighbour(corner):
         assert_same(m, run_plan(m, L), oracle_solution(m, L), f"corner {corner} L={L}")
 
 
-def test_front_batch_of_mixed_layer_counts_and_reuse():
+@pytest.mark.parametrize("schedule", [0, 2])
+def test_front_batch_of_mixed_layer_counts_and_reuse(schedule):
     """Mazes that end in different rounds, propagated again with other counts
     (the planes of a tile last visited in an odd round are cleared too)."""
     import paper_2004_00540_amd as omap
     ms = [workloads.random_maze(30 + 37 * i, 333 - 31 * i, 0.3, 1 + i % 3, 9, 4200 + i) for i in range(9)]
-    with omap.Batch([(to_dev(m.occ), m.sources, m.targets) for m in ms]) as b:
+    with omap.Batch([(to_dev(m.occ), m.sources, m.targets) for m in ms], schedule=schedule) as b:
         for rep in range(3):
             layers = [(-1, 3 + 20 * i, 64, 128, 70 + i)[(i + rep) % 5] for i in range(len(ms))]
             infos = b.propagate(layers)
