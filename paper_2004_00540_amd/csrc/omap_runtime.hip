@@ -22,6 +22,7 @@
 #include <new>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <unistd.h>
 #include <unordered_map>
 #include <vector>
@@ -584,6 +585,7 @@ class Solver {
     int parity = 0;                           // next_round mod 2: activity buffer holding the latest values
     int grid = 0;
     std::vector<void*> owned;                 // solver-level device allocations
+    size_t schedule_bytes = 0;                // counts, scheduled counts and flags, from d_count on
 
     // profiling of the sweep kernel
     bool prof = false;
@@ -607,20 +609,6 @@ class Solver {
         if (d_start_) (void)hipFree(d_start_);
         d_start_ = nullptr;
         start_cap_ = 0;
-        if (h_pinned) (void)hipHostFree(h_pinned);
-        h_pinned = nullptr;
-        if (h_posted) (void)hipHostFree(h_posted);
-        h_posted = nullptr;
-        if (h_fin_last) (void)hipHostFree(h_fin_last);
-        h_fin_last = nullptr;
-        if (h_fin_visits) (void)hipHostFree(h_fin_visits);
-        h_fin_visits = nullptr;
-        if (h_bad) (void)hipHostFree(h_bad);
-        h_bad = nullptr;
-        if (h_fin_min) (void)hipHostFree(h_fin_min);
-        h_fin_min = nullptr;
-        if (h_fin_reached) (void)hipHostFree(h_fin_reached);
-        h_fin_reached = nullptr;
         for (auto& e : prof_events) {
             (void)hipEventDestroy(e.first);
             (void)hipEventDestroy(e.second);
@@ -670,50 +658,63 @@ class Solver {
         slots.assign(cap_slots, Slot());
         free_tiles.clear();
         free_tiles[0] = cap_tiles;
-        OK_TRY(dalloc(&d_mazes, cap_slots));
-        OK_TRY(dalloc(&d_tile_maze, cap_tiles));
-        OK_TRY(dalloc(&d_list[0], 2 * (size_t)cap_tiles));   // (tile id, slot) pairs
-        OK_TRY(dalloc(&d_list[1], 2 * (size_t)cap_tiles));
-        OK_TRY(dalloc(&d_count, 3));
-        OK_TRY(dalloc(&d_flags[0], cap_tiles));
-        OK_TRY(dalloc(&d_flags[1], cap_tiles));
-        OK_TRY(dalloc(&d_sched, 3 * (size_t)cap_slots));
-        OK_TRY(dalloc(&d_dchg, 3 * (size_t)cap_slots));
-        OK_TRY(dalloc(&d_last_round, cap_slots));
-        OK_TRY(dalloc(&d_touched, cap_tiles));
-        OK_TRY(dalloc(&d_bad_slot, cap_slots));
-        HIP_TRY(hipHostMalloc((void**)&h_bad, sizeof(int32_t) * cap_slots, hipHostMallocDefault));
+        // One device block for the tables and one pinned block for the host's side
+        // (a hipHostMalloc costs 23 us, so seven of them were a third of a small plan's
+        // creation).  The zeroed tables come first, the schedule's (reset before
+        // a propagation) at the very front.
+        const size_t S = (size_t)cap_slots, N = (size_t)cap_tiles;
+        char* base = nullptr;
+        size_t at = 0, zeroed = 0;
+        auto table = [&](auto** q, size_t n) {
+            typedef typename std::remove_pointer<typename std::remove_reference<decltype(*q)>::type>::type T;
+            if (base) *q = reinterpret_cast<T*>(base + at);
+            at = (at + n * sizeof(T) + 255) & ~size_t(255);
+        };
+        auto lay_out = [&]() {
+            at = 0;
+            table(&d_count, 3);
+            table(&d_sched, 3 * S);
+            table(&d_dchg, 3 * S);
+            table(&d_flags[0], N);
+            table(&d_flags[1], N);
+            schedule_bytes = at;
+            table(&d_last_round, S);
+            table(&d_bad_slot, S);
+            table(&d_visits, S * kSpread);
+            table(&d_cell_visits, S * kSpread);
+            table(&d_total_cells, kSpread);
+            table(&d_reached_copies, S * kSpread);
+            table(&d_layer_copies, S * kSpread);
+            table(&d_touched, N);
+            table(&d_bad, 1);
+            zeroed = at;
+            table(&d_mazes, S);
+            table(&d_tile_maze, N);          // (written for the tile ids that are handed out)
+            table(&d_list[0], 2 * N);        // (tile id, slot) pairs
+            table(&d_list[1], 2 * N);
+            table(&d_min, S);
+            table(&d_reached, S);
+            table(&d_sel, S);
+        };
+        lay_out();
+        OK_TRY(dalloc(&base, at));
+        lay_out();
+        HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(base), (int64_t)(zeroed / 4), 0, stream));
         h_mazes.assign(cap_slots, MazeDev());
         h_tile_maze.assign(cap_tiles, -1);
-        OK_TRY(dalloc(&d_visits, (size_t)cap_slots * kSpread));
-        OK_TRY(dalloc(&d_cell_visits, (size_t)cap_slots * kSpread));
-        OK_TRY(dalloc(&d_total_cells, kSpread));
-        OK_TRY(dalloc(&d_reached_copies, (size_t)cap_slots * kSpread));
-        OK_TRY(dalloc(&d_layer_copies, (size_t)cap_slots * kSpread));
-        OK_TRY(dalloc(&d_min, cap_slots));
-        OK_TRY(dalloc(&d_reached, cap_slots));
-        OK_TRY(dalloc(&d_bad, 1));
-        OK_TRY(dalloc(&d_sel, cap_slots));
-        HIP_TRY(hipHostMalloc((void**)&h_pinned, 64 * sizeof(int32_t), hipHostMallocDefault));
-        HIP_TRY(hipHostMalloc((void**)&h_posted, kPosted * sizeof(uint64_t), hipHostMallocDefault));
+        const size_t fixed = 64 * 4 + kPosted * 8 + S * (3 * 4 + 2 * 8) + 8 * 256;
+        if (!pin.init(pinned_bytes + fixed)) return fail(OMAP_ERR_OUT_OF_MEMORY, "pinned staging (%zu bytes)", pinned_bytes);
+        base = static_cast<char*>(pin.alloc(fixed));   // kept as long as the pool
+        if (!base) return fail(OMAP_ERR_OUT_OF_MEMORY, "pinned tables (%zu bytes)", fixed);
+        at = 0;
+        table(&h_pinned, 64);
+        table(&h_posted, kPosted);
+        table(&h_bad, S);
+        table(&h_fin_min, S);
+        table(&h_fin_last, S);
+        table(&h_fin_reached, S);
+        table(&h_fin_visits, S);
         std::memset(h_posted, 0xff, kPosted * sizeof(uint64_t));
-        HIP_TRY(hipHostMalloc((void**)&h_fin_last, sizeof(int32_t) * cap_slots, hipHostMallocDefault));
-        HIP_TRY(hipHostMalloc((void**)&h_fin_visits, sizeof(int64_t) * cap_slots, hipHostMallocDefault));
-        HIP_TRY(hipHostMalloc((void**)&h_fin_min, sizeof(int32_t) * cap_slots, hipHostMallocDefault));
-        HIP_TRY(hipHostMalloc((void**)&h_fin_reached, sizeof(unsigned long long) * cap_slots, hipHostMallocDefault));
-        if (!pin.init(pinned_bytes)) return fail(OMAP_ERR_OUT_OF_MEMORY, "pinned staging (%zu bytes)", pinned_bytes);
-        HIP_TRY(hipMemsetAsync(d_tile_maze, 0xff, sizeof(int32_t) * cap_tiles, stream));
-        HIP_TRY(hipMemsetAsync(d_flags[0], 0, sizeof(int32_t) * cap_tiles, stream));
-        HIP_TRY(hipMemsetAsync(d_flags[1], 0, sizeof(int32_t) * cap_tiles, stream));
-        HIP_TRY(hipMemsetAsync(d_count, 0, 3 * sizeof(int32_t), stream));
-        HIP_TRY(hipMemsetAsync(d_sched, 0, 3 * sizeof(int32_t) * cap_slots, stream));
-        HIP_TRY(hipMemsetAsync(d_dchg, 0, 3 * sizeof(int32_t) * cap_slots, stream));
-        HIP_TRY(hipMemsetAsync(d_last_round, 0, sizeof(int32_t) * cap_slots, stream));
-        HIP_TRY(hipMemsetAsync(d_touched, 0, cap_tiles, stream));
-        HIP_TRY(hipMemsetAsync(d_bad_slot, 0, sizeof(int32_t) * cap_slots, stream));
-        HIP_TRY(hipMemsetAsync(d_visits, 0, sizeof(int64_t) * cap_slots * kSpread, stream));
-        HIP_TRY(hipMemsetAsync(d_cell_visits, 0, sizeof(int64_t) * cap_slots * kSpread, stream));
-        HIP_TRY(hipMemsetAsync(d_total_cells, 0, sizeof(unsigned long long) * kSpread, stream));
         int dev = 0;
         HIP_TRY(hipGetDevice(&dev));
         int cus = 0;
@@ -1133,11 +1134,7 @@ class Solver {
 
     // Empty schedule (before starting every resident maze afresh).
     omap_status_t reset_schedule() {
-        HIP_TRY(hipMemsetAsync(d_count, 0, 3 * sizeof(int32_t), stream));
-        HIP_TRY(hipMemsetAsync(d_flags[0], 0, sizeof(int32_t) * std::max(tile_hwm, 1), stream));
-        HIP_TRY(hipMemsetAsync(d_flags[1], 0, sizeof(int32_t) * std::max(tile_hwm, 1), stream));
-        HIP_TRY(hipMemsetAsync(d_sched, 0, 3 * sizeof(int32_t) * cap_slots, stream));
-        HIP_TRY(hipMemsetAsync(d_dchg, 0, 3 * sizeof(int32_t) * cap_slots, stream));
+        HIP_TRY(launch_fill(d_count, (int64_t)(schedule_bytes / 4), 0, stream));
         return OMAP_OK;
     }
 
