@@ -119,16 +119,29 @@ hipError_t launch_fill(int32_t* p, int64_t n_elems, int32_t value, hipStream_t s
 // (src_slot: per-source slots, or nullptr for `slot`)
 hipError_t launch_seed(const RoundArgs& a, int32_t slot, const int32_t* src_rc, const int32_t* src_slot,
                        int32_t n_src, int32_t* bad_count, hipStream_t s);
-hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, int32_t* bad_count,
-                                hipStream_t s);
+// posted (a word of pinned host memory, or null): the number of sources on
+// obstacles, with the tag in the upper 16 bits.
+hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, uint64_t* posted,
+                                uint32_t tag, hipStream_t s);
 bool sweep_supported(int T, int C);
 // e0 / e1 (optional, both or neither): events that record the kernel's own
 // start and end (hipExtLaunchKernel), for profiling.
 hipError_t launch_sweep(int T, int C, const RoundArgs& a, int32_t grid, hipStream_t s,
                         hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-// Clears slot's counters before its seeds (last round = r-1; dense: marks the
-// maze for a visit in the round about to run through a.dchg_prev).
-hipError_t launch_slot_reset(const RoundArgs& a, const int32_t* slots, int32_t n, hipStream_t s);
+
+// What a start does before its seeds (k_start).
+struct StartArgs {
+    const MazeDev* staged;        // descriptors of every slot, copied to mazes_out
+    MazeDev* mazes_out;
+    const int32_t* sel;           // per slot: 1 = zero its written tiles, 2 = all its tiles
+    int32_t tile_begin, n_tiles;  // tile ids to look at
+    int32_t* zero;                // words to zero (the schedule's tables)
+    int64_t n_zero;
+    int32_t n_zero_blocks;        // set by the launch wrapper
+    const int32_t* started;       // slots whose counters are reset
+    int32_t n_started;
+};
+hipError_t launch_start(const RoundArgs& a, StartArgs st, hipStream_t s);
 
 // Packing of several mazes' occupancy in one launch.
 struct PackJob {
@@ -150,22 +163,31 @@ hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* r
                                const int32_t* last_round, const int64_t* visits, int32_t n_slots, int32_t* maze_min,
                                unsigned long long* maze_reached, int32_t* last_out, int64_t* visits_out,
                                hipStream_t s);
-hipError_t launch_path_lengths(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
-                               int32_t n_tgt, int32_t parity, int32_t* len, hipStream_t s);
-// order (optional): receives the targets by path length, longest first
-hipError_t launch_scan_offsets(const int32_t* len, int32_t n, int64_t* offsets, hipStream_t s,
-                               int32_t* order = nullptr);
-// order (optional): the walk's order of the targets (from launch_scan_offsets)
+// Lengths (mazes null: len holds them already) and offsets of the paths.  order
+// (optional) receives the targets by path length, longest first; posted (a word
+// of pinned host memory, or null) the number of path cells, tagged as above.
+// Up to kScanLengths targets the scan's one block computes the lengths too, at
+// most four gathers per thread in place of a launch and its gap (5 us).
+constexpr int kScanLengths = 4096;
+hipError_t launch_lengths_offsets(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc, int32_t n_tgt,
+                                  int32_t parity, int32_t* len, int64_t* offsets, int32_t* order, uint64_t* posted,
+                                  uint32_t tag, hipStream_t s);
+// Caller's arrays that a walk copies lengths and offsets to (null: none).
+struct WalkOut {
+    int32_t* len = nullptr;
+    int64_t* off = nullptr;
+};
+// order (optional): the walk's order of the targets (from launch_lengths_offsets)
 hipError_t launch_walk(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                        int32_t n_tgt, int32_t parity, const int32_t* len, const int64_t* offsets,
-                       int32_t* cells, hipStream_t s, const int32_t* order = nullptr);
+                       int32_t* cells, hipStream_t s, const int32_t* order = nullptr, const WalkOut& out = {});
 hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                               const int32_t* tgt_local, int32_t n_tgt, int32_t parity, uint64_t seed,
                               const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s,
-                              const int32_t* order);
+                              const int32_t* order, const WalkOut& out);
 hipError_t launch_walk_euclid(bool write, const MazeDev* mazes, const int32_t* tgt_slot,
                               const int32_t* tgt_rc, int32_t n_tgt, int32_t parity, int32_t* len,
-                              const int64_t* offsets, int32_t* cells, hipStream_t s);
+                              const int64_t* offsets, int32_t* cells, hipStream_t s, const WalkOut& out);
 hipError_t launch_source_index(const MazeDev* mazes, const int32_t* tgt_slot, int32_t n_tgt,
                                const int32_t* len, const int64_t* offsets, const int32_t* cells,
                                const int32_t* src_sorted, const int32_t* src_base, const int32_t* src_n,
@@ -176,11 +198,6 @@ hipError_t launch_activity(const MazeDev* mazes, int32_t slot, int32_t H, int32_
 hipError_t launch_selftest(int32_t* out, hipStream_t s);
 // *counter += add (one thread): advances the round counter of graph replays.
 hipError_t launch_round_advance(int32_t* counter, int32_t add, hipStream_t s);
-// Zeroes both activity buffers (and bit planes) over the interiors of the
-// touched tiles among tile ids [tile_begin, +n_tiles) of the selected mazes
-// (sel == nullptr: all) and clears their touched flags.
-hipError_t launch_clear_touched(const RoundArgs& a, int32_t tile_begin, int32_t n_tiles, const int32_t* sel,
-                                hipStream_t s);
 int sweep_max_waves_per_cu(int T, int C);
 
 }  // namespace omap

@@ -57,12 +57,28 @@ __device__ __forceinline__ int64_t mask_word(const MazeDev& md, int32_t r, int32
     return (int64_t)r * md.mrow + (int64_t)(c >> 5) * md.mcol;
 }
 
-__global__ void k_check_sources(MazeDev md, const int32_t* __restrict__ src, int32_t n, int32_t* __restrict__ bad) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t r = src[2 * i], c = src[2 * i + 1];
-    const uint32_t w = md.mask[mask_word(md, r, c)];
-    if ((w >> (c & 31)) & 1u) atomicAdd(bad, 1);
+// Stores a value below 2^48 with its tag in one word of pinned host memory (one
+// thread; `posted` null: nothing).  What was enqueued before this kernel is done
+// by then.
+__device__ __forceinline__ void post(uint64_t* posted, uint64_t value, uint32_t tag) {
+    if (posted != nullptr)
+        __hip_atomic_store(posted, (uint64_t)tag << 48 | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Posts the number of sources on obstacles (one block).
+__global__ void k_check_sources(MazeDev md, const int32_t* __restrict__ src, int32_t n, uint64_t* posted,
+                                uint32_t tag) {
+    __shared__ int bad;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const int32_t r = src[2 * i], c = src[2 * i + 1];
+        mine += (md.mask[mask_word(md, r, c)] >> (c & 31)) & 1u;
+    }
+    if (mine) atomicAdd(&bad, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) post(posted, (uint64_t)(uint32_t)bad, tag);
 }
 
 // Seed V := K at the sources (both buffers) and, when `schedule` is set,
@@ -92,7 +108,10 @@ __global__ void k_seed(RoundArgs a, int32_t slot0, const int32_t* __restrict__ s
     }
     const int ty = r / a.tile_rows, tx = c / a.tile_cols;
     a.touched[md.tile_base + ty * md.tiles_x + tx] = 1;
-    if (!schedule) return;
+    if (!schedule) {   // dense: the maze counts as changed, so the first round visits it
+        a.dchg_prev[slot] = 1;
+        return;
+    }
     for (int dy = -1; dy <= 1; ++dy)
         for (int dx = -1; dx <= 1; ++dx) {
             const int ny = ty + dy, nx = tx + dx;
@@ -101,45 +120,16 @@ __global__ void k_seed(RoundArgs a, int32_t slot0, const int32_t* __restrict__ s
         }
 }
 
-// Marks each of slots[0..n) for its first round: counters cleared, last round
-// = r - 1; in the dense schedule the maze is flagged as changed so round r
-// visits it.
-__global__ void k_slot_reset(RoundArgs a, const int32_t* __restrict__ slots, int32_t n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int slot = slots[i];
-    a.maze_last_round[slot] = a.round_id - 1;
-    for (int k = 0; k < kSpread; ++k) {
-        a.maze_visits[slot * kSpread + k] = 0;
-        a.maze_cell_visits[slot * kSpread + k] = 0;
-        a.maze_reached[slot * kSpread + k] = 0;
-        a.maze_layer[slot * kSpread + k] = 0;
-    }
-    if (a.dense) a.dchg_prev[slot] = 1;
-}
-
-// One wave per tile id in [tile_begin, tile_begin + n_tiles) whose maze is
-// selected (sel == nullptr: every maze): zero the interior of touched tiles in
-// both activity buffers (front propagation: in its one buffer and both
-// reached-set planes), and clear their touched flags.
-__global__ __launch_bounds__(kBlockThreads) void k_clear_touched(RoundArgs a, int32_t tile_begin,
-                                                                 int32_t n_tiles,
-                                                                 const int32_t* __restrict__ sel) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = blockIdx.x * kWavesPerBlock + wave;
-    if (t >= n_tiles) return;
-    const int g = tile_begin + t;
-    if (!a.touched[g]) return;
-    const int slot = a.tile_maze[g];
-    if (slot < 0 || (sel != nullptr && sel[slot] == 0)) return;
-    const MazeDev md = a.mazes[slot];
-    const int lt = g - md.tile_base;
-    const int ty = lt / md.tiles_x, tx = lt - ty * md.tiles_x;
-    const int r0 = ty * a.tile_rows, c0 = tx * a.tile_cols;
-    const int rows = min(a.tile_rows, md.H - r0), cols = min(a.tile_cols, md.W - c0);
-    if (md.R[0] != nullptr) {   // front tiles: whole rows and words of 64 x 64 cells
-        static_assert(kFrontCols == kLanes && kFrontTileRows == kLanes, "front tile");
-        for (int k = 0; k < rows; ++k) md.V[0][(int64_t)(r0 + k) * md.pitch + c0 + lane_id()] = 0;
+// Zeroes the interior of tile (ty, tx): both activity buffers, or the front
+// propagation's one buffer and both reached-set planes (one wave).
+__device__ __forceinline__ void clear_tile(const MazeDev& md, int ty, int tx, int tile_rows, int tile_cols) {
+    const int r0 = ty * tile_rows, c0 = tx * tile_cols;
+    const int rows = min(tile_rows, md.H - r0), cols = min(tile_cols, md.W - c0);
+    if (md.R[0] != nullptr) {   // front tiles: whole rows and words of 64 x 64 cells, 16 bytes a lane
+        static_assert(kFrontCols == 64 && kFrontTileRows == kLanes, "front tile");
+        const int4 zero = make_int4(0, 0, 0, 0);
+        for (int k = lane_id() >> 4; k < rows; k += 4)
+            *reinterpret_cast<int4*>(md.V[0] + (int64_t)(r0 + k) * md.pitch + c0 + 4 * (lane_id() & 15)) = zero;
         if (lane_id() < rows) {
             for (int j = 0; j < kFrontCols / 32; ++j) {
                 const int64_t x = mask_word(md, r0 + lane_id(), c0 + 32 * j);
@@ -147,14 +137,54 @@ __global__ __launch_bounds__(kBlockThreads) void k_clear_touched(RoundArgs a, in
                 md.R[1][x] = 0;
             }
         }
-    } else {
-        for (int k = lane_id(); k < rows * cols; k += kLanes) {
-            const int64_t x = (int64_t)(r0 + k / cols) * md.pitch + c0 + k % cols;
-            md.V[0][x] = 0;
-            md.V[1][x] = 0;
-        }
+        return;
     }
-    if (lane_id() == 0) a.touched[g] = 0;
+    for (int k = lane_id(); k < rows * cols; k += kLanes) {
+        const int64_t x = (int64_t)(r0 + k / cols) * md.pitch + c0 + k % cols;
+        md.V[0][x] = 0;
+        md.V[1][x] = 0;
+    }
+}
+
+// What a start needs before its seeds, in one launch.  The first blocks take a
+// tile id in [tile_begin, + n_tiles) per wave: the tile of a selected maze is
+// zeroed if it was written since the last time (select 2: always).  The next
+// n_zero_blocks blocks zero n_zero words (the schedule's tables), the last one
+// copies the descriptors to their table and resets the started slots' counters
+// (last round = r - 1).
+__global__ __launch_bounds__(kBlockThreads) void k_start(RoundArgs a, StartArgs st) {
+    const int nb = (st.n_tiles + kWavesPerBlock - 1) / kWavesPerBlock;
+    int b = blockIdx.x;
+    if (b < nb) {
+        const int t = b * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (t >= st.n_tiles) return;
+        const int g = st.tile_begin + t;
+        const int slot = a.tile_maze[g];
+        if (slot < 0 || st.sel[slot] == 0 || (st.sel[slot] == 1 && !a.touched[g])) return;
+        const MazeDev& md = st.staged[slot];
+        const int lt = g - md.tile_base;
+        const int ty = lt / md.tiles_x;
+        clear_tile(md, ty, lt - ty * md.tiles_x, a.tile_rows, a.tile_cols);
+        if (lane_id() == 0) a.touched[g] = 0;
+        return;
+    }
+    b -= nb;
+    if (b < st.n_zero_blocks) {
+        for (int64_t i = (int64_t)b * kBlockThreads + threadIdx.x; i < st.n_zero; i += (int64_t)st.n_zero_blocks * kBlockThreads)
+            st.zero[i] = 0;
+        return;
+    }
+    const uint32_t* from = reinterpret_cast<const uint32_t*>(st.staged);
+    uint32_t* to = reinterpret_cast<uint32_t*>(st.mazes_out);
+    for (int i = threadIdx.x; i < (int)(sizeof(MazeDev) / 4) * a.n_slots; i += kBlockThreads) to[i] = from[i];
+    for (int i = threadIdx.x; i < st.n_started * kSpread; i += kBlockThreads) {
+        const int slot = st.started[i / kSpread], x = slot * kSpread + i % kSpread;
+        if (i % kSpread == 0) a.maze_last_round[slot] = a.round_id - 1;
+        a.maze_visits[x] = 0;
+        a.maze_cell_visits[x] = 0;
+        a.maze_reached[x] = 0;
+        a.maze_layer[x] = 0;
+    }
 }
 
 // Packs the occupancy of several mazes (job j: words [word_begin[j],
@@ -281,15 +311,16 @@ __global__ void k_front_report(const MazeDev* __restrict__ mazes, const unsigned
 // paths: lengths, offsets, gradient walk (one lane per target)
 // ---------------------------------------------------------------------------
 
+__device__ __forceinline__ int path_length(const MazeDev& md, int r, int c, int parity) {
+    const int v = (parity ? md.V[1] : md.V[0])[(int64_t)r * md.pitch + c];
+    return v > 0 ? md.K - v : -1;
+}
+
 __global__ void k_path_lengths(const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot,
                                const int32_t* __restrict__ trc, int32_t n, int32_t parity,
                                int32_t* __restrict__ len) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const MazeDev md = mazes[tslot[i]];
-    const int32_t r = trc[2 * i], c = trc[2 * i + 1];
-    const int v = (parity ? md.V[1] : md.V[0])[(int64_t)r * md.pitch + c];
-    len[i] = v > 0 ? md.K - v : -1;
+    if (i < n) len[i] = path_length(mazes[tslot[i]], trc[2 * i], trc[2 * i + 1], parity);
 }
 
 // Offsets of the paths (exclusive scan of length + 1 over reached targets),
@@ -316,10 +347,18 @@ __device__ __forceinline__ int wave_bucket_slot(int* bucket, int k) {
     return slot;
 }
 
-__global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ len, int32_t n,
-                                               int64_t* __restrict__ off, int32_t* __restrict__ order) {
+// (lengths: computed here first, for up to kScanLengths targets; posted: the
+// number of path cells goes to the host as soon as it is known)
+__global__ __launch_bounds__(1024) void k_scan(const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot,
+                                               const int32_t* __restrict__ trc, int32_t parity,
+                                               int32_t* __restrict__ len, int32_t n, int64_t* __restrict__ off,
+                                               int32_t* __restrict__ order, uint64_t* posted, uint32_t tag) {
     __shared__ int64_t part[1024];
     const int t = threadIdx.x;
+    if (mazes != nullptr) {
+        for (int i = t; i < n; i += 1024) len[i] = path_length(mazes[tslot[i]], trc[2 * i], trc[2 * i + 1], parity);
+        __syncthreads();
+    }
     const int chunk = (n + 1023) / 1024;
     const int b = min(n, t * chunk), e = min(n, b + chunk);
     int64_t s = 0;
@@ -334,7 +373,10 @@ __global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ len, 
         __syncthreads();
     }
     int64_t base = t ? part[t - 1] : 0;
-    if (t == 0) off[0] = 0;
+    if (t == 0) {
+        off[0] = 0;
+        post(posted, (uint64_t)part[1023], tag);
+    }
 #pragma unroll 8
     for (int i = b; i < e; ++i) {
         base += len[i] >= 0 ? (int64_t)len[i] + 1 : 0;
@@ -474,6 +516,15 @@ __device__ __forceinline__ int nth_bit(uint64_t m, int j) {
     return __builtin_ctzll(m);
 }
 
+// Copies target i's length and offset to the caller's arrays (null: they are the
+// caller's already), and after target 0's the end of the last path.
+__device__ __forceinline__ void walk_results(const WalkOut& out, int i, int n, const int32_t* len, const int64_t* off) {
+    if (out.len == nullptr || lane_id() != 0) return;
+    out.len[i] = len[i];
+    out.off[i] = off[i];
+    if (i == 0) out.off[n] = off[n];
+}
+
 // RANDOM: among a cell's maximal neighbours, those holding v0 + 1, the one at
 // position hash mod count in the fixed order is taken, not the first; the
 // hashes of 64 moves are computed together, one per lane.
@@ -482,7 +533,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
     const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot, const int32_t* __restrict__ trc,
     int32_t n, int32_t parity, const int32_t* __restrict__ len, const int64_t* __restrict__ off,
     int32_t* __restrict__ cells, const int32_t* __restrict__ order, const int32_t* __restrict__ tlocal,
-    uint64_t seed) {
+    uint64_t seed, WalkOut out) {
     __shared__ __attribute__((aligned(16))) int32_t win_all[kWalkWaves][kWinRows * kWinCols];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id();
@@ -491,6 +542,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
     // (order: longest paths first, see k_scan)
     const int i = order ? __builtin_amdgcn_readfirstlane(order[w]) : w;
     const int steps = __builtin_amdgcn_readfirstlane(len[i]);
+    walk_results(out, i, n, len, off);
     if (steps < 0) return;
     const int slot = __builtin_amdgcn_readfirstlane(tslot[i]);
     const MazeDev md = mazes[slot];
@@ -634,12 +686,14 @@ constexpr uint64_t kNbr4 = 0x20502ull;   // up, left, right, down of block cell 
 template <bool WRITE>
 __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
     const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot, const int32_t* __restrict__ trc, int32_t n,
-    int32_t parity, int32_t* __restrict__ len, const int64_t* __restrict__ off, int32_t* __restrict__ cells) {
+    int32_t parity, int32_t* __restrict__ len, const int64_t* __restrict__ off, int32_t* __restrict__ cells,
+    WalkOut out) {
     __shared__ __attribute__((aligned(16))) int32_t win_all[kWalkWaves][kWinRows * kWinCols];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id();
     const int i = blockIdx.x * kWalkWaves + wave;
     if (i >= n) return;
+    if (WRITE) walk_results(out, i, n, len, off);
     const int slot = __builtin_amdgcn_readfirstlane(tslot[i]);
     const MazeDev md = mazes[slot];
     const int32_t* __restrict__ V = parity ? md.V[1] : md.V[0];
@@ -807,9 +861,9 @@ hipError_t launch_fill(int32_t* p, int64_t n_elems, int32_t value, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, int32_t* bad_count,
-                                hipStream_t s) {
-    hipLaunchKernelGGL(k_check_sources, dim3(grid_for(n_src, 256)), dim3(256), 0, s, md, src_rc, n_src, bad_count);
+hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, uint64_t* posted,
+                                uint32_t tag, hipStream_t s) {
+    hipLaunchKernelGGL(k_check_sources, dim3(1), dim3(n_src > 256 ? 1024 : 64), 0, s, md, src_rc, n_src, posted, tag);
     return hipGetLastError();
 }
 
@@ -821,9 +875,11 @@ hipError_t launch_seed(const RoundArgs& a, int32_t slot, const int32_t* src_rc, 
     return hipGetLastError();
 }
 
-hipError_t launch_slot_reset(const RoundArgs& a, const int32_t* slots, int32_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_slot_reset, dim3(grid_for(n, 64)), dim3(64), 0, s, a, slots, n);
+hipError_t launch_start(const RoundArgs& a, StartArgs st, hipStream_t s) {
+    const int64_t zero_blocks = (st.n_zero + 4 * kBlockThreads - 1) / (4 * kBlockThreads);
+    st.n_zero_blocks = (int32_t)(zero_blocks < 1024 ? zero_blocks : 1024);
+    const int blocks = (st.n_tiles + kWavesPerBlock - 1) / kWavesPerBlock + st.n_zero_blocks + 1;
+    hipLaunchKernelGGL(k_start, dim3(blocks), dim3(kBlockThreads), 0, s, a, st);
     return hipGetLastError();
 }
 
@@ -891,49 +947,48 @@ hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* r
     return hipGetLastError();
 }
 
-hipError_t launch_path_lengths(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
-                               int32_t n_tgt, int32_t parity, int32_t* len, hipStream_t s) {
-    if (n_tgt <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_path_lengths, dim3(grid_for(n_tgt, 256)), dim3(256), 0, s, mazes, tgt_slot,
-                       tgt_rc, n_tgt, parity, len);
-    return hipGetLastError();
-}
-
-hipError_t launch_scan_offsets(const int32_t* len, int32_t n, int64_t* offsets, hipStream_t s, int32_t* order) {
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, len, n, offsets, order);
+hipError_t launch_lengths_offsets(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc, int32_t n_tgt,
+                                  int32_t parity, int32_t* len, int64_t* offsets, int32_t* order, uint64_t* posted,
+                                  uint32_t tag, hipStream_t s) {
+    const bool within = n_tgt <= kScanLengths;
+    if (mazes != nullptr && !within)
+        hipLaunchKernelGGL(k_path_lengths, dim3(grid_for(n_tgt, 256)), dim3(256), 0, s, mazes, tgt_slot, tgt_rc, n_tgt,
+                           parity, len);
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, within ? mazes : nullptr, tgt_slot, tgt_rc, parity, len,
+                       n_tgt, offsets, order, posted, tag);
     return hipGetLastError();
 }
 
 hipError_t launch_walk(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                        int32_t n_tgt, int32_t parity, const int32_t* len, const int64_t* offsets,
-                       int32_t* cells, hipStream_t s, const int32_t* order) {
+                       int32_t* cells, hipStream_t s, const int32_t* order, const WalkOut& out) {
     if (n_tgt <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_walk<false>, dim3((n_tgt + kWalkWaves - 1) / kWalkWaves), dim3(kLanes * kWalkWaves), 0, s,
-                       mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order, nullptr, 0);
+                       mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order, nullptr, 0, out);
     return hipGetLastError();
 }
 
 hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                               const int32_t* tgt_local, int32_t n_tgt, int32_t parity, uint64_t seed,
                               const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s,
-                              const int32_t* order) {
+                              const int32_t* order, const WalkOut& out) {
     if (n_tgt <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_walk<true>, dim3((n_tgt + kWalkWaves - 1) / kWalkWaves), dim3(kLanes * kWalkWaves), 0, s,
-                       mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order, tgt_local, seed);
+                       mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order, tgt_local, seed, out);
     return hipGetLastError();
 }
 
 hipError_t launch_walk_euclid(bool write, const MazeDev* mazes, const int32_t* tgt_slot,
                               const int32_t* tgt_rc, int32_t n_tgt, int32_t parity, int32_t* len,
-                              const int64_t* offsets, int32_t* cells, hipStream_t s) {
+                              const int64_t* offsets, int32_t* cells, hipStream_t s, const WalkOut& out) {
     if (n_tgt <= 0) return hipSuccess;
     const dim3 grid((n_tgt + kWalkWaves - 1) / kWalkWaves), block(kLanes * kWalkWaves);
     if (write)
         hipLaunchKernelGGL(k_walk_euclid<true>, grid, block, 0, s, mazes, tgt_slot, tgt_rc, n_tgt, parity, len,
-                           offsets, cells);
+                           offsets, cells, out);
     else
         hipLaunchKernelGGL(k_walk_euclid<false>, grid, block, 0, s, mazes, tgt_slot, tgt_rc, n_tgt, parity, len,
-                           offsets, cells);
+                           offsets, cells, out);
     return hipGetLastError();
 }
 
@@ -954,14 +1009,6 @@ hipError_t launch_activity(const MazeDev* mazes, int32_t slot, int32_t H, int32_
     const int64_t blocks = (int64_t)H * col_blocks;
     hipLaunchKernelGGL(k_activity, dim3((uint32_t)blocks), dim3(256), 0, s, mazes, slot, parity,
                        offset, dst, dpitch, col_blocks);
-    return hipGetLastError();
-}
-
-hipError_t launch_clear_touched(const RoundArgs& a, int32_t tile_begin, int32_t n_tiles, const int32_t* sel,
-                                hipStream_t s) {
-    if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_clear_touched, dim3((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock),
-                       dim3(kBlockThreads), 0, s, a, tile_begin, n_tiles, sel);
     return hipGetLastError();
 }
 

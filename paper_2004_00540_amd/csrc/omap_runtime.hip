@@ -575,6 +575,8 @@ class Solver {
     int32_t* h_pinned = nullptr;              // 64 int32 of pinned host scratch
     uint64_t* h_posted = nullptr;             // pinned, [kPosted]: counts posted by the rounds
     bool posting = false;                     // rounds launched now post their counts
+    uint64_t* h_post = nullptr;               // pinned: a value posted by a kernel, tagged
+    uint16_t post_tag = 0;                    // tag of the value awaited
     void* d_scratch = nullptr;                // grow-only path scratch
     size_t scratch_bytes = 0;
     int32_t* d_start_ = nullptr;              // grow-only staging of start_many
@@ -702,19 +704,21 @@ class Solver {
         HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(base), (int64_t)(zeroed / 4), 0, stream));
         h_mazes.assign(cap_slots, MazeDev());
         h_tile_maze.assign(cap_tiles, -1);
-        const size_t fixed = 64 * 4 + kPosted * 8 + S * (3 * 4 + 2 * 8) + 8 * 256;
+        const size_t fixed = 64 * 4 + kPosted * 8 + 16 + S * (3 * 4 + 2 * 8) + 9 * 256;
         if (!pin.init(pinned_bytes + fixed)) return fail(OMAP_ERR_OUT_OF_MEMORY, "pinned staging (%zu bytes)", pinned_bytes);
         base = static_cast<char*>(pin.alloc(fixed));   // kept as long as the pool
         if (!base) return fail(OMAP_ERR_OUT_OF_MEMORY, "pinned tables (%zu bytes)", fixed);
         at = 0;
         table(&h_pinned, 64);
         table(&h_posted, kPosted);
+        table(&h_post, 1);
         table(&h_bad, S);
         table(&h_fin_min, S);
         table(&h_fin_last, S);
         table(&h_fin_reached, S);
         table(&h_fin_visits, S);
         std::memset(h_posted, 0xff, kPosted * sizeof(uint64_t));
+        *h_post = 0;
         int dev = 0;
         HIP_TRY(hipGetDevice(&dev));
         int cus = 0;
@@ -804,13 +808,6 @@ class Solver {
         return s.V[0] && s.mask && s.R[0] && s.R[1];
     }
 
-    // Copies slot k's descriptor to the device (stream-ordered; the host
-    // mirror outlives the copy).
-    omap_status_t upload_desc(int32_t k) {
-        set_desc(k);
-        return upload(d_mazes + k, &h_mazes[k], sizeof(MazeDev));
-    }
-
     // Host mirror of slot k's descriptor.
     void set_desc(int32_t k) {
         const Slot& s = slots[k];
@@ -896,10 +893,10 @@ class Solver {
     }
 
     // Pack one maze into slot k and check its sources on the device; the
-    // verdict is read by commit() (stream-ordered, no host wait).
+    // verdict is read by checked() (stream-ordered, no host wait here).
     // With check_sources = false the caller has checked the sources itself.
     omap_status_t pack_async(int32_t k, const uint8_t* occ_dev, const int32_t* src, int32_t n_src,
-                             const int32_t* tgt, int32_t n_tgt, bool check_sources = true) {
+                             const int32_t* tgt, int32_t n_tgt, bool check_sources) {
         Slot& s = slots[k];
         OK_TRY(validate_problem(s.g.H, s.g.W, occ_dev, src, n_src, tgt, n_tgt));
         s.src.assign(src, src + 2 * n_src);
@@ -912,8 +909,7 @@ class Solver {
             s.d_src = static_cast<int32_t*>(mem->alloc(sizeof(int32_t) * 2 * n_src));
             if (!s.d_src) return fail(OMAP_ERR_OUT_OF_MEMORY, "source list (%d sources)", n_src);
             OK_TRY(upload(s.d_src, s.src.data(), sizeof(int32_t) * 2 * n_src));
-            HIP_TRY(launch_fill(d_bad_slot + k, 1, 0, stream));
-            HIP_TRY(launch_check_sources(h_mazes[k], s.d_src, n_src, d_bad_slot + k, stream));
+            HIP_TRY(launch_check_sources(h_mazes[k], s.d_src, n_src, h_post, ++post_tag, stream));
         }
         s.started = s.finalized = false;
         s.layers = -1;
@@ -933,20 +929,26 @@ class Solver {
         return OMAP_OK;
     }
 
+    // Waits for the verdict of the last pack_async, and with it for the packing.
+    omap_status_t checked() {
+        uint64_t bad = 0;
+        OK_TRY(posted_value(&bad));
+        if (bad != 0) return fail(OMAP_ERR_SOURCE_ON_OBSTACLE, "%d source(s) lie on obstacles", (int)bad);
+        return OMAP_OK;
+    }
+
     // Re-pack slot k with a new problem of the same size (synchronous).
     omap_status_t pack(int32_t k, const uint8_t* occ_dev, const int32_t* src, int32_t n_src,
                        const int32_t* tgt, int32_t n_tgt) {
-        OK_TRY(pack_async(k, occ_dev, src, n_src, tgt, n_tgt));
-        std::vector<int32_t> one{k};
-        return commit(one, nullptr);
+        OK_TRY(pack_async(k, occ_dev, src, n_src, tgt, n_tgt, true));
+        return checked();
     }
 
-    // Allocate slot buffers and a tile id range, then pack.  With defer the
-    // source check is left to a later commit(); otherwise it is synchronous and
-    // a failing maze is removed again.
+    // Allocate slot buffers and a tile id range, then pack.  check_sources: wait
+    // for the packing and the source check, and remove a failing maze again
+    // (else the caller has checked the sources itself).
     omap_status_t add(int32_t H, int32_t W, const uint8_t* occ_dev, const int32_t* src,
-                      int32_t n_src, const int32_t* tgt, int32_t n_tgt, int32_t* slot_out,
-                      bool defer = false, bool check_sources = true) {
+                      int32_t n_src, const int32_t* tgt, int32_t n_tgt, int32_t* slot_out, bool check_sources) {
         OK_TRY(validate_problem(H, W, occ_dev, src, n_src, tgt, n_tgt));
         const int32_t k = free_slot_index();
         if (k < 0) return fail(OMAP_ERR_OUT_OF_MEMORY, "no free maze slot (capacity %d)", cap_slots);
@@ -964,11 +966,7 @@ class Solver {
         }
         omap_status_t st = pack_async(k, occ_dev, src, n_src, tgt, n_tgt, check_sources);
         if (st == OMAP_OK) st = upload_tile_range(s.tile_base, s.n_tiles, k);
-        if (st == OMAP_OK) st = upload_desc(k);
-        if (st == OMAP_OK && !defer) {
-            std::vector<int32_t> one{k};
-            st = commit(one, nullptr);
-        }
+        if (st == OMAP_OK && check_sources) st = checked();
         if (st != OMAP_OK) {
             const std::string msg = g_last_error;
             remove(k);
@@ -1056,16 +1054,11 @@ class Solver {
         return OMAP_OK;
     }
 
-    // Reset slot k's activity and seed it for L layers (L < 0: run-time L).
-    // Stream-ordered: the maze's tiles join the next round.
-    omap_status_t start(int32_t k, int64_t L) {
-        std::vector<int32_t> one{k};
-        return start_many(one, &L);
-    }
-
-    // The same for several slots at once (Ls[i] for which[i]): one descriptor
-    // copy, one clear, one reset and one seed launch for all of them.
-    omap_status_t start_many(const std::vector<int32_t>& which, const int64_t* Ls) {
+    // Reset the activity of the slots `which` and seed them for Ls[i] layers (< 0:
+    // run-time L).  Stream-ordered: their tiles join the next round.  fresh: the
+    // schedule is emptied first (every resident maze starts).  One copy, one
+    // launch for everything before the seeds, one for the seeds.
+    omap_status_t start_many(const std::vector<int32_t>& which, const int64_t* Ls, bool fresh) {
         if (which.empty()) return OMAP_OK;
         for (size_t i = 0; i < which.size(); ++i) {
             const int64_t L = Ls[i];
@@ -1073,9 +1066,7 @@ class Solver {
             if (L >= 0 && L + 1 > 0x7fffffffLL)
                 return fail(OMAP_ERR_TOO_LARGE, "L + 1 = %lld does not fit int32 activity", (long long)(L + 1));
         }
-        std::vector<int32_t> sel(cap_slots, 0), seed_slot;
-        std::vector<int32_t> seed_rc;
-        int32_t lo = tile_hwm, hi = 0;
+        int32_t lo = tile_hwm, hi = 0, n_seed = 0;
         for (size_t i = 0; i < which.size(); ++i) {
             const int32_t k = which[i];
             Slot& s = slots[k];
@@ -1083,58 +1074,62 @@ class Solver {
             s.K = Ls[i] < 0 ? 0x7fffffff : (int32_t)(Ls[i] + 1);
             s.first_round = next_round;
             set_desc(k);
-            sel[k] = 1;
-            if (s.cleared) {
+            n_seed += (int32_t)(s.src.size() / 2);
+            // (the integer sweeps also read the columns between width and pitch,
+            // which no tile covers: their first clear is a fill below)
+            if (s.cleared || s.g.front) {
                 lo = std::min(lo, s.tile_base);
                 hi = std::max(hi, s.tile_base + s.n_tiles);
             }
-            seed_rc.insert(seed_rc.end(), s.src.begin(), s.src.end());
-            seed_slot.insert(seed_slot.end(), s.src.size() / 2, k);
         }
-        OK_TRY(upload(d_mazes, h_mazes.data(), sizeof(MazeDev) * cap_slots));
         const RoundArgs a = round_args(true);
-        // staging: selection | slot list | seed (r, c) pairs | seed slots
-        const int32_t n_seed = (int32_t)seed_slot.size(), n_which = (int32_t)which.size();
-        std::vector<int32_t> stage;
-        stage.reserve(cap_slots + n_which + 3 * n_seed);
-        stage.insert(stage.end(), sel.begin(), sel.end());
-        stage.insert(stage.end(), which.begin(), which.end());
-        stage.insert(stage.end(), seed_rc.begin(), seed_rc.end());
-        stage.insert(stage.end(), seed_slot.begin(), seed_slot.end());
+        // staging: descriptors | selection | slot list | seed (r, c) pairs | seed slots
+        const int32_t n_which = (int32_t)which.size();
+        const size_t desc_words = sizeof(MazeDev) / 4 * (size_t)cap_slots;
+        std::vector<int32_t> stage(desc_words + cap_slots + n_which + 3 * (size_t)n_seed, 0);
+        std::memcpy(stage.data(), h_mazes.data(), sizeof(MazeDev) * cap_slots);
+        int32_t* const sel = stage.data() + desc_words;
+        int32_t* const slot_list = sel + cap_slots;
+        int32_t* seed_rc = slot_list + n_which;
+        int32_t* seed_slot = seed_rc + 2 * n_seed;
+        for (size_t i = 0; i < which.size(); ++i) {
+            const Slot& s = slots[which[i]];
+            sel[which[i]] = s.cleared ? 1 : (s.g.front ? 2 : 0);
+            slot_list[i] = which[i];
+            seed_rc = std::copy(s.src.begin(), s.src.end(), seed_rc);
+            seed_slot = std::fill_n(seed_slot, s.src.size() / 2, which[i]);
+        }
         int32_t* d_stage = nullptr;
         OK_TRY(start_scratch(stage.size(), &d_stage));
         OK_TRY(upload(d_stage, stage.data(), sizeof(int32_t) * stage.size()));
-        const int32_t* d_sel_s = d_stage;
-        const int32_t* d_which = d_stage + cap_slots;
-        const int32_t* d_seed_rc = d_which + n_which;
-        const int32_t* d_seed_slot = d_seed_rc + 2 * n_seed;
-        if (hi > lo) HIP_TRY(launch_clear_touched(a, lo, hi - lo, d_sel_s, stream));
         for (int32_t k : which) {
             Slot& s = slots[k];
-            if (s.cleared) continue;
-            HIP_TRY(launch_fill(s.V[0], s.g.v_bytes / 4, 0, stream));
-            if (!s.g.front) HIP_TRY(launch_fill(s.V[1], s.g.v_bytes / 4, 0, stream));
-            if (s.g.front) {
-                HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(s.R[0]), s.g.m_bytes / 4, 0, stream));
-                HIP_TRY(launch_fill(reinterpret_cast<int32_t*>(s.R[1]), s.g.m_bytes / 4, 0, stream));
+            if (!s.cleared && !s.g.front) {
+                HIP_TRY(launch_fill(s.V[0], s.g.v_bytes / 4, 0, stream));
+                HIP_TRY(launch_fill(s.V[1], s.g.v_bytes / 4, 0, stream));
+                HIP_TRY(hipMemsetAsync(d_touched + s.tile_base, 0, s.n_tiles, stream));
             }
-            HIP_TRY(hipMemsetAsync(d_touched + s.tile_base, 0, s.n_tiles, stream));
             s.cleared = true;
         }
-        HIP_TRY(launch_slot_reset(a, d_which, n_which, stream));
-        HIP_TRY(launch_seed(a, 0, d_seed_rc, d_seed_slot, n_seed, d_bad, stream));
+        StartArgs st{};
+        st.staged = reinterpret_cast<const MazeDev*>(d_stage);
+        st.mazes_out = d_mazes;
+        st.sel = d_stage + desc_words;
+        st.tile_begin = lo;
+        st.n_tiles = std::max(0, hi - lo);
+        st.zero = d_count;
+        st.n_zero = fresh ? (int64_t)(schedule_bytes / 4) : 0;
+        st.started = st.sel + cap_slots;
+        st.n_started = n_which;
+        HIP_TRY(launch_start(a, st, stream));
+        const int32_t* d_seed_rc = st.started + n_which;
+        HIP_TRY(launch_seed(a, 0, d_seed_rc, d_seed_rc + 2 * n_seed, n_seed, d_bad, stream));
         for (int32_t k : which) {
             Slot& s = slots[k];
             s.started = true;
             s.finalized = false;
             s.layers = -1;
         }
-        return OMAP_OK;
-    }
-
-    // Empty schedule (before starting every resident maze afresh).
-    omap_status_t reset_schedule() {
-        HIP_TRY(launch_fill(d_count, (int64_t)(schedule_bytes / 4), 0, stream));
         return OMAP_OK;
     }
 
@@ -1311,27 +1306,46 @@ class Solver {
 #endif
     static constexpr int kAhead = KA;
 
-    // The count posted by round r, waiting for it.  A stream that has drained
-    // (or failed) without posting it is an error, not a wait.
-    omap_status_t posted_count(int64_t r, int32_t* n) {
-        const volatile uint64_t* p = &h_posted[(uint32_t)r % kPosted];
-        for (int64_t spin = 1;; ++spin) {
-            const uint64_t v = *p;
-            if ((uint32_t)(v >> 32) == (uint32_t)r) {
-                *n = (int32_t)(uint32_t)v;
-                return OMAP_OK;
-            }
+    // Waits until seen() holds for what a kernel on the stream stores in pinned
+    // host memory.  A stream that has drained (or failed) without storing it is
+    // an error, not a wait.
+    template <class Seen>
+    omap_status_t wait_posted(Seen seen) {
+        for (int64_t spin = 1; !seen(); ++spin) {
             _mm_pause();
             if (spin % 50000 == 0) {
                 const hipError_t e = hipStreamQuery(stream);
                 if (e != hipErrorNotReady) {
                     if (e != hipSuccess) HIP_TRY(e);
-                    if ((uint32_t)(*p >> 32) == (uint32_t)r) continue;
-                    return fail(OMAP_ERR_HIP, "round %lld ended without posting its count", (long long)r);
+                    if (seen()) break;
+                    return fail(OMAP_ERR_HIP, "the stream ended without posting a result");
                 }
                 (void)hipGetLastError();
             }
         }
+        return OMAP_OK;
+    }
+
+    // The count posted by round r.
+    omap_status_t posted_count(int64_t r, int32_t* n) {
+        uint64_t v = 0;
+        OK_TRY(wait_posted([&] {
+            v = __atomic_load_n(&h_posted[(uint32_t)r % kPosted], __ATOMIC_ACQUIRE);
+            return (uint32_t)(v >> 32) == (uint32_t)r;
+        }));
+        *n = (int32_t)(uint32_t)v;
+        return OMAP_OK;
+    }
+
+    // The value posted with the current tag (post_tag).
+    omap_status_t posted_value(uint64_t* v) {
+        uint64_t w = 0;
+        OK_TRY(wait_posted([&] {
+            w = __atomic_load_n(h_post, __ATOMIC_ACQUIRE);
+            return (uint16_t)(w >> 48) == post_tag;
+        }));
+        *v = w & ((uint64_t(1) << 48) - 1);
+        return OMAP_OK;
     }
 
     // Enqueues the reduction of the selected slots: their smallest positive
@@ -1454,121 +1468,96 @@ class Solver {
         return OMAP_OK;
     }
 
-    // Paths of the targets of `which` (in that order), written to caller
-    // buffers: device buffers, or host buffers with host_out.  mode: 0 simple
-    // reconstruction (fixed tie order), 1 simple with seeded random ties,
-    // 2 Euclidean.  src_out (optional): index of the source each path ends on.
-    // Scratch comes from a grow-only device buffer.
+    // Paths of the targets of `which` (in that order), written to the caller's
+    // device buffers.  mode: 0 simple reconstruction (fixed tie order), 1 simple
+    // with seeded random ties, 2 Euclidean.  src_out (optional): index of the
+    // source each path ends on.  Scratch comes from a grow-only device buffer.
     omap_status_t extract(const std::vector<int32_t>& which, int32_t* len_out, int64_t* off_out,
-                          int32_t* cells_out, int64_t capacity, int64_t* needed, bool host_out,
+                          int32_t* cells_out, int64_t capacity, int64_t* needed,
                           int mode = 0, uint64_t seed = 0, int32_t* src_out = nullptr) {
-        std::vector<int32_t> tslot, trc, tlocal, sbase, scount, ssorted;
+        size_t nt = 0, ns = 0;
+        for (int32_t k : which) {
+            if (!slots[k].started) return fail(OMAP_ERR_NOT_PROPAGATED, "maze %d has not been propagated", k);
+            nt += slots[k].tgt.size() / 2;
+            ns += slots[k].src.size() / 2;
+        }
+        const int32_t n = (int32_t)nt;
+        auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+        // staged in one copy: target slots | (r, c) pairs | for random ties the
+        // targets' own indices | for src_out their sources' ranges and the
+        // (linear cell, first list index) pairs; then on the device alone: len | off | order
+        const size_t b_i = up(sizeof(int32_t) * (nt + 1)), b_rc = up(sizeof(int32_t) * (2 * nt + 2));
+        const size_t b_off = up(sizeof(int64_t) * (nt + 1)), b_ss = src_out ? up(sizeof(int32_t) * (2 * ns + 2)) : 0;
+        const size_t at_rc = b_i, at_local = at_rc + b_rc, at_base = at_local + (mode == 1 ? b_i : 0);
+        const size_t at_count = at_base + (src_out ? b_i : 0), at_ss = at_count + (src_out ? b_i : 0);
+        const size_t staged = at_ss + b_ss;
+        const size_t at_len = staged, at_off = at_len + b_i, at_order = at_off + b_off;
+        std::vector<char> stage(staged);
+        auto words = [&](size_t at) { return reinterpret_cast<int32_t*>(stage.data() + at); };
+        int32_t *tslot = words(0), *trc = words(at_rc);
+        size_t t0 = 0, s0 = 0;
+        std::vector<std::pair<int32_t, int32_t>> by_cell;
         for (int32_t k : which) {
             const Slot& s = slots[k];
-            if (!s.started) return fail(OMAP_ERR_NOT_PROPAGATED, "maze %d has not been propagated", k);
-            const int32_t n = (int32_t)(s.tgt.size() / 2);
-            tslot.insert(tslot.end(), n, k);
-            trc.insert(trc.end(), s.tgt.begin(), s.tgt.end());
-            for (int32_t t = 0; t < n; ++t) tlocal.push_back(t);
+            const size_t m = s.tgt.size() / 2;
+            std::fill_n(tslot + t0, m, k);
+            std::copy(s.tgt.begin(), s.tgt.end(), trc + 2 * t0);
+            if (mode == 1)
+                for (size_t t = 0; t < m; ++t) words(at_local)[t0 + t] = (int32_t)t;
             if (src_out) {
-                // (linear cell, first list index), sorted by cell, duplicates dropped
-                std::vector<std::pair<int32_t, int32_t>> v;
+                // sorted by cell, duplicates dropped
+                by_cell.clear();
                 for (size_t j = 0; j < s.src.size() / 2; ++j)
-                    v.push_back({s.src[2 * j] * s.g.W + s.src[2 * j + 1], (int32_t)j});
-                std::sort(v.begin(), v.end());
-                v.erase(std::unique(v.begin(), v.end(),
-                                    [](const std::pair<int32_t, int32_t>& a, const std::pair<int32_t, int32_t>& b) {
-                                        return a.first == b.first;
-                                    }),
-                        v.end());
-                const int32_t base = (int32_t)(ssorted.size() / 2);
-                for (auto& e : v) {
-                    ssorted.push_back(e.first);
-                    ssorted.push_back(e.second);
+                    by_cell.push_back({s.src[2 * j] * s.g.W + s.src[2 * j + 1], (int32_t)j});
+                std::sort(by_cell.begin(), by_cell.end());
+                by_cell.erase(std::unique(by_cell.begin(), by_cell.end(),
+                                          [](const std::pair<int32_t, int32_t>& a, const std::pair<int32_t, int32_t>& b) {
+                                              return a.first == b.first;
+                                          }),
+                              by_cell.end());
+                std::fill_n(words(at_base) + t0, m, (int32_t)s0);
+                std::fill_n(words(at_count) + t0, m, (int32_t)by_cell.size());
+                for (auto& e : by_cell) {
+                    words(at_ss)[2 * s0] = e.first;
+                    words(at_ss)[2 * s0 + 1] = e.second;
+                    ++s0;
                 }
-                sbase.insert(sbase.end(), n, base);
-                scount.insert(scount.end(), n, (int32_t)v.size());
             }
+            t0 += m;
         }
-        const int32_t n = (int32_t)tslot.size();
-        auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-        const size_t b_i = up(sizeof(int32_t) * (n + 1)), b_rc = up(sizeof(int32_t) * (2 * n + 2));
-        const size_t b_off = up(sizeof(int64_t) * (n + 1)), b_ss = up(sizeof(int32_t) * (ssorted.size() + 2));
-        // layout: tslot | trc | tlocal | len | off | sbase | scount | ssorted | order | (cells for host_out)
-        const size_t fixed = b_i + b_rc + b_i + b_i + b_off + b_i + b_i + b_ss + b_i;
         char* base = nullptr;
-        OK_TRY(scratch(fixed, &base));
-        auto carve = [&](char* b) {
-            struct P { int32_t *tslot, *trc, *tlocal, *len; int64_t* off; int32_t *sbase, *scount, *ss, *order; char* end; } q;
-            q.tslot = reinterpret_cast<int32_t*>(b); b += b_i;
-            q.trc = reinterpret_cast<int32_t*>(b); b += b_rc;
-            q.tlocal = reinterpret_cast<int32_t*>(b); b += b_i;
-            q.len = reinterpret_cast<int32_t*>(b); b += b_i;
-            q.off = reinterpret_cast<int64_t*>(b); b += b_off;
-            q.sbase = reinterpret_cast<int32_t*>(b); b += b_i;
-            q.scount = reinterpret_cast<int32_t*>(b); b += b_i;
-            q.ss = reinterpret_cast<int32_t*>(b); b += b_ss;
-            q.order = reinterpret_cast<int32_t*>(b); b += b_i;
-            q.end = b;
-            return q;
-        };
-        auto q = carve(base);
+        OK_TRY(scratch(at_order + b_i, &base));
+        auto dev = [&](size_t at) { return reinterpret_cast<int32_t*>(base + at); };
+        int32_t* const d_len = dev(at_len);
+        int64_t* const d_off = reinterpret_cast<int64_t*>(base + at_off);
+        if (n > 0) OK_TRY(upload(base, stage.data(), staged));
         // lengths and offsets (the Euclidean walk learns its lengths by walking)
-        auto lengths = [&](decltype(q)& d) -> omap_status_t {
-            if (n > 0) {
-                OK_TRY(upload(d.tslot, tslot.data(), sizeof(int32_t) * n));
-                OK_TRY(upload(d.trc, trc.data(), sizeof(int32_t) * 2 * n));
-                OK_TRY(upload(d.tlocal, tlocal.data(), sizeof(int32_t) * n));
-                if (src_out) {
-                    OK_TRY(upload(d.sbase, sbase.data(), sizeof(int32_t) * n));
-                    OK_TRY(upload(d.scount, scount.data(), sizeof(int32_t) * n));
-                    OK_TRY(upload(d.ss, ssorted.data(), sizeof(int32_t) * ssorted.size()));
-                }
-                if (mode == 2)
-                    HIP_TRY(launch_walk_euclid(false, d_mazes, d.tslot, d.trc, n, vparity(), d.len, nullptr, nullptr, stream));
-                else
-                    HIP_TRY(launch_path_lengths(d_mazes, d.tslot, d.trc, n, vparity(), d.len, stream));
-            }
-            HIP_TRY(launch_scan_offsets(d.len, n, d.off, stream, mode != 2 ? d.order : nullptr));
-            return OMAP_OK;
-        };
-        OK_TRY(lengths(q));
-        HIP_TRY(hipMemcpyAsync(h_pinned, q.off + n, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-        HIP_TRY(hipStreamSynchronize(stream));
-        int64_t total = 0;
-        std::memcpy(&total, h_pinned, sizeof total);
+        if (mode == 2)
+            HIP_TRY(launch_walk_euclid(false, d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, nullptr, nullptr, stream,
+                                       {}));
+        HIP_TRY(launch_lengths_offsets(mode == 2 ? nullptr : d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off,
+                                       mode == 2 ? nullptr : dev(at_order), h_post, ++post_tag, stream));
+        uint64_t posted = 0;
+        OK_TRY(posted_value(&posted));
+        const int64_t total = (int64_t)posted;
         if (needed) *needed = total;
         if (capacity < total || (total > 0 && cells_out == nullptr))
             return fail(OMAP_ERR_BUFFER_TOO_SMALL, "paths need %lld cells, capacity %lld",
                         (long long)total, (long long)capacity);
-        int32_t* walk_dst = cells_out;
-        if (host_out || src_out) {
-            // cells go to scratch first (host copy and/or source lookup read them there)
-            const size_t b_cells = up(sizeof(int32_t) * (size_t)(total + 1));
-            char* base2 = nullptr;
-            OK_TRY(scratch(fixed + b_cells, &base2));
-            if (base2 != base) {   // scratch moved: redo the lengths in the new place
-                q = carve(base2);
-                OK_TRY(lengths(q));
-                base = base2;
-            }
-            if (host_out) walk_dst = reinterpret_cast<int32_t*>(q.end);
-        }
+        const WalkOut out{len_out, off_out};
         if (mode == 2)
-            HIP_TRY(launch_walk_euclid(true, d_mazes, q.tslot, q.trc, n, vparity(), q.len, q.off, walk_dst, stream));
+            HIP_TRY(launch_walk_euclid(true, d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off, cells_out, stream,
+                                       out));
         else if (mode == 1)
-            HIP_TRY(launch_walk_random(d_mazes, q.tslot, q.trc, q.tlocal, n, vparity(), seed, q.len, q.off, walk_dst, stream,
-                                       q.order));
+            HIP_TRY(launch_walk_random(d_mazes, dev(0), dev(at_rc), dev(at_local), n, vparity(), seed, d_len, d_off,
+                                       cells_out, stream, dev(at_order), out));
         else
-            HIP_TRY(launch_walk(d_mazes, q.tslot, q.trc, n, vparity(), q.len, q.off, walk_dst, stream, q.order));
-        const hipMemcpyKind kind = host_out ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
+            HIP_TRY(launch_walk(d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off, cells_out, stream,
+                                dev(at_order), out));
+        if (n == 0) HIP_TRY(hipMemcpyAsync(off_out, d_off, sizeof(int64_t), hipMemcpyDeviceToDevice, stream));
         if (src_out)
-            HIP_TRY(launch_source_index(d_mazes, q.tslot, n, q.len, q.off, walk_dst, q.ss, q.sbase, q.scount,
-                                        src_out, stream));
-        if (n > 0) HIP_TRY(hipMemcpyAsync(len_out, q.len, sizeof(int32_t) * n, kind, stream));
-        HIP_TRY(hipMemcpyAsync(off_out, q.off, sizeof(int64_t) * (n + 1), kind, stream));
-        if (host_out && total > 0)
-            HIP_TRY(hipMemcpyAsync(cells_out, walk_dst, sizeof(int32_t) * total, kind, stream));
+            HIP_TRY(launch_source_index(d_mazes, dev(0), n, d_len, d_off, cells_out, dev(at_ss), dev(at_base),
+                                        dev(at_count), src_out, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         return OMAP_OK;
     }
@@ -1867,7 +1856,7 @@ static omap_status_t engine_admit(omap_engine_s* e) {
         omap_status_t st = r == hipSuccess
                                ? sv.add(q.H, q.W, static_cast<uint8_t*>(g.occ_dev), q.src.data(),
                                         (int32_t)(q.src.size() / 2), q.tgt.empty() ? nullptr : q.tgt.data(),
-                                        (int32_t)(q.tgt.size() / 2), &slot, /*defer=*/true, /*check_sources=*/false)
+                                        (int32_t)(q.tgt.size() / 2), &slot, /*check_sources=*/false)
                                : fail(OMAP_ERR_HIP, "occupancy upload: %s", hipGetErrorString(r));
         if (st == OMAP_ERR_OUT_OF_MEMORY && e->resident() > (int32_t)e->staged.size()) {
             e->reserved += g.reserve;   // fragmented arena: retry when something retires
@@ -1889,7 +1878,7 @@ static omap_status_t engine_admit(omap_engine_s* e) {
         ids.push_back(id);
     }
     if (!started.empty()) {
-        omap_status_t st = sv.start_many(started, Ls.data());
+        omap_status_t st = sv.start_many(started, Ls.data(), /*fresh=*/false);
         if (st != OMAP_OK) {
             const std::string msg = g_last_error;
             for (size_t i = 0; i < ids.size(); ++i) {
@@ -2019,9 +2008,9 @@ static omap_status_t retire_begin(omap_engine_s* e) {
     if (n > 0) {
         OK_TRY(sv.upload(d_tslot, tslot.data(), 4 * n));
         OK_TRY(sv.upload(d_trc, trc.data(), 8 * n));
-        HIP_TRY(launch_path_lengths(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, sv.stream));
     }
-    HIP_TRY(launch_scan_offsets(d_len, R.n, d_off, sv.stream));
+    HIP_TRY(launch_lengths_offsets(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, d_off, nullptr, nullptr, 0,
+                                   sv.stream));
     OK_TRY(R.h_lo.reserve(lo_offsets_at(n) + 8 * (n + 1)));
     if (n > 0) HIP_TRY(hipMemcpyAsync(R.h_lo.p, d_len, 4 * n, hipMemcpyDeviceToHost, sv.stream));
     HIP_TRY(hipMemcpyAsync(R.h_lo.p + lo_offsets_at(n), d_off, 8 * (n + 1), hipMemcpyDeviceToHost, sv.stream));
@@ -2254,7 +2243,8 @@ omap_status_t omap_plan_create(omap_plan_t* out, int32_t height, int32_t width,
     HIP_TRY(hipGetDevice(&p->device));
     const Geometry g = make_geometry(height, width, o);
     OK_TRY(p->solver.init(static_cast<hipStream_t>(stream), o, &p->mem, 1, g.tiles_x * g.tiles_y));
-    OK_TRY(p->solver.add(height, width, occupancy_dev, sources_host, n_sources, targets_host, n_targets, &p->slot));
+    OK_TRY(p->solver.add(height, width, occupancy_dev, sources_host, n_sources, targets_host, n_targets, &p->slot,
+                         /*check_sources=*/true));
     *out = p.release();
     return OMAP_OK;
     API_GUARD_END
@@ -2277,8 +2267,7 @@ omap_status_t omap_propagate(omap_plan_t plan, int64_t max_layers, omap_propagat
     if (!plan) return fail(OMAP_ERR_INVALID_ARG, "plan is NULL");
     Solver& s = plan->solver;
     plan->propagated = false;
-    OK_TRY(s.reset_schedule());
-    OK_TRY(s.start(plan->slot, max_layers));
+    OK_TRY(s.start_many({plan->slot}, &max_layers, /*fresh=*/true));
     OK_TRY(s.run_to_convergence());
     plan->propagated = true;
     if (info) {
@@ -2306,7 +2295,7 @@ omap_status_t omap_extract_paths(omap_plan_t plan, int32_t* len_dev, int64_t* of
     const int32_t nt = (int32_t)(plan->solver.slots[plan->slot].tgt.size() / 2);
     if (!offsets_dev || (nt > 0 && !len_dev)) return fail(OMAP_ERR_INVALID_ARG, "len/offsets pointer is NULL");
     std::vector<int32_t> one{plan->slot};
-    return plan->solver.extract(one, len_dev, offsets_dev, cells_dev, cells_capacity, cells_needed_host, false);
+    return plan->solver.extract(one, len_dev, offsets_dev, cells_dev, cells_capacity, cells_needed_host);
     API_GUARD_END
 }
 
@@ -2333,8 +2322,8 @@ omap_status_t omap_extract_paths_ex(omap_plan_t plan, const omap_walk_options* w
     const int32_t nt = (int32_t)(plan->solver.slots[plan->slot].tgt.size() / 2);
     if (!offsets_dev || (nt > 0 && !len_dev)) return fail(OMAP_ERR_INVALID_ARG, "len/offsets pointer is NULL");
     std::vector<int32_t> one{plan->slot};
-    return plan->solver.extract(one, len_dev, offsets_dev, cells_dev, cells_capacity, cells_needed_host, false,
-                                mode, seed, source_index_dev);
+    return plan->solver.extract(one, len_dev, offsets_dev, cells_dev, cells_capacity, cells_needed_host, mode,
+                                seed, source_index_dev);
     API_GUARD_END
 }
 
@@ -2389,9 +2378,9 @@ static omap_status_t extract_noalloc(omap_plan_t plan, int32_t* len_dev, int64_t
             if (staged) sv.pin.release_now(staged);
             HIP_TRY(e);
         }
-        HIP_TRY(launch_path_lengths(sv.d_mazes, d_tslot, d_trc, n, sv.vparity(), len_dev, sv.stream));
     }
-    HIP_TRY(launch_scan_offsets(len_dev, n, offsets_dev, sv.stream));
+    HIP_TRY(launch_lengths_offsets(sv.d_mazes, d_tslot, d_trc, n, sv.vparity(), len_dev, offsets_dev, nullptr, nullptr, 0,
+                                   sv.stream));
     HIP_TRY(hipMemcpyAsync(sv.h_pinned, offsets_dev + n, sizeof(int64_t), hipMemcpyDeviceToHost, sv.stream));
     const hipError_t sync = hipStreamSynchronize(sv.stream);   // the staging copy above has completed too
     if (staged) sv.pin.release_now(staged);
@@ -2488,10 +2477,9 @@ omap_status_t omap_batch_propagate(omap_batch_t batch, const int64_t* max_layers
     if (!batch) return fail(OMAP_ERR_INVALID_ARG, "batch is NULL");
     Solver& s = batch->solver;
     batch->propagated = false;
-    OK_TRY(s.reset_schedule());
     std::vector<int64_t> Ls(batch->slots.size(), (int64_t)OMAP_AUTO_LAYERS);
     if (max_layers_host) Ls.assign(max_layers_host, max_layers_host + batch->slots.size());
-    OK_TRY(s.start_many(batch->slots, Ls.data()));
+    OK_TRY(s.start_many(batch->slots, Ls.data(), /*fresh=*/true));
     OK_TRY(s.run_to_convergence());
     batch->propagated = true;
     if (infos_host) {
@@ -2524,7 +2512,7 @@ omap_status_t omap_batch_extract_paths(omap_batch_t batch, int32_t* len_dev, int
     if (!batch->propagated) return fail(OMAP_ERR_NOT_PROPAGATED, "call omap_batch_propagate first");
     if (!offsets_dev || !len_dev) return fail(OMAP_ERR_INVALID_ARG, "len/offsets pointer is NULL");
     return batch->solver.extract(batch->slots, len_dev, offsets_dev, cells_dev, cells_capacity,
-                                 cells_needed_host, false);
+                                 cells_needed_host);
     API_GUARD_END
 }
 
@@ -2540,7 +2528,7 @@ omap_status_t omap_batch_extract_paths_ex(omap_batch_t batch, const omap_walk_op
     if (!batch->propagated) return fail(OMAP_ERR_NOT_PROPAGATED, "call omap_batch_propagate first");
     if (!offsets_dev || !len_dev) return fail(OMAP_ERR_INVALID_ARG, "len/offsets pointer is NULL");
     return batch->solver.extract(batch->slots, len_dev, offsets_dev, cells_dev, cells_capacity,
-                                 cells_needed_host, false, mode, seed, source_index_dev);
+                                 cells_needed_host, mode, seed, source_index_dev);
     API_GUARD_END
 }
 
