@@ -192,8 +192,7 @@ hipError_t launch_source_index(const MazeDev* mazes, const int32_t* tgt_slot, in
                                const int32_t* len, const int64_t* offsets, const int32_t* cells,
                                const int32_t* src_sorted, const int32_t* src_base, const int32_t* src_n,
                                int32_t* out, hipStream_t s);
-hipError_t launch_activity(const MazeDev* mazes, int32_t slot, int32_t H, int32_t W,
-                           int32_t parity, int32_t offset, int32_t* dst, int64_t dpitch,
+hipError_t launch_activity(const MazeDev& md, int32_t parity, int32_t offset, int32_t* dst, int64_t dpitch,
                            hipStream_t s);
 hipError_t launch_selftest(int32_t* out, hipStream_t s);
 // *counter += add (one thread): advances the round counter of graph replays.

@@ -1569,7 +1569,7 @@ class Solver {
         if (!s.started) return fail(OMAP_ERR_NOT_PROPAGATED, "maze %d has not been propagated", k);
         OK_TRY(ensure_finalized(k));
         const int64_t off = (int64_t)s.K - s.layers - 1;
-        HIP_TRY(launch_activity(d_mazes, k, s.g.H, s.g.W, vparity(), (int32_t)off, dst, dpitch, stream));
+        HIP_TRY(launch_activity(h_mazes[k], vparity(), (int32_t)off, dst, dpitch, stream));
         return OMAP_OK;
     }
 
@@ -2097,8 +2097,7 @@ static omap_status_t retire_paths(omap_engine_s* e) {
             const Query& q = e->queries[R.ids[i]];
             const Slot& s = sv.slots[q.slot];
             int32_t* d = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(R.d_act) + (R.act_off[i] - act_at));
-            HIP_TRY(launch_activity(sv.d_mazes, q.slot, q.H, q.W, sv.vparity(), (int32_t)((int64_t)s.K - s.layers - 1),
-                                    d, q.W, xs));
+            HIP_TRY(launch_activity(sv.h_mazes[q.slot], sv.vparity(), (int32_t)((int64_t)s.K - s.layers - 1), d, q.W, xs));
             HIP_TRY(hipMemcpyAsync(R.h_out.p + R.act_off[i], d, 4 * (size_t)q.H * q.W, hipMemcpyDeviceToHost, xs));
         }
     }
