@@ -29,10 +29,10 @@
 // settled, and nothing outside them comes near its middle rows in 16 layers);
 // if no wave gains a cell the visit is over.
 //
-// The registers of the 16 layers of the tile's own two words form a unary
-// code of each cell's arrival, turned into 4 bit planes by 11 selects per
-// word; each step's planes and arrivals are kept in LDS, and at the end the
-// waves write activity rows from them, one lane per column.
+// The registers of the 16 layers of the tile's own words form a unary code of
+// each cell's arrival, turned into 4 bit planes by 11 selects per word; the
+// planes and arrivals of the visit are kept in LDS, and at the end the waves
+// write the activity from them, four columns a lane.
 //
 // Dense schedule: every tile of a maze that changed in the round before, no
 // lists and no claims; a tile that gained a cell flags its maze.
@@ -47,13 +47,16 @@
 // What bounds it: on one large maze the chain of rounds (launch gap, list and
 // region loads, four steps, claims), 64 layers per round instead of 16 of the
 // two-wave integer visit it replaced: 23170^2 maze with L* = 7124 per pass
-// (load, propagate, 4096 paths) 6.4 -> 2.5 ms, 4096^2 corridors (L* = 11,000)
-// 12.4 -> 3.7 ms; with fronts everywhere (26,000^2, 5000 sources, 650 layers)
-// VALU issue and the activity writes, 67.7 -> 12.3 ms.  A lone visit takes 10 us:
+// (load, propagate, 4096 paths) 6.4 -> 2.2 ms, 4096^2 corridors (L* = 11,000)
+// 12.4 -> 3.3 ms; with fronts everywhere (26,000^2, 5000 sources, 650 layers)
+// VALU issue and the activity writes, 67.7 -> 10.0 ms.  A lone visit takes 10 us:
 // list entry 0.9, region 0.6, steps 2.1 + 1.7 + 1.3 + 1.2, claims and activity
-// rows 1.5, and 1.6 us pass before the next round's first wave.  Against the earlier
+// 1.3, and 1.6 us pass before the next round's first wave.  Tiles of 64 x 128
+// cells take a third fewer operations per cell but 3 us longer per visit:
+// 26,000^2 propagation 9.0 against 8.6 ms here, corridors 2.85 against 2.30.
+// Against the earlier
 // bit-sliced sweep (one row of 1984 columns per wave, 8 layers per visit, a
-// per-lane loop to write activity) a batch of 512 mazes takes 10.9 instead of
+// per-lane loop to write activity) a batch of 512 mazes takes 9.0 instead of
 // 21.3 ms.
 #pragma once
 
@@ -77,8 +80,10 @@ static_assert(kFrontLayers <= kFrontRows && kFrontLayers <= kFrontCols, "a front
 struct FrontShared {
     uint32_t r[2][kFrontRegionWords][kFrontRegionRows];   // reached, double-buffered over the steps
     uint32_t f[kFrontRegionWords][kFrontRegionRows];      // free
-    uint4 code[kFrontSteps][kFrontWords][kFrontRows];     // layer of arrival within a step, 4 bit planes
-    uint32_t fresh[kFrontSteps][kFrontWords][kFrontRows]; // the tile's cells that arrived in a step
+    // per word of the tile: the layer of arrival within the visit as 6 bit planes
+    // (lo: the 4 within a step, hi.x, hi.y: the step's) and the cells that
+    // arrived in the visit (hi.z)
+    uint4 lo[kFrontRows][kFrontWords], hi[kFrontRows][kFrontWords];
     int32_t active[kFrontSteps];                          // some wave gained a cell in step k
     int32_t last;                                         // a cell of the tile arrived in the last layer
 };
@@ -135,7 +140,6 @@ __device__ __forceinline__ void front_step(FrontShared& sh, int k, int g) {
         first[w] = r[w] = sh.r[cur][W0 + w][row];
         f[w] = sh.f[W0 + w][row];
     }
-    uint32_t h[15][OWN];   // the tile's words after 1 .. 15 layers
     front_layer<NW>(r, f);
     uint32_t gain = 0;
 #pragma unroll
@@ -149,11 +153,31 @@ __device__ __forceinline__ void front_step(FrontShared& sh, int k, int g) {
         return;
     }
     if (lane == 0) sh.active[k] = 1;
+    // The arrivals of 8 layers are coded at a time (fewer registers): after
+    // layers 1 .. 8 of a half, in4 = in the set after 4, in2 = after 2 or 6 by
+    // in4, in1 = after 1, 3, 5 or 7 by both.
+    uint32_t in8[OWN], in4[2][OWN], in2[2][OWN], in1[2][OWN], before[OWN];
 #pragma unroll
-    for (int j = 0; j < 15; ++j) {
+    for (int half = 0; half < 2; ++half) {
+        uint32_t h[7][OWN];
 #pragma unroll
-        for (int c = 0; c < OWN; ++c) h[j][c] = r[C0 + c];
+        for (int j = 0; j < 7; ++j) {
+            if (half != 0 || j != 0) front_layer<NW>(r, f);
+#pragma unroll
+            for (int c = 0; c < OWN; ++c) h[j][c] = r[C0 + c];
+        }
         front_layer<NW>(r, f);
+#pragma unroll
+        for (int c = 0; c < OWN; ++c) {
+            in4[half][c] = h[3][c];
+            in2[half][c] = bit_select(h[3][c], h[1][c], h[5][c]);
+            in1[half][c] = bit_select(in2[half][c], bit_select(h[3][c], h[0][c], h[4][c]),
+                                      bit_select(h[3][c], h[2][c], h[6][c]));
+            if (half == 0) in8[c] = r[C0 + c];
+            else before[c] = h[6][c];
+            // (or the compiler moves the selects down to their use and keeps every h)
+            asm volatile("" : "+v"(in4[half][c]), "+v"(in2[half][c]), "+v"(in1[half][c]));
+        }
     }
     if (mid) {
 #pragma unroll
@@ -166,24 +190,24 @@ __device__ __forceinline__ void front_step(FrontShared& sh, int k, int g) {
     for (int c = 0; c < OWN; ++c) {
         fresh[c] = own ? r[C0 + c] & ~first[C0 + c] : 0u;
         any |= fresh[c];
-        lastb |= fresh[c] & ~h[14][c];
+        lastb |= fresh[c] & ~before[c];
     }
     if (__ballot(any != 0) == 0) return;
     if (LAST && __ballot(lastb != 0) != 0 && lane == 0) sh.last = 1;
     if (!own) return;
+    // (one lane owns each word; the steps are separated by barriers)
 #pragma unroll
     for (int c = 0; c < OWN; ++c) {
-        // arrival a in 0 .. 15: a cell of layer a + 1 is in the sets after a + 1, a + 2, ...
-        const uint32_t in8 = h[7][c];
-        const uint32_t in4 = bit_select(in8, h[3][c], h[11][c]);
-        const uint32_t q0 = bit_select(in8, h[1][c], h[9][c]), q1 = bit_select(in8, h[5][c], h[13][c]);
-        const uint32_t in2 = bit_select(in4, q0, q1);
-        const uint32_t e0 = bit_select(in8, h[0][c], h[8][c]), e1 = bit_select(in8, h[2][c], h[10][c]);
-        const uint32_t e2 = bit_select(in8, h[4][c], h[12][c]), e3 = bit_select(in8, h[6][c], h[14][c]);
-        const uint32_t p0 = bit_select(in4, e0, e2), p1 = bit_select(in4, e1, e3);
-        const uint32_t in1 = bit_select(in2, p0, p1);
-        sh.code[k][T0 + c][ti] = make_uint4(~in1, ~in2, ~in4, ~in8);
-        sh.fresh[k][T0 + c][ti] = fresh[c];
+        uint4 lo = sh.lo[ti][T0 + c], hi = sh.hi[ti][T0 + c];
+        lo.x |= fresh[c] & ~bit_select(in8[c], in1[0][c], in1[1][c]);
+        lo.y |= fresh[c] & ~bit_select(in8[c], in2[0][c], in2[1][c]);
+        lo.z |= fresh[c] & ~bit_select(in8[c], in4[0][c], in4[1][c]);
+        lo.w |= fresh[c] & ~in8[c];
+        hi.x |= k & 1 ? fresh[c] : 0u;
+        hi.y |= k & 2 ? fresh[c] : 0u;
+        hi.z |= fresh[c];
+        sh.lo[ti][T0 + c] = lo;
+        sh.hi[ti][T0 + c] = hi;
     }
 }
 
@@ -197,8 +221,10 @@ __device__ __forceinline__ int front_tile_row(const MazeDev& md, int lt) {
 // One round: T = kFrontLayers layers of every listed tile.  ONE: a single maze,
 // described in the arguments (copying either description into one variable
 // kept both in scalar registers, and their spills cost 0.9 us of a round).
+// (6 waves per SIMD: at most 80 registers, three blocks to a CU instead of two;
+// 512-maze batch 9.55 -> 9.15 ms, 23170^2 propagation 1.76 -> 1.67)
 template <bool ONE, bool DENSE>
-__global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
+__global__ __launch_bounds__(kFrontThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_front(RoundArgs a) {
     // first list entry and count issued before anything else (see k_sweep)
     int i = (int)blockIdx.x - 1;   // block 0: the accounting block
     const int ie = i >= 0 && i < a.n_tile_ids ? i : 0;
@@ -278,8 +304,8 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
                 a.flags_in[g] = 0;
             a.maze_last_round[slot] = a.round_id;
         }
-        for (int t = threadIdx.x; t < kFrontSteps * kFrontWords * kFrontRows; t += kFrontThreads)
-            (&sh.fresh[0][0][0])[t] = 0;
+        for (int t = threadIdx.x; t < kFrontWords * kFrontRows; t += kFrontThreads)
+            (&sh.lo[0][0])[t] = (&sh.hi[0][0])[t] = make_uint4(0, 0, 0, 0);
         if (threadIdx.x < kFrontSteps) sh.active[threadIdx.x] = 0;
         if (threadIdx.x == 0) sh.last = 0;
 #pragma unroll
@@ -299,15 +325,15 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
             // the last 32 layers need the words next to the tile only; the last step
             // is split by the tile's words too (its rows take two waves, the
             // block's other SIMDs would idle)
-            constexpr int H = kFrontHaloWords;
-            static_assert(H == 2 && kFrontWords == 2 && kFrontSteps == 4, "words of a step");
+            constexpr int H = kFrontHaloWords, NW = kFrontWords, HALF = NW / 2;
+            static_assert(H == 2 && NW % 2 == 0 && kFrontSteps == 4, "words of a step");
             if (k < kFrontSteps - 2) {
-                if (wave < kFrontGroups - k) front_step<0, RW, 0, 2, false>(sh, k, wave);
+                if (wave < kFrontGroups - k) front_step<0, RW, 0, NW, false>(sh, k, wave);
             } else if (k < kFrontSteps - 1) {
-                if (wave < kFrontGroups - k) front_step<H - 1, 4, 0, 2, false>(sh, k, wave);
+                if (wave < kFrontGroups - k) front_step<H - 1, NW + 2, 0, NW, false>(sh, k, wave);
             } else {
-                if (wave < 2) front_step<H - 1, 3, 0, 1, true>(sh, k, wave);
-                else if (wave < 4) front_step<H, 3, 1, 1, true>(sh, k, wave - 2);
+                if (wave < 2) front_step<H - 1, HALF + 2, 0, HALF, true>(sh, k, wave);
+                else if (wave < 4) front_step<H - 1 + HALF, HALF + 2, HALF, HALF, true>(sh, k, wave - 2);
             }
             lds_barrier();
             if (sh.active[k] == 0) break;   // nothing moves any more
@@ -319,44 +345,38 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
         const int base_v = md.K - 1 - (int)n0;
         if (wave < kFrontWords) {
             const uint32_t rf = sh.r[fin][kFrontHaloWords + wave][kFrontHaloRows + lane];
-            uint32_t late = 0;   // cells past the maze's last layer do not count
-            uint32_t count = 0;
-            int top = -1;        // the latest arrival among the counted cells
-            for (int j = 0; j < k; ++j) {
-                uint32_t fr = sh.fresh[j][wave][lane];
-                if (__ballot(fr != 0) == 0) continue;
-                const uint4 code = sh.code[j][wave][lane];
-                if (limit < 16 * (j + 1)) {
-                    const int lim = max(limit - 16 * j, 0);   // arrivals below lim count
-                    uint32_t less = 0, same = fr;
-                    const uint32_t plane[4] = {code.x, code.y, code.z, code.w};
+            const uint4 lo = sh.lo[lane][wave], hi = sh.hi[lane][wave];
+            const uint32_t plane[6] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y};
+            uint32_t fr = hi.z;
+            if (limit < kFrontLayers) {   // cells past the maze's last layer do not count
+                uint32_t less = 0, same = fr;
 #pragma unroll
-                    for (int b = 3; b >= 0; --b) {
-                        if ((lim >> b) & 1) {
-                            less |= same & ~plane[b];
-                            same &= plane[b];
-                        } else {
-                            same &= ~plane[b];
-                        }
+                for (int b = 5; b >= 0; --b) {
+                    if ((limit >> b) & 1) {
+                        less |= same & ~plane[b];
+                        same &= plane[b];
+                    } else {
+                        same &= ~plane[b];
                     }
-                    late |= fr & ~less;
-                    fr = less;
                 }
-                uint32_t m = fr;
-                if (__ballot(m != 0) == 0) continue;
-                int t = 0;
-                if (__ballot((m & code.w) != 0)) { t |= 8; m &= code.w; }
-                if (__ballot((m & code.z) != 0)) { t |= 4; m &= code.z; }
-                if (__ballot((m & code.y) != 0)) { t |= 2; m &= code.y; }
-                if (__ballot((m & code.x) != 0)) t |= 1;
-                top = 16 * j + t;
-                count += __popc(fr);
+                fr = less;
             }
-            if (r0 + lane < md.H) Rout[(int64_t)(j0 + wave) * md.mcol + r0 + lane] = rf & ~late;
+            if (r0 + lane < md.H && j0 + wave < md.mpitch)
+                Rout[(int64_t)(j0 + wave) * md.mcol + r0 + lane] = rf & ~(hi.z & ~fr);
             const int sp = blockIdx.x & (kSpread - 1);
             if (wave == 0 && lane == 0 && k > 0)   // 16 layers of the tile's cells per step that moved
                 atomicAdd(a.total_cells + sp, (unsigned long long)(k * tile_cells(md, ty, tx, kFrontRows, kFrontCols)));
-            if (top >= 0) {
+            if (__ballot(fr != 0) != 0) {
+                int top = 0;   // the latest arrival among the counted cells
+                uint32_t m = fr;
+#pragma unroll
+                for (int b = 5; b >= 0; --b) {
+                    if (__ballot((m & plane[b]) != 0) != 0) {
+                        top |= 1 << b;
+                        m &= plane[b];
+                    }
+                }
+                int count = __popc(fr);
                 for (int o = kLanes / 2; o > 0; o >>= 1) count += __shfl_xor(count, o);
                 if (lane == 0) {
                     atomicAdd(&a.maze_reached[slot * kSpread + sp], (unsigned long long)count);
@@ -368,9 +388,8 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
         if (wave == kFrontWaves - 1) {
             if (left > kFrontLayers) {
                 uint32_t fr = 0;
-                for (int j = 0; j < k; ++j)
 #pragma unroll
-                    for (int c = 0; c < kFrontWords; ++c) fr |= sh.fresh[j][c][lane];
+                for (int c = 0; c < kFrontWords; ++c) fr |= sh.hi[lane][c].z;
                 const bool last = sh.last != 0;
                 if (DENSE) {
                     if (__ballot(fr != 0) != 0 && lane == 0) {
@@ -401,24 +420,38 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(RoundArgs a) {
             lds_barrier();   // the block's LDS is reused by the next tile
             continue;
         }
-        // activity rows: lane = column of the tile
-        const int c = lane >> 5, b = lane & 31;
+        // activity: 4 columns a lane.  A nibble of each plane is spread to a bit per
+        // byte by a multiplication, so the 4 arrivals are the bytes of one word.
+        constexpr int kQuads = kFrontCols / 4, kRowsAtOnce = kLanes / kQuads, kTimes = kFrontRows / kRowsAtOnce;
+        const int c = (lane % kQuads) >> 3, b = 4 * (lane & 7);
+        int32_t* const V = md.V[0] + (int64_t)r0 * md.pitch + j0 * 32 + 4 * (lane % kQuads);
         // (waves 0 .. kFrontWords-1 have had their part: they take the last rows)
-        constexpr int kHelp = kFrontWords, kWriters = kFrontWaves - 1 - kHelp, kRest = 9;
+        constexpr int kHelp = kFrontWords, kWriters = kFrontWaves - 1 - kHelp, kRest = kTimes * kHelp / (kHelp + 2 * kWriters);
         const bool helper = wave < kHelp;
-        int row = helper ? kFrontRows - kRest + wave : wave - kHelp;
-        const int row_end = helper ? kFrontRows : kFrontRows - kRest, row_step = helper ? kHelp : kWriters;
-        for (; row < row_end; row += row_step) {
-            uint32_t f[4] = {};
-#pragma unroll
-            for (int j = 0; j < kFrontSteps; ++j) f[j] = sh.fresh[j][c][row];
-            const bool here = ((f[0] | f[1] | f[2] | f[3]) >> b) & 1u;
-            if (__ballot(here) == 0) continue;
-            const int j = (int)(((f[1] | f[3]) >> b) & 1u) | (int)(((f[2] | f[3]) >> b) & 1u) << 1;   // its step
-            const uint4 code = sh.code[j][c][row];
-            const int t = 16 * j + (int)(((code.x >> b) & 1u) | ((code.y >> b) & 1u) << 1 | ((code.z >> b) & 1u) << 2 |
-                                         ((code.w >> b) & 1u) << 3);
-            if (here && t < limit) md.V[0][(int64_t)(r0 + row) * md.pitch + j0 * 32 + lane] = base_v - t;
+        int it = helper ? kTimes - kRest + wave : wave - kHelp;
+        const int it_end = helper ? kTimes : kTimes - kRest, it_step = helper ? kHelp : kWriters;
+        for (; it < it_end; it += it_step) {
+            const int row = it * kRowsAtOnce + lane / kQuads;
+            const uint4 hi = sh.hi[row][c];
+            uint32_t here = (hi.z >> b) & 15u;
+            if (__ballot(here != 0) == 0) continue;
+            const uint4 lo = sh.lo[row][c];
+            auto spread = [&](uint32_t plane) { return __umul24((plane >> b) & 15u, 0x204081u) & 0x01010101u; };
+            const uint32_t t = spread(lo.x) | spread(lo.y) << 1 | spread(lo.z) << 2 | spread(lo.w) << 3 |
+                               spread(hi.x) << 4 | spread(hi.y) << 5;
+            const int t0 = (int)(t & 0xff), t1 = (int)(t >> 8 & 0xff), t2 = (int)(t >> 16 & 0xff), t3 = (int)(t >> 24);
+            if (limit < kFrontLayers)
+                here &= (uint32_t)(t0 < limit) | (uint32_t)(t1 < limit) << 1 | (uint32_t)(t2 < limit) << 2 |
+                        (uint32_t)(t3 < limit) << 3;
+            int32_t* const q = V + (int64_t)row * md.pitch;
+            if (here == 15u) {
+                *(__attribute__((address_space(1))) v4i32*)q = v4i32{base_v - t0, base_v - t1, base_v - t2, base_v - t3};
+            } else {
+                if (here & 1u) q[0] = base_v - t0;
+                if (here & 2u) q[1] = base_v - t1;
+                if (here & 4u) q[2] = base_v - t2;
+                if (here & 8u) q[3] = base_v - t3;
+            }
         }
         lds_barrier();   // the block's LDS is reused by the next tile
     }

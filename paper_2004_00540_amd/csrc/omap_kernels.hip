@@ -125,13 +125,16 @@ __global__ void k_seed(RoundArgs a, int32_t slot0, const int32_t* __restrict__ s
 __device__ __forceinline__ void clear_tile(const MazeDev& md, int ty, int tx, int tile_rows, int tile_cols) {
     const int r0 = ty * tile_rows, c0 = tx * tile_cols;
     const int rows = min(tile_rows, md.H - r0), cols = min(tile_cols, md.W - c0);
-    if (md.R[0] != nullptr) {   // front tiles: whole rows and words of 64 x 64 cells, 16 bytes a lane
-        static_assert(kFrontCols == 64 && kFrontTileRows == kLanes, "front tile");
+    if (md.R[0] != nullptr) {   // front tiles: whole words and rows up to the pitch, 16 bytes a lane
+        constexpr int kQuads = kFrontCols / 4;
+        static_assert(kLanes % kQuads == 0 && kFrontTileRows == kLanes, "front tile");
         const int4 zero = make_int4(0, 0, 0, 0);
-        for (int k = lane_id() >> 4; k < rows; k += 4)
-            *reinterpret_cast<int4*>(md.V[0] + (int64_t)(r0 + k) * md.pitch + c0 + 4 * (lane_id() & 15)) = zero;
+        const int c = c0 + 4 * (lane_id() % kQuads);
+        if (c < md.pitch)
+            for (int k = lane_id() / kQuads; k < rows; k += kLanes / kQuads)
+                *reinterpret_cast<int4*>(md.V[0] + (int64_t)(r0 + k) * md.pitch + c) = zero;
         if (lane_id() < rows) {
-            for (int j = 0; j < kFrontCols / 32; ++j) {
+            for (int j = 0; j < kFrontCols / 32 && c0 + 32 * j < md.pitch; ++j) {
                 const int64_t x = mask_word(md, r0 + lane_id(), c0 + 32 * j);
                 md.R[0][x] = 0;
                 md.R[1][x] = 0;
