@@ -682,9 +682,31 @@ __device__ __forceinline__ uint32_t tie_remainders(uint64_t seed, uint64_t targe
 // One wave per target, from the same windows and 8 x 8 blocks as k_walk: a
 // block serves three moves, with ballots of the cells holding v .. v + 3 (a
 // cell's maximal 4-neighbour holds v + 1, v or less, its maximal 8-neighbour
-// v + 1).  Everything but the block's read and the ballots is scalar.  A
-// lane per target reading its neighbours from memory took 0.9 us per move.
+// v + 1); choosing them is a scalar chain.  Moves are logged three to a lane,
+// and when the window is left its points are straightened together: point x is
+// dropped if x - 1 and x + 1 are diagonal neighbours and x - 1 was kept (after
+// a drop the next point is kept in any case: no move from one diagonal
+// neighbour of a cell reaches another), so in a run of candidates every other
+// one goes, beginning with the first.  2048 targets on 2048 x 2048, one pass: a
+// lane per target reading its neighbours from memory 2.2 ms, straightening
+// move by move in this kernel 0.37 ms.
 constexpr uint64_t kNbr4 = 0x20502ull;   // up, left, right, down of block cell 9: cells 1, 8, 10, 17
+
+// Whether two cells of a window (row * kWinCols + column) are diagonal neighbours.
+__device__ __forceinline__ bool diagonal(int a, int b) {
+    const int dr = (a >> 6) - (b >> 6), dc = (a & 63) - (b & 63);
+    return dr * dr == 1 && dc * dc == 1;
+}
+
+// Every other bit of each run of ones in m, beginning with the run's first (or,
+// for a run that begins at bit 0 after a dropped point, with its second).
+__device__ __forceinline__ uint64_t every_other(uint64_t m, bool after_drop) {
+    const uint64_t even = 0x5555555555555555ull;
+    uint64_t begin = m & ~(m << 1) & even;
+    if (after_drop) begin &= ~1ull;
+    const uint64_t on_even = m & ~(m + begin);   // the runs that take their even bits
+    return (on_even & even) | (m & ~on_even & ~even);
+}
 
 template <bool WRITE>
 __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
@@ -692,6 +714,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
     int32_t parity, int32_t* __restrict__ len, const int64_t* __restrict__ off, int32_t* __restrict__ cells,
     WalkOut out) {
     __shared__ __attribute__((aligned(16))) int32_t win_all[kWalkWaves][kWinRows * kWinCols];
+    __shared__ uint16_t seq_all[kWalkWaves][3 * kLanes + 8];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id();
     const int i = blockIdx.x * kWalkWaves + wave;
@@ -701,6 +724,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
     const MazeDev md = mazes[slot];
     const int32_t* __restrict__ V = parity ? md.V[1] : md.V[0];
     int32_t* win = win_all[wave];
+    uint16_t* seq = seq_all[wave];   // window positions: last decided point, pending point, the moves
     const int my_off = ((lane >> 3) - 3) * kWinCols + ((lane & 7) - 3);
     int r = __builtin_amdgcn_readfirstlane(trc[2 * i]);
     int c = __builtin_amdgcn_readfirstlane(trc[2 * i + 1]);
@@ -709,76 +733,110 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
         if (!WRITE && lane == 0) len[i] = -1;
         return;
     }
+    const int K = md.K, W = md.W;
     int64_t o = WRITE ? off[i] : 0;
-    // kept points: lane k holds the k-th of those not yet stored
-    int kept = 0, count = 0;
-    auto keep = [&](int pr, int pc) {
-        if (WRITE) {
-            kept = lane == (count & (kLanes - 1)) ? pr * md.W + pc : kept;
-            if ((count & (kLanes - 1)) == kLanes - 1) {
-                cells[o + lane] = kept;
-                o += kLanes;
-            }
-        }
-        ++count;
-    };
-    keep(r, c);
-    int kr = r, kc = c;     // last kept point
-    int pr = -1, pc = -1;   // pending point (not yet decided)
+    int count = 1;   // points kept
+    if (WRITE && lane == 0) cells[o] = r * W + c;
+    ++o;
+    int kr = r, kc = c;              // last decided point, and whether it was dropped
+    bool dropped = false;
+    int pr = 0, pc = 0;              // pending point (decided by the move after it)
+    bool pending = false;
     bool sideways_before = false;
     int dr_prev = 0, dc_prev = 0;
-    while (v != md.K) {
+    while (v != K) {
         const int R0 = r - walk_row(dr_prev), C0 = (c - walk_col(dc_prev)) & ~3;
         walk_window(md, V, R0, C0, win);
-        const int r_in = r, c_in = c;
-        int moves = 0;
-        while (v != md.K && walk_room(r - R0, c - C0) >= 0) {
-            const int d = win[(r - R0) * kWinCols + (c - C0) + my_off] - v;
+        int lr = r - R0, lc = c - C0;
+        const int lr_in = lr, lc_in = lc;
+        int log = 0, it = 0, moves = 0;
+        while (v != K && it < kLanes && walk_room(lr, lc) >= 0) {
+            const int pos = lr * kWinCols + lc;
+            const int d = win[pos + my_off] - v;
             uint64_t m0 = __ballot(d == 0), m1 = __ballot(d == 1), m2 = __ballot(d == 2), m3 = __ballot(d == 3);
-            const int br = r - 3, bc = c - 3;   // the block's corner
-            int q = 27;
+            int q = 27, e = pos, done = 0;
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                const uint64_t up4 = m1 & (kNbr4 << (q - 9)), side = m0 & (kNbr4 << (q - 9));
-                const bool sideways = up4 == 0 && side != 0 && !sideways_before;
-                q = __builtin_ctzll(up4 != 0 ? up4 : (sideways ? side : m1 & (kNbr << (q - 9))));
-                sideways_before = sideways;
-                if (!sideways) {
-                    m0 = m1;
-                    m1 = m2;
-                    m2 = m3;
-                    ++v;
-                }
-                ++moves;
-                r = br + (q >> 3);
-                c = bc + (q & 7);
-                // straightening: the pending point is dropped when the last kept point
-                // and the new point are diagonal neighbours
-                if (pr >= 0) {
-                    const int ar = kr > r ? kr - r : r - kr, ac = kc > c ? kc - c : c - kc;
-                    if (!(ar == 1 && ac == 1)) {
-                        keep(pr, pc);
-                        kr = pr;
-                        kc = pc;
+                if (j == 0 || v != K) {
+                    const uint64_t up = m1 & (kNbr4 << (q - 9));
+                    uint64_t to = up;
+                    if (__builtin_expect(up == 0, 0)) {
+                        const uint64_t side = m0 & (kNbr4 << (q - 9));
+                        const bool sideways = side != 0 && !sideways_before;
+                        to = sideways ? side : m1 & (kNbr << (q - 9));
+                        sideways_before = sideways;
+                    } else {
+                        sideways_before = false;
                     }
+                    q = __builtin_ctzll(to);
+                    if (!sideways_before) {
+                        m0 = m1;
+                        m1 = m2;
+                        m2 = m3;
+                        ++v;
+                    }
+                    ++done;
                 }
-                pr = r;
-                pc = c;
-                if (v == md.K) break;
+                e = e << 6 | q;
+            }
+            log = lane == it ? e : log;
+            ++it;
+            moves += done;
+            lr += (q >> 3) - 3;
+            lc += (q & 7) - 3;
+        }
+        r = R0 + lr;
+        c = C0 + lc;
+        // ---- straighten what the window gave
+        const int first = pending ? 2 : 1;   // index of the first move in seq
+        if (lane == 0) {
+            seq[0] = (uint16_t)((kr - R0) * kWinCols + (kc - C0));
+            if (pending) seq[1] = (uint16_t)((pr - R0) * kWinCols + (pc - C0));
+        }
+        if (lane < it) {
+            const int pos = log >> 18;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int q = (log >> (12 - 6 * j)) & 63;
+                if (3 * lane + j < moves)
+                    seq[first + 3 * lane + j] = (uint16_t)(pos + ((q >> 3) - 3) * kWinCols + ((q & 7) - 3));
             }
         }
-        dr_prev = r - r_in;
-        dc_prev = c - c_in;
+        walk_window_done();
+        const int end = first + moves - 1;   // the last point stays pending
+        for (int x0 = 1; x0 < end; x0 += kLanes) {
+            const int x = x0 + lane;
+            const bool valid = x < end;
+            const int here = valid ? seq[x] : 0;
+            const uint64_t cand = __ballot(valid && diagonal(seq[valid ? x - 1 : 0], seq[valid ? x + 1 : 0]));
+            const uint64_t drop = every_other(cand, dropped);
+            const uint64_t keep = __ballot(valid) & ~drop;
+            if (WRITE && (keep >> lane & 1))
+                cells[o + __popcll(keep & ((1ull << lane) - 1))] = (R0 + (here >> 6)) * W + C0 + (here & 63);
+            o += __popcll(keep);
+            count += __popcll(keep);
+            dropped = (drop >> (min(end - x0, kLanes) - 1)) & 1;
+        }
+        if (end > 1) {
+            const int k = __builtin_amdgcn_readfirstlane(seq[end - 1]);
+            kr = R0 + (k >> 6);
+            kc = C0 + (k & 63);
+        }
+        pr = r;
+        pc = c;
+        pending = true;
+        dr_prev = lr - lr_in;
+        dc_prev = lc - lc_in;
+        // a move of less than a third of the moves counts as no direction
         if (3 * abs(dr_prev) < moves) dr_prev = 0;
         if (3 * abs(dc_prev) < moves) dc_prev = 0;
         walk_window_done();
     }
-    if (pr >= 0) keep(pr, pc);
-    if (WRITE) {
-        if (lane < (count & (kLanes - 1))) cells[o + lane] = kept;
-    } else if (lane == 0) {
-        len[i] = count - 1;
+    if (pending) {
+        if (WRITE && lane == 0) cells[o] = pr * W + pc;
+        ++count;
     }
+    if (!WRITE && lane == 0) len[i] = count - 1;
 }
 
 // Index (in its maze's source list) of the source each path ends on; -1 if no
