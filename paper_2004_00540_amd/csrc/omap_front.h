@@ -128,10 +128,9 @@ __device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t 
 // the region (one wave).  Of the tile's words it takes OWN from T0 on (their
 // arrivals, and in the last step their sets alone).
 template <int W0, int NW, int T0, int OWN, bool LAST>
-__device__ __forceinline__ void front_step(FrontShared& sh, int k, int g) {
+__device__ __forceinline__ void front_step(FrontShared& sh, int k, int g, int lane) {
     constexpr int C0 = kFrontHaloWords + T0 - W0;   // the first of them among the lane's
     constexpr int S0 = LAST ? C0 : 0, S1 = LAST ? C0 + OWN : NW;   // words stored
-    const int lane = lane_id();
     const int row = 16 * k + 32 * g + lane;
     const int cur = k & 1;
     uint32_t r[NW], f[NW], first[NW];
@@ -259,62 +258,64 @@ __global__ __launch_bounds__(kFrontThreads) __attribute__((amdgpu_waves_per_eu(6
             e = (uint64_t)(uint32_t)s << 32 | (uint32_t)i;
         }
         // (opaque to the compiler, which would otherwise compute everything that
-        // depends on the lane alone before the loop, ahead of the first visit's loads)
-        int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
-        asm volatile("" : "+s"(wave), "+v"(lane));
+        // depends on these alone before the loop, ahead of the first visit's loads)
+        int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id(), round = a.round_id;
+        asm volatile("" : "+s"(wave), "+v"(lane), "+s"(round));
+        const int tid = wave * kLanes + lane;
         const int g = __builtin_amdgcn_readfirstlane((int)(uint32_t)e);
         const int slot = __builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32));
-        if (!DENSE && i + stride < n) e = *reinterpret_cast<const uint64_t*>(a.list_in + 2 * (i + stride));
         const MazeDev& md = ONE ? a.md0 : a.mazes[slot];
-        const int64_t n0 = (int64_t)(a.round_id - md.round0) * kFrontLayers;   // layers done before this round
-        const int64_t left = (int64_t)md.K - 1 - n0;                           // layers the maze still has
-        if (left <= 0) {   // every layer below K is done
-            if (!DENSE && threadIdx.x == 0) a.flags_in[g] = 0;
-            continue;
-        }
-        const int limit = left < kFrontLayers ? (int)left : kFrontLayers;
         const int lt = g - md.tile_base;
         const int ty = front_tile_row(md, lt), tx = lt - ty * md.tiles_x;
         const int r0 = ty * kFrontRows, j0 = tx * kFrontWords;
         const uint32_t* Rin = a.parity ? md.R[1] : md.R[0];
         uint32_t* Rout = a.parity ? md.R[0] : md.R[1];
-        // ---- load the region: chunks of 64 rows of one word, all loads issued
-        // before the first is used; outside the maze nothing is free or reached
-        constexpr int kChunks = RW * (RR / kLanes), kPer = (kChunks + kFrontWaves - 1) / kFrontWaves;
+        // ---- load the region: wave w takes word w, every row; all loads are issued
+        // before the first is used.  A strip is addressed through a buffer resource
+        // over its rows near the tile: rows outside the maze (a negative offset is a
+        // large unsigned one) and words outside it (an empty resource) read 0.
+        static_assert(RW < kFrontWaves && RR % kLanes == 0, "a wave per word of the region");
+        constexpr int kPer = RR / kLanes;
         uint32_t vr[kPer], vm[kPer];
+        const int row0 = max(r0 - kFrontHaloRows, 0), row_off = r0 - kFrontHaloRows - row0 + lane;
+        const int j = j0 - kFrontHaloWords + wave;
+        const bool word_ok = wave < RW && j >= 0 && j < md.mpitch;
+        if (wave < RW) {
+            const int64_t x = word_ok ? (int64_t)j * md.mcol + row0 : 0;
+            const int bytes = word_ok ? 4 * min(md.H - row0, RR) : 0;
+            const __amdgpu_buffer_rsrc_t br = raw_rsrc(Rin + x, bytes), bm = raw_rsrc(md.mask + x, bytes);
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int c = wave + q * kFrontWaves;
-            const int j = j0 - kFrontHaloWords + c / (RR / kLanes);
-            const int r = r0 - kFrontHaloRows + (c % (RR / kLanes)) * kLanes + lane;
-            const bool ok = c < kChunks && j >= 0 && j < md.mpitch && r >= 0 && r < md.H;
-            const int64_t x = ok ? (int64_t)j * md.mcol + r : 0;
-            vr[q] = *(gconst_u32*)(Rin + x);
-            vm[q] = *(gconst_u32*)(md.mask + x);
-            if (!ok) {
-                vr[q] = 0;
-                vm[q] = 0xffffffffu;
+            for (int q = 0; q < kPer; ++q) {
+                vr[q] = (uint32_t)bload<1>(br, 4 * (row_off + q * kLanes), 0)[0];
+                vm[q] = (uint32_t)bload<1>(bm, 4 * (row_off + q * kLanes), 0)[0];
             }
         }
-        if (threadIdx.x == 0) {   // (the touched flag is set by a tile that gained a cell)
+        if (!DENSE && i + stride < n) e = *reinterpret_cast<const uint64_t*>(a.list_in + 2 * (i + stride));
+        const int64_t n0 = (int64_t)(round - md.round0) * kFrontLayers;   // layers done before this round
+        const int64_t left = (int64_t)md.K - 1 - n0;                      // layers the maze still has
+        if (left <= 0) {   // every layer below K is done
+            if (!DENSE && tid == 0) a.flags_in[g] = 0;
+            continue;
+        }
+        if (tid == 0) {   // (the touched flag is set by a tile that gained a cell)
             if (DENSE)
                 atomicAdd(reinterpret_cast<unsigned long long*>(
                               &a.maze_visits[slot * kSpread + (blockIdx.x & (kSpread - 1))]), 1ull);
             else
                 a.flags_in[g] = 0;
-            a.maze_last_round[slot] = a.round_id;
+            a.maze_last_round[slot] = round;
         }
-        for (int t = threadIdx.x; t < kFrontWords * kFrontRows; t += kFrontThreads)
+        for (int t = tid; t < kFrontWords * kFrontRows; t += kFrontThreads)
             (&sh.lo[0][0])[t] = (&sh.hi[0][0])[t] = make_uint4(0, 0, 0, 0);
-        if (threadIdx.x < kFrontSteps) sh.active[threadIdx.x] = 0;
-        if (threadIdx.x == 0) sh.last = 0;
+        if (tid < kFrontSteps) sh.active[tid] = 0;
+        if (tid == 0) sh.last = 0;
+        if (wave < RW) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int c = wave + q * kFrontWaves;
-            if (c < kChunks) {
-                const int j = c / (RR / kLanes), r = (c % (RR / kLanes)) * kLanes + lane;
-                sh.r[0][j][r] = vr[q];
-                sh.f[j][r] = ~vm[q];   // guard bits (columns >= W) are obstacles
+            for (int q = 0; q < kPer; ++q) {
+                const int row = row_off + row0 + q * kLanes;
+                sh.r[0][wave][q * kLanes + lane] = vr[q];
+                // guard bits (columns >= W) are obstacles, so is all outside the maze
+                sh.f[wave][q * kLanes + lane] = word_ok && row >= 0 && row < md.H ? ~vm[q] : 0u;
             }
         }
         lds_barrier();
@@ -328,12 +329,12 @@ __global__ __launch_bounds__(kFrontThreads) __attribute__((amdgpu_waves_per_eu(6
             constexpr int H = kFrontHaloWords, NW = kFrontWords, HALF = NW / 2;
             static_assert(H == 2 && NW % 2 == 0 && kFrontSteps == 4, "words of a step");
             if (k < kFrontSteps - 2) {
-                if (wave < kFrontGroups - k) front_step<0, RW, 0, NW, false>(sh, k, wave);
+                if (wave < kFrontGroups - k) front_step<0, RW, 0, NW, false>(sh, k, wave, lane);
             } else if (k < kFrontSteps - 1) {
-                if (wave < kFrontGroups - k) front_step<H - 1, NW + 2, 0, NW, false>(sh, k, wave);
+                if (wave < kFrontGroups - k) front_step<H - 1, NW + 2, 0, NW, false>(sh, k, wave, lane);
             } else {
-                if (wave < 2) front_step<H - 1, HALF + 2, 0, HALF, true>(sh, k, wave);
-                else if (wave < 4) front_step<H - 1 + HALF, HALF + 2, HALF, HALF, true>(sh, k, wave - 2);
+                if (wave < 2) front_step<H - 1, HALF + 2, 0, HALF, true>(sh, k, wave, lane);
+                else if (wave < 4) front_step<H - 1 + HALF, HALF + 2, HALF, HALF, true>(sh, k, wave - 2, lane);
             }
             lds_barrier();
             if (sh.active[k] == 0) break;   // nothing moves any more
@@ -343,6 +344,7 @@ __global__ __launch_bounds__(kFrontThreads) __attribute__((amdgpu_waves_per_eu(6
         // that is all it does), waves 0 .. kFrontWords-1 store the reached set
         // and count, and they and the others write activity rows
         const int base_v = md.K - 1 - (int)n0;
+        const int limit = left < kFrontLayers ? (int)left : kFrontLayers;
         if (wave < kFrontWords) {
             const uint32_t rf = sh.r[fin][kFrontHaloWords + wave][kFrontHaloRows + lane];
             const uint4 lo = sh.lo[lane][wave], hi = sh.hi[lane][wave];
