@@ -148,9 +148,11 @@ struct PackJob {
     const uint8_t* occ;
     uint32_t* mask;
     int32_t H, W, mpitch, mrow, mcol;
-    int64_t word_begin;   // first word of this maze in the concatenation
+    int64_t block_begin;   // blocks of the jobs before this one
 };
-hipError_t launch_pack_mask_many(const PackJob* jobs, int32_t n_jobs, int64_t total_words, hipStream_t s);
+int64_t pack_blocks(int32_t H, int32_t mpitch);   // blocks of a maze's packing
+hipError_t launch_pack_mask_many(const PackJob& first, const PackJob* jobs, int32_t n_jobs, int64_t blocks,
+                                 hipStream_t s);
 hipError_t launch_check_sources_many(const MazeDev* mazes, const int32_t* src_rc, const int32_t* src_slot,
                                      int32_t n, int32_t* bad, hipStream_t s);
 // Smallest positive activity and reached count of the touched tiles in

@@ -11,33 +11,91 @@ namespace omap {
 // ingest: occupancy bytes -> obstacle bit mask
 // ---------------------------------------------------------------------------
 
-// (a wave takes 8 words of 8 rows: 256 contiguous bytes of each row are read,
-// and in the strip layout 8 contiguous words of each strip are written)
-__global__ void k_pack_mask(const uint8_t* __restrict__ occ, int32_t H, int32_t W,
-                            uint32_t* __restrict__ mask, int32_t mpitch, int32_t mrow, int32_t mcol) {
-    const int32_t wb = (mpitch + 7) / 8;
-    const int64_t n = (int64_t)((H + 7) / 8) * wb * 64;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t q = i >> 6;
-        const int32_t rb = (int32_t)(q / wb);
-        const int32_t r = rb * 8 + (int32_t)((i >> 3) & 7);
-        const int32_t w = (int32_t)(q - (int64_t)rb * wb) * 8 + (int32_t)(i & 7);
-        if (r >= H || w >= mpitch) continue;
-        const int32_t c0 = w * 32;
-        const uint8_t* row = occ + (int64_t)r * W;
-        uint32_t word = 0;
-        if (c0 + 32 <= W) {
-#pragma unroll
-            for (int b = 0; b < 32; ++b) word |= (row[c0 + b] != 0 ? 1u : 0u) << b;
+// A block packs 32 rows x 1024 columns: a wave reads eight rows, 16 bytes a lane
+// with every load issued before the first is used, turns each byte into a bit
+// (nonzero bytes to 0x01, four of them to a nibble by a dot product with 1, 2, 4,
+// 8) and two lanes' bits into a word; the block's words go through LDS to the
+// mask's layout, 128 contiguous bytes of a strip or of a row.  One job per maze,
+// blocks in job order.  Bound by the read of the occupancy: 3.8 TB/s on
+// 26,000^2 cells (0.179 ms) and 4.0 on 23,170^2 (0.133); a thread per word, 32
+// byte loads each, took 0.19 ms.  512 mazes of up to 2,048^2 cells take 0.095 ms;
+// with a thread per word, each searching its job, 0.46.
+constexpr int kPackRows = 32, kPackWords = 32, kPackGrid = 65536;
+typedef uint32_t v4u32_bytes __attribute__((ext_vector_type(4), aligned(1)));
+
+__global__ __launch_bounds__(256) void k_pack_mask(PackJob one, const PackJob* __restrict__ jobs, int32_t n_jobs,
+                                                   int64_t blocks) {
+    __shared__ uint32_t tile[kPackWords][kPackRows + 1];
+    const int wave = threadIdx.x >> 6, lane = lane_id();
+    for (int64_t q = blockIdx.x; q < blocks; q += gridDim.x) {
+        PackJob jb = one;
+        if (n_jobs > 1) {
+            int lo = 0, hi = n_jobs - 1;   // the last job with block_begin <= q
+            while (lo < hi) {
+                const int m = (lo + hi + 1) >> 1;
+                if (jobs[m].block_begin <= q) lo = m;
+                else hi = m - 1;
+            }
+            jb = jobs[lo];
+        }
+        const int32_t col_tiles = (jb.mpitch + kPackWords - 1) / kPackWords;
+        const int64_t b = q - jb.block_begin;
+        const int32_t rt = (int32_t)(b / col_tiles), ct = (int32_t)(b - (int64_t)rt * col_tiles);
+        const int64_t row0 = (int64_t)rt * kPackRows;
+        const auto occ = (const __attribute__((address_space(1))) uint8_t*)jb.occ;
+        if (jb.W < 16) {   // narrower than a lane's load; columns past the row are obstacles
+            for (int t = threadIdx.x; t < kPackWords * kPackRows; t += 256) {
+                uint32_t word = ~0u;
+                const int64_t r = min(row0 + t % kPackRows, (int64_t)jb.H - 1);
+                if (t < kPackRows) {
+                    for (int e = 0; e < jb.W; ++e)
+                        if (occ[r * jb.W + e] == 0) word &= ~(1u << e);
+                }
+                tile[t / kPackRows][t % kPackRows] = word;
+            }
         } else {
-            for (int b = 0; b < 32; ++b) {
-                const int32_t c = c0 + b;
-                const uint32_t bit = (c >= W) ? 1u : (row[c] != 0 ? 1u : 0u);
-                word |= bit << b;
+            // (a lane past the row's last 16 bytes reads those and shifts its bits)
+            const int32_t c = ct * (32 * kPackWords) + 16 * lane;
+            const int32_t at = min(c, jb.W - 16), past = min(c - at, 16);
+            v4u32_bytes v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int64_t r = min(row0 + 8 * wave + k, (int64_t)jb.H - 1);
+                v[k] = *(const __attribute__((address_space(1))) v4u32_bytes*)(occ + r * jb.W + at);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                uint32_t bits = 0;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t y[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const uint32_t x = v[k][2 * h + e];
+                        y[e] = ((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) >> 7) & 0x01010101u;
+                    }
+                    const uint32_t low = __builtin_amdgcn_udot4(y[0], 0x08040201u, 0, false);
+                    bits |= __builtin_amdgcn_udot4(y[1], 0x80402010u, low, false) << (8 * h);
+                }
+                bits = (bits | 0xffff0000u) >> past & 0xffffu;
+                const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, 0xF5, 0xF, 0xF, true);   // quad_perm [1, 1, 3, 3]
+                if ((lane & 1) == 0) tile[lane >> 1][8 * wave + k] = bits | next << 16;
             }
         }
-        mask[(int64_t)r * mrow + (int64_t)w * mcol] = word;
+        __syncthreads();
+        const int32_t w0 = ct * kPackWords;
+        if (jb.mrow == 1) {   // strips
+            for (int t = threadIdx.x; t < kPackWords * kPackRows; t += 256) {
+                const int w = t / kPackRows, r = t % kPackRows;
+                if (w0 + w < jb.mpitch && row0 + r < jb.H) jb.mask[(int64_t)(w0 + w) * jb.mcol + row0 + r] = tile[w][r];
+            }
+        } else {
+            for (int t = threadIdx.x; t < kPackWords * kPackRows; t += 256) {
+                const int r = t / kPackWords, w = t % kPackWords;
+                if (w0 + w < jb.mpitch && row0 + r < jb.H) jb.mask[(row0 + r) * jb.mrow + w0 + w] = tile[w][r];
+            }
+        }
+        __syncthreads();   // the next tile overwrites the words
     }
 }
 
@@ -187,33 +245,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_start(RoundArgs a, StartArgs 
         a.maze_cell_visits[x] = 0;
         a.maze_reached[x] = 0;
         a.maze_layer[x] = 0;
-    }
-}
-
-// Packs the occupancy of several mazes (job j: words [word_begin[j],
-// word_begin[j+1]) of the concatenated masks); one thread per mask word.
-__global__ void k_pack_mask_many(const PackJob* __restrict__ jobs, int32_t n_jobs, int64_t total_words) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total_words;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        int lo = 0, hi = n_jobs - 1;   // last job with word_begin <= i
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (jobs[mid].word_begin <= i) lo = mid;
-            else hi = mid - 1;
-        }
-        const PackJob jb = jobs[lo];
-        const int64_t wi = i - jb.word_begin;
-        const int32_t r = (int32_t)(wi / jb.mpitch);
-        const int32_t w = (int32_t)(wi - (int64_t)r * jb.mpitch);
-        const int32_t c0 = w * 32;
-        const uint8_t* row = jb.occ + (int64_t)r * jb.W;
-        uint32_t word = 0;
-        for (int b = 0; b < 32; ++b) {
-            const int32_t c = c0 + b;
-            const uint32_t bit = (c >= jb.W) ? 1u : (row[c] != 0 ? 1u : 0u);
-            word |= bit << b;
-        }
-        jb.mask[(int64_t)r * jb.mrow + (int64_t)w * jb.mcol] = word;
     }
 }
 
@@ -933,10 +964,14 @@ static int grid_for(int64_t n, int block, int cap = 1 << 20) {
     return (int)g;
 }
 
+int64_t pack_blocks(int32_t H, int32_t mpitch) {
+    return (int64_t)((H + kPackRows - 1) / kPackRows) * ((mpitch + kPackWords - 1) / kPackWords);
+}
+
 hipError_t launch_pack_mask(const uint8_t* occ, const MazeDev& md, uint32_t* mask, hipStream_t s) {
-    const int64_t n = (int64_t)((md.H + 7) / 8) * ((md.mpitch + 7) / 8) * 64;
-    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, occ, md.H, md.W, mask,
-                       md.mpitch, md.mrow, md.mcol);
+    const PackJob jb{occ, mask, md.H, md.W, md.mpitch, md.mrow, md.mcol, 0};
+    const int64_t blocks = pack_blocks(md.H, md.mpitch);
+    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(blocks, 1, kPackGrid)), dim3(256), 0, s, jb, nullptr, 1, blocks);
     return hipGetLastError();
 }
 
@@ -969,10 +1004,10 @@ hipError_t launch_start(const RoundArgs& a, StartArgs st, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_pack_mask_many(const PackJob* jobs, int32_t n_jobs, int64_t total_words, hipStream_t s) {
-    if (n_jobs <= 0 || total_words <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pack_mask_many, dim3(grid_for(total_words, 256, 65536)), dim3(256), 0, s, jobs, n_jobs,
-                       total_words);
+hipError_t launch_pack_mask_many(const PackJob& first, const PackJob* jobs, int32_t n_jobs, int64_t blocks,
+                                 hipStream_t s) {
+    if (n_jobs <= 0 || blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(blocks, 1, kPackGrid)), dim3(256), 0, s, first, jobs, n_jobs, blocks);
     return hipGetLastError();
 }
 

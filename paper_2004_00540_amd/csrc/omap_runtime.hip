@@ -984,7 +984,7 @@ class Solver {
     omap_status_t add_many(const omap_maze_desc* d, int32_t n, std::vector<int32_t>* out_slots) {
         std::vector<PackJob> jobs;
         std::vector<int32_t> src_rc, src_slot;
-        int64_t words = 0;
+        int64_t blocks = 0;
         for (int32_t i = 0; i < n; ++i) {
             OK_TRY(validate_problem(d[i].height, d[i].width, d[i].occupancy_dev, d[i].sources_host, d[i].n_sources,
                                     d[i].targets_host, d[i].n_targets));
@@ -1012,8 +1012,8 @@ class Solver {
             jb.mpitch = s.g.mpitch;
             jb.mrow = s.g.mrow;
             jb.mcol = s.g.mcol;
-            jb.word_begin = words;
-            words += (int64_t)s.g.H * s.g.mpitch;
+            jb.block_begin = blocks;
+            blocks += pack_blocks(s.g.H, s.g.mpitch);
             jobs.push_back(jb);
             src_rc.insert(src_rc.end(), s.src.begin(), s.src.end());
             src_slot.insert(src_slot.end(), (size_t)d[i].n_sources, k);
@@ -1033,7 +1033,7 @@ class Solver {
         OK_TRY(upload(d_tile_maze, h_tile_maze.data(), sizeof(int32_t) * tile_hwm));
         OK_TRY(upload(d_mazes, h_mazes.data(), sizeof(MazeDev) * cap_slots));
         HIP_TRY(hipMemsetAsync(d_bad_slot, 0, sizeof(int32_t) * cap_slots, stream));
-        HIP_TRY(launch_pack_mask_many(reinterpret_cast<const PackJob*>(base), n, words, stream));
+        HIP_TRY(launch_pack_mask_many(jobs[0], reinterpret_cast<const PackJob*>(base), n, blocks, stream));
         HIP_TRY(launch_check_sources_many(d_mazes, reinterpret_cast<const int32_t*>(base + b_jobs),
                                           reinterpret_cast<const int32_t*>(base + b_jobs + b_rc),
                                           (int32_t)src_slot.size(), d_bad_slot, stream));
