@@ -169,11 +169,14 @@ hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* r
 // (optional) receives the targets by path length, longest first; posted (a word
 // of pinned host memory, or null) the number of path cells, tagged as above.
 // Up to kScanLengths targets the scan's one block computes the lengths too, at
-// most four gathers per thread in place of a launch and its gap (5 us).
+// most four gathers per thread in place of a launch and its gap (5 us).  More
+// targets are scanned by many blocks if there is `work` (scan_work_bytes(n), 8-byte
+// aligned), else by the one block.
 constexpr int kScanLengths = 4096;
+size_t scan_work_bytes(int32_t n);
 hipError_t launch_lengths_offsets(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc, int32_t n_tgt,
-                                  int32_t parity, int32_t* len, int64_t* offsets, int32_t* order, uint64_t* posted,
-                                  uint32_t tag, hipStream_t s);
+                                  int32_t parity, int32_t* len, int64_t* offsets, int32_t* order, void* work,
+                                  uint64_t* posted, uint32_t tag, hipStream_t s);
 // Caller's arrays that a walk copies lengths and offsets to (null: none).
 struct WalkOut {
     int32_t* len = nullptr;

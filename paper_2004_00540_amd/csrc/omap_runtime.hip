@@ -1491,7 +1491,7 @@ class Solver {
         const size_t at_rc = b_i, at_local = at_rc + b_rc, at_base = at_local + (mode == 1 ? b_i : 0);
         const size_t at_count = at_base + (src_out ? b_i : 0), at_ss = at_count + (src_out ? b_i : 0);
         const size_t staged = at_ss + b_ss;
-        const size_t at_len = staged, at_off = at_len + b_i, at_order = at_off + b_off;
+        const size_t at_len = staged, at_off = at_len + b_i, at_order = at_off + b_off, at_work = at_order + b_i;
         std::vector<char> stage(staged);
         auto words = [&](size_t at) { return reinterpret_cast<int32_t*>(stage.data() + at); };
         int32_t *tslot = words(0), *trc = words(at_rc);
@@ -1526,7 +1526,7 @@ class Solver {
             t0 += m;
         }
         char* base = nullptr;
-        OK_TRY(scratch(at_order + b_i, &base));
+        OK_TRY(scratch(at_work + scan_work_bytes(n), &base));
         auto dev = [&](size_t at) { return reinterpret_cast<int32_t*>(base + at); };
         int32_t* const d_len = dev(at_len);
         int64_t* const d_off = reinterpret_cast<int64_t*>(base + at_off);
@@ -1536,7 +1536,7 @@ class Solver {
             HIP_TRY(launch_walk_euclid(false, d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, nullptr, nullptr, stream,
                                        {}));
         HIP_TRY(launch_lengths_offsets(mode == 2 ? nullptr : d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off,
-                                       mode == 2 ? nullptr : dev(at_order), h_post, ++post_tag, stream));
+                                       mode == 2 ? nullptr : dev(at_order), dev(at_work), h_post, ++post_tag, stream));
         uint64_t posted = 0;
         OK_TRY(posted_value(&posted));
         const int64_t total = (int64_t)posted;
@@ -2000,7 +2000,8 @@ static omap_status_t retire_begin(omap_engine_s* e) {
     const size_t n = (size_t)R.n;
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
     char* base = nullptr;
-    OK_TRY(sv.scratch(up(4 * (n + 1)) + up(8 * (n + 1)) + up(4 * (n + 1)) + up(8 * (n + 1)), &base));
+    const size_t at_work = up(4 * (n + 1)) + up(8 * (n + 1)) + up(4 * (n + 1)) + up(8 * (n + 1));
+    OK_TRY(sv.scratch(at_work + scan_work_bytes(R.n), &base));
     int32_t* d_tslot = reinterpret_cast<int32_t*>(base);
     int32_t* d_trc = reinterpret_cast<int32_t*>(base + up(4 * (n + 1)));
     int32_t* d_len = reinterpret_cast<int32_t*>(base + up(4 * (n + 1)) + up(8 * (n + 1)));
@@ -2009,8 +2010,8 @@ static omap_status_t retire_begin(omap_engine_s* e) {
         OK_TRY(sv.upload(d_tslot, tslot.data(), 4 * n));
         OK_TRY(sv.upload(d_trc, trc.data(), 8 * n));
     }
-    HIP_TRY(launch_lengths_offsets(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, d_off, nullptr, nullptr, 0,
-                                   sv.stream));
+    HIP_TRY(launch_lengths_offsets(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, d_off, nullptr,
+                                   R.n > kScanLengths ? base + at_work : nullptr, nullptr, 0, sv.stream));
     OK_TRY(R.h_lo.reserve(lo_offsets_at(n) + 8 * (n + 1)));
     if (n > 0) HIP_TRY(hipMemcpyAsync(R.h_lo.p, d_len, 4 * n, hipMemcpyDeviceToHost, sv.stream));
     HIP_TRY(hipMemcpyAsync(R.h_lo.p + lo_offsets_at(n), d_off, 8 * (n + 1), hipMemcpyDeviceToHost, sv.stream));
@@ -2378,8 +2379,8 @@ static omap_status_t extract_noalloc(omap_plan_t plan, int32_t* len_dev, int64_t
             HIP_TRY(e);
         }
     }
-    HIP_TRY(launch_lengths_offsets(sv.d_mazes, d_tslot, d_trc, n, sv.vparity(), len_dev, offsets_dev, nullptr, nullptr, 0,
-                                   sv.stream));
+    HIP_TRY(launch_lengths_offsets(sv.d_mazes, d_tslot, d_trc, n, sv.vparity(), len_dev, offsets_dev, nullptr, nullptr,
+                                   nullptr, 0, sv.stream));
     HIP_TRY(hipMemcpyAsync(sv.h_pinned, offsets_dev + n, sizeof(int64_t), hipMemcpyDeviceToHost, sv.stream));
     const hipError_t sync = hipStreamSynchronize(sv.stream);   // the staging copy above has completed too
     if (staged) sv.pin.release_now(staged);

@@ -1,0 +1,58 @@
+"""Offsets and paths of more targets than one block scans (4,096), at the edges of
+the scan's blocks (256 targets) and of the blocks that one block scans (256 of
+them), for each kind of walk and for an engine's retirement."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_helpers import to_dev
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = (4095, 4096, 4097, 4352, 4353, 65536, 65537)
+
+
+def _problem(n):
+    """A maze with unreached targets, and n targets drawn from its free cells."""
+    m = workloads.random_maze(60, 70, 0.42, 2, 4, 77)
+    free = np.argwhere(m.occ == 0).astype(np.int32)
+    pick = np.random.default_rng(n).integers(0, len(free), n)
+    d, ecc = oracle.bfs(m.occ, m.sources)
+    return m, oracle.activity_from_bfs(d, ecc), free, pick
+
+
+def _expand(ref, pick):
+    """The results of targets `pick` from those of every free cell."""
+    ln, off, cells = ref
+    n_cells = np.maximum(ln + 1, 0)[pick]
+    out = np.concatenate([[0], np.cumsum(n_cells)]).astype(np.int64)
+    at = np.repeat(off[:-1][pick] - out[:-1], n_cells) + np.arange(out[-1])
+    return ln[pick], out, cells[at]
+
+
+@pytest.mark.parametrize("n", COUNTS)
+def test_many_targets(n):
+    import paper_2004_00540_amd as omap
+    m, A, free, pick = _problem(n)
+    targets = free[pick]
+    with omap.Plan(to_dev(m.occ), m.sources, targets) as plan:
+        plan.propagate()
+        for mode in (None, "euclidean"):
+            walk = oracle.walk_euclidean if mode else oracle.walk
+            ref = _expand(walk(A, m.sources, free), pick)
+            assert (ref[0] < 0).any() and (ref[0] >= 0).any()
+            for g, r in zip(plan.paths(mode), ref):
+                assert np.array_equal(g.cpu().numpy(), r), (n, mode)
+        got = plan.paths("random", 5)
+        assert np.array_equal(got[1].cpu().numpy(), _expand(oracle.walk(A, m.sources, free), pick)[1])
+    with omap.Engine(1 << 28) as e:
+        qid = e.submit(m.occ, m.sources, targets)
+        for _ in range(200):
+            e.step()
+            if e.poll(qid) in (omap.QUERY_DONE, omap.QUERY_FAILED):
+                break
+        res = e.fetch(qid)
+    ref = _expand(oracle.walk(A, m.sources, free), pick)
+    for g, r in zip((res.lengths, res.offsets, res.cells), ref):
+        assert np.array_equal(g, r), n
