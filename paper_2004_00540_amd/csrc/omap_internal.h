@@ -183,9 +183,10 @@ struct WalkOut {
     int64_t* off = nullptr;
 };
 // order (optional): the walk's order of the targets (from launch_lengths_offsets)
+// (total: cells of all the paths)
 hipError_t launch_walk(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                        int32_t n_tgt, int32_t parity, const int32_t* len, const int64_t* offsets,
-                       int32_t* cells, hipStream_t s, const int32_t* order = nullptr, const WalkOut& out = {});
+                       int32_t* cells, int64_t total, hipStream_t s, const int32_t* order = nullptr, const WalkOut& out = {});
 hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                               const int32_t* tgt_local, int32_t n_tgt, int32_t parity, uint64_t seed,
                               const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s,

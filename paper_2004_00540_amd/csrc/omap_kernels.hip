@@ -788,6 +788,164 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
     }
 }
 
+// A few targets with long paths: a block per target, which spends its threads on
+// shortening the chain.  For every cell of a 64 x 64 window the next cell of its
+// path is worked out (bytes of one-hot activity modulo 3, four cells a register:
+// adjacent reached cells differ by at most one, so a neighbour with one more is
+// one whose class follows), then the cell 2, 4 and 8 moves on by pointer doubling
+// in LDS.  The chain is one LDS read per 8 moves; the moves between are filled in
+// by all threads, move k of the window from the chain's read k / 8 by the pointers
+// of k's bits.  A cell on the window's border, a source and a cell without a path
+// point to themselves.
+//
+// Bound by a window's latency, 3.3 us (about 1 us the load, the rest the steps
+// between barriers), whatever its moves: about 60 straight on.  The wave's three
+// moves per LDS read take 0.23 us and its window 1.5.  Extraction of one path of
+// 9,125 moves in corridors 0.757 -> 0.550 ms, of 64 of up to 10,164 0.837 -> 0.578.
+// 16 moves a hop, 1,024 threads, or loading the window that lies ahead meanwhile
+// measured no better (0.560, 0.557, 0.654 ms), 256 threads 0.692.
+//
+// Taken by the number of targets and their moves on average (of reached targets
+// and others): 160 targets of 37 moves 39.7 us with a wave each, 43.4 with a block;
+// 64 of 162 62 and 56; 256 of 1,263 182 and 138.  Where two blocks share a CU a
+// window takes longer: 512 targets of 261 moves 85 and 93, of 1,256 185 and 174, of
+// 5,547 928 and 700; 1,024 of 5,364 942 and 1,040.
+constexpr int kWalkTileTargets = 256, kWalkTileMoves = 64;          // a block per CU
+constexpr int kWalkTileTargetsLong = 512, kWalkTileMovesLong = 1024;   // two
+constexpr int kTileWalkThreads = 512;
+constexpr int kTileWalkLevels = 3;   // the longest hop is 2^3 moves
+constexpr int kTileWalkPitch = 18;   // dwords of a row of classes: 16 and one of none on either side
+
+struct TileWalkShared {
+    int32_t v[64 * 64];
+    uint32_t cls[66 * kTileWalkPitch];
+    uint16_t next[kTileWalkLevels + 1][64 * 64];   // the cell 1, 2, 4, 8, 16 moves on
+};
+
+__global__ __launch_bounds__(kTileWalkThreads) void k_walk_tile(
+    const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot, const int32_t* __restrict__ trc,
+    int32_t n, int32_t parity, const int32_t* __restrict__ len, const int64_t* __restrict__ off,
+    int32_t* __restrict__ cells, const int32_t* __restrict__ order, WalkOut out) {
+    __shared__ __attribute__((aligned(16))) TileWalkShared sh;
+    typedef uint16_t v4u16 __attribute__((ext_vector_type(4)));
+    constexpr int kGroups = 64 * 64 / 4 / kTileWalkThreads;   // groups of four cells a thread
+    constexpr int kRowStep = kTileWalkThreads / 16;
+    const int t = threadIdx.x, lane = lane_id();
+    const int i = order ? __builtin_amdgcn_readfirstlane(order[blockIdx.x]) : (int)blockIdx.x;
+    const int steps = __builtin_amdgcn_readfirstlane(len[i]);
+    if (t < kLanes) walk_results(out, i, n, len, off);
+    if (steps < 0) return;
+    const MazeDev md = mazes[__builtin_amdgcn_readfirstlane(tslot[i])];
+    const int32_t* __restrict__ V = parity ? md.V[1] : md.V[0];
+    int r = __builtin_amdgcn_readfirstlane(trc[2 * i]), c = __builtin_amdgcn_readfirstlane(trc[2 * i + 1]);
+    int32_t* __restrict__ to = cells + off[i];
+    for (int q = t; q < 66 * kTileWalkPitch; q += kTileWalkThreads) sh.cls[q] = 0;   // (the frame stays 0)
+    const int row = t >> 4, col = 4 * (t & 15);
+    v4i32 ld[kGroups];
+    auto load = [&](int R0, int C0) {
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            const int R = R0 + row + g * kRowStep, cs = C0 + col;
+            const bool ok = R >= 0 && R < md.H && cs >= 0 && cs < md.pitch;   // a chunk lies inside or outside a row
+            ld[g] = *(const __attribute__((address_space(1))) v4i32*)(V + (ok ? (int64_t)R * md.pitch + cs : 0));
+        }
+    };
+    int R0 = r - 32, C0 = (c - 30) & ~3;
+    load(R0, C0);
+    for (int s = 0, v0 = md.K - steps; s < steps;) {   // v0: activity of the current cell
+        lds_barrier();   // the last window's tables are no longer read
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            const int wr = row + g * kRowStep, R = R0 + wr, cs = C0 + col;
+            const bool rok = R >= 0 && R < md.H && cs >= 0;
+            uint32_t cls = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int v = rok && cs + e < md.W ? ld[g][e] : 0;
+                cls |= (v > 0 ? 1u << ((uint32_t)v % 3u) : 0u) << (8 * e);
+            }
+            *(__attribute__((address_space(3))) v4i32*)(sh.v + 64 * wr + col) = ld[g];
+            sh.cls[(wr + 1) * kTileWalkPitch + 1 + (t & 15)] = cls;
+        }
+        lds_barrier();
+        v4u16 own[kGroups];
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            const int wr = row + g * kRowStep;
+            const uint32_t* p = sh.cls + (wr + 1) * kTileWalkPitch + 1 + (t & 15);
+            const uint32_t own_cls = p[0];
+            const uint32_t want = ((own_cls << 1) & 0x06060606u) | ((own_cls >> 2) & 0x01010101u);
+            // the first neighbour wanted, as (row + 1) << 2 | column + 1; 5: none
+            uint32_t code = 0x05050505u;
+#pragma unroll
+            for (int d = 8; d >= 0; --d) {
+                if (d == 4) continue;
+                const uint32_t* q = p + (d / 3 - 1) * kTileWalkPitch;
+                const uint32_t nb = d % 3 == 0   ? __builtin_amdgcn_alignbyte(q[0], q[-1], 3)
+                                    : d % 3 == 1 ? q[0]
+                                                 : __builtin_amdgcn_alignbyte(q[1], q[0], 1);
+                uint32_t m = nb & want;
+                m = (m | m >> 1 | m >> 2) & 0x01010101u;
+                m = (m << 8) - m;
+                code = (code & ~m) | ((uint32_t)(((d / 3) << 2 | d % 3) * 0x01010101u) & m);
+            }
+            if (wr == 0 || wr == 63) code = 0x05050505u;
+            if (col == 0) code = (code & ~0xffu) | 5u;
+            if (col == 60) code = (code & 0x00ffffffu) | 5u << 24;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t k = (code >> (8 * e)) & 0xfu;
+                own[g][e] = (uint16_t)(64 * wr + col + e + (k >> 2) * 64 + (k & 3) - 65);
+            }
+            *(__attribute__((address_space(3))) v4u16*)(sh.next[0] + 64 * wr + col) = own[g];
+        }
+        lds_barrier();
+#pragma unroll
+        for (int l = 1; l <= kTileWalkLevels; ++l) {
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) own[g][e] = sh.next[l - 1][own[g][e]];
+                *(__attribute__((address_space(3))) v4u16*)(sh.next[l] + 64 * (row + g * kRowStep) + col) = own[g];
+            }
+            lds_barrier();
+        }
+        // the chain, by every wave for itself; lane h keeps the cell after 8 h moves
+        const int entry = (r - R0) * 64 + (c - C0);
+        int at = entry, log = 0;
+        for (int h = 0; h < kLanes; ++h) {
+            log = lane == h ? at : log;
+            const int to_cell = __builtin_amdgcn_readfirstlane((int)sh.next[kTileWalkLevels][at]);
+            if (to_cell == at) break;
+            at = to_cell;
+        }
+        const int moves = min(__builtin_amdgcn_readfirstlane(sh.v[at]) - v0, steps - s);
+        const int from_r = R0, from_c = C0;
+        const int dr = (at >> 6) - (entry >> 6), dc = (at & 63) - (entry & 63);
+        r = R0 + (at >> 6);
+        c = C0 + (at & 63);
+        if (moves <= 0) return;   // (a map that is not an activity map: no move)
+        if (s + moves < steps) {
+            // the most room in the direction the path went; less than a third of
+            // the moves counts as none
+            R0 = r - (3 * abs(dr) < moves ? 32 : (dr < 0 ? 62 : 1));
+            C0 = (c - (3 * abs(dc) < moves ? 30 : (dc < 0 ? 59 : 1))) & ~3;
+            load(R0, C0);
+        }
+        for (int k0 = t - lane; k0 < moves; k0 += kTileWalkThreads) {
+            const int k = k0 + lane;
+            int q = __shfl(log, min(k >> kTileWalkLevels, kLanes - 1));   // (every lane takes part)
+#pragma unroll
+            for (int b = 0; b < kTileWalkLevels; ++b)
+                if (k >> b & 1) q = sh.next[b][q];
+            if (k < moves) to[s + k] = (from_r + (q >> 6)) * md.W + from_c + (q & 63);
+        }
+        s += moves;
+        v0 += moves;
+    }
+    if (t == 0) to[steps] = r * md.W + c;
+}
+
 // ---- random ties and Euclidean reconstruction ------------------------------
 
 // SplitMix64 output function on seed ^ (target << 32) ^ step: the counter-based
@@ -1205,8 +1363,14 @@ hipError_t launch_lengths_offsets(const MazeDev* mazes, const int32_t* tgt_slot,
 
 hipError_t launch_walk(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc,
                        int32_t n_tgt, int32_t parity, const int32_t* len, const int64_t* offsets,
-                       int32_t* cells, hipStream_t s, const int32_t* order, const WalkOut& out) {
+                       int32_t* cells, int64_t total, hipStream_t s, const int32_t* order, const WalkOut& out) {
     if (n_tgt <= 0) return hipSuccess;
+    if ((n_tgt <= kWalkTileTargets && total >= (int64_t)n_tgt * kWalkTileMoves) ||
+        (n_tgt <= kWalkTileTargetsLong && total >= (int64_t)n_tgt * kWalkTileMovesLong)) {
+        hipLaunchKernelGGL(k_walk_tile, dim3(n_tgt), dim3(kTileWalkThreads), 0, s, mazes, tgt_slot, tgt_rc, n_tgt,
+                           parity, len, offsets, cells, order, out);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_walk<false>, dim3((n_tgt + kWalkWaves - 1) / kWalkWaves), dim3(kLanes * kWalkWaves), 0, s,
                        mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, order, nullptr, 0, out);
     return hipGetLastError();

@@ -1552,7 +1552,7 @@ class Solver {
             HIP_TRY(launch_walk_random(d_mazes, dev(0), dev(at_rc), dev(at_local), n, vparity(), seed, d_len, d_off,
                                        cells_out, stream, dev(at_order), out));
         else
-            HIP_TRY(launch_walk(d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off, cells_out, stream,
+            HIP_TRY(launch_walk(d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off, cells_out, total, stream,
                                 dev(at_order), out));
         if (n == 0) HIP_TRY(hipMemcpyAsync(off_out, d_off, sizeof(int64_t), hipMemcpyDeviceToDevice, stream));
         if (src_out)
@@ -2050,7 +2050,7 @@ static omap_status_t retire_paths(omap_engine_s* e) {
         R.cells_cap = want;
     }
     if (n > 0 && R.total > 0)
-        HIP_TRY(launch_walk(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, d_off, R.d_cells, xs));
+        HIP_TRY(launch_walk(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, d_off, R.d_cells, R.total, xs));
     // host layout: last_round | visits | cell visits | cells | activity maps
     const size_t b_lr = up(4 * (size_t)sv.cap_slots), b_v = up(8 * (size_t)sv.cap_slots * kSpread);
     size_t act_bytes = 0;
@@ -2392,7 +2392,8 @@ static omap_status_t extract_noalloc(omap_plan_t plan, int32_t* len_dev, int64_t
         return fail(OMAP_ERR_BUFFER_TOO_SMALL, "paths need %lld cells, capacity %lld", (long long)total,
                     (long long)cells_capacity);
     if (n > 0 && total > 0)
-        HIP_TRY(launch_walk(sv.d_mazes, d_tslot, d_trc, n, sv.vparity(), len_dev, offsets_dev, cells_dev, sv.stream));
+        HIP_TRY(launch_walk(sv.d_mazes, d_tslot, d_trc, n, sv.vparity(), len_dev, offsets_dev, cells_dev, total,
+                            sv.stream));
     HIP_TRY(hipStreamSynchronize(sv.stream));
     return OMAP_OK;
 }
