@@ -595,12 +595,36 @@ constexpr int kWalkWaves = 4;
 // neighbours of block cell 9 (row 1, column 1): cells 0, 1, 2, 8, 10, 16, 17, 18
 constexpr uint64_t kNbr = 0x70507ull;
 
+// A wave reads what its lanes wrote, and writes the next window after every
+// lane's reads: LDS operations of a wave complete in order; the wave barrier
+// keeps the compiler from moving them past each other.
+__device__ __forceinline__ void walk_window_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Loads the window with corner (R0, C0), C0 a multiple of 4, into a wave's LDS;
 // cells outside the grid read -1.  Every chunk's load is issued before the
 // first is used, so the window costs one global round trip.
+// A window inside the grid needs no masks, which were most of its instructions
+// (4096 paths of a 23,170^2 map 0.674 -> 0.636 ms, 512 of 1021 x 1533 84.5 -> 79.1
+// us, Euclidean walks 0.910 -> 0.866 ms).
 __device__ __forceinline__ void walk_window(const MazeDev& md, const int32_t* V, int R0, int C0, int32_t* win) {
     const int lane = lane_id();
     v4i32 ld[kWinChunks / kLanes];
+    if (R0 >= 0 && R0 + kWinRows <= md.H && C0 >= 0 && C0 + kWinCols <= md.W) {   // (uniform)
+        const char* base = reinterpret_cast<const char*>(V + (int64_t)R0 * md.pitch + C0);
+        const uint32_t off = 4 * ((uint32_t)(lane >> 4) * (uint32_t)md.pitch + 4 * (lane & 15));
+#pragma unroll
+        for (int k = 0; k < kWinChunks / kLanes; ++k)
+            ld[k] = *(const __attribute__((address_space(1))) v4i32*)(base + (int64_t)k * (16 * (int64_t)md.pitch) + off);
+#pragma unroll
+        for (int k = 0; k < kWinChunks / kLanes; ++k)
+            *(__attribute__((address_space(3))) v4i32*)(win + 4 * (lane + kLanes * k)) = ld[k];
+        walk_window_sync();
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < kWinChunks / kLanes; ++k) {
         const int q = lane + kLanes * k;
@@ -622,19 +646,7 @@ __device__ __forceinline__ void walk_window(const MazeDev& md, const int32_t* V,
         for (int e = 0; e < 4; ++e) m[e] = (rok && cs + e >= 0 && cs + e < md.W) ? ld[k][e] : -1;
         *(__attribute__((address_space(3))) v4i32*)(win + wr * kWinCols + wc) = m;
     }
-    // the same wave reads what its lanes wrote: LDS operations of a wave
-    // complete in order; the wave barrier keeps the compiler from moving
-    // the reads above the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The next window overwrites this one only after every lane's reads.
-__device__ __forceinline__ void walk_window_done() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    walk_window_sync();
 }
 
 // Row and column of the current cell in its next window: the most room in the
@@ -784,7 +796,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk(
         if (3 * abs(dc_prev) < nst) dc_prev = 0;
         r = R0 + lr;
         c = C0 + lc;
-        walk_window_done();
+        walk_window_sync();
     }
 }
 
@@ -1098,7 +1110,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
                     seq[first + 3 * lane + j] = (uint16_t)(pos + ((q >> 3) - 3) * kWinCols + ((q & 7) - 3));
             }
         }
-        walk_window_done();
+        walk_window_sync();
         const int end = first + moves - 1;   // the last point stays pending
         for (int x0 = 1; x0 < end; x0 += kLanes) {
             const int x = x0 + lane;
@@ -1126,7 +1138,7 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
         // a move of less than a third of the moves counts as no direction
         if (3 * abs(dr_prev) < moves) dr_prev = 0;
         if (3 * abs(dc_prev) < moves) dc_prev = 0;
-        walk_window_done();
+        walk_window_sync();
     }
     if (pending) {
         if (WRITE && lane == 0) cells[o] = pr * W + pc;
