@@ -49,7 +49,7 @@ LDS_SOURCES = KERNEL_SOURCES + ("omap_kernels.hip",)
 # LDS: 256 CUs x 128 B per clock (32 banks of 4 B) x 2.4 GHz
 LDS_PEAK_GBS = 256 * 128 * 2.4
 # kernels whose LDS use is summarized: (part of the name in the counter files, label)
-LDS_KERNELS = (("omap::k_front(", "k_front"), ("omap::k_walk(", "k_walk"))
+LDS_KERNELS = (("omap::k_front<", "k_front"), ("omap::k_walk<", "k_walk"))
 LDS_COUNTERS = ("SQ_INSTS_LDS", "SQ_LDS_IDX_ACTIVE", "SQ_LDS_BANK_CONFLICT", "SQ_WAVES")
 
 
@@ -196,7 +196,7 @@ def summarize_counters(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, out
     the counter reads for a plain pass of known size (bench.py --workload
     copy: 1 GiB read + 1 GiB written per launch)."""
     import paper_2004_00540_amd as omap
-    kern = "omap::k_front("
+    kern = "omap::k_front<"
     f_kib, n = _counter_per_dispatch(fetch_dir, "FETCH_SIZE", kern)
     w_kib, _ = _counter_per_dispatch(write_dir, "WRITE_SIZE", kern)
     cf_kib, _ = _counter_per_dispatch(copy_fetch_dir, "FETCH_SIZE", "neg_kernel")

@@ -18,10 +18,7 @@ constexpr int kSpread = 16;
 constexpr int kPosted = 64;
 // Bit-packed front propagation (omap_front.h): layers per tile visit, in steps
 // of 16, and the tile.
-#ifndef OMAP_FRONT_STEPS
-#define OMAP_FRONT_STEPS 4
-#endif
-constexpr int kFrontSteps = OMAP_FRONT_STEPS;
+constexpr int kFrontSteps = 4;
 constexpr int kFrontLayers = 16 * kFrontSteps;
 constexpr int kFrontTileRows = 64;
 constexpr int kFrontCols = 64;

@@ -584,10 +584,7 @@ __global__ __launch_bounds__(kScanBlock) void k_block_offsets(const int32_t* __r
 // ever matches.  The window is placed so that the path's direction over the
 // previous window has the most room ahead; it is reloaded when the 8 x 8
 // block around the current cell no longer fits.
-#ifndef OMAP_WALK_ROWS
-#define OMAP_WALK_ROWS 48
-#endif
-constexpr int kWinRows = OMAP_WALK_ROWS;
+constexpr int kWinRows = 48;
 constexpr int kWinCols = 64;                       // window row: 64 cells = 16 chunks of 4
 constexpr int kWinChunks = kWinRows * kWinCols / 4;
 static_assert(kWinRows >= 16 && kWinChunks % kLanes == 0, "walk window");

@@ -48,17 +48,15 @@ std::vector<Candidate> candidates(int32_t use) {
         c.o.tile_rows = TH;
         out.push_back(c);
     };
-    add(OMAP_SCHEDULE_DEFAULT, 0, 0, 0);   // the reference: the defaults of this use
+    // the reference: the defaults of this use, which every shape of the bit-sliced
+    // schedule runs as too; then shapes of the integer sweep
+    add(OMAP_SCHEDULE_DEFAULT, 0, 0, 0);
     if (use == OMAP_USE_PLAN) {
-        const int a[][3] = {{16, 1, 16}, {16, 1, 32}, {12, 1, 12}, {12, 1, 24}, {8, 1, 8}, {8, 1, 16},
+        const int a[][3] = {{16, 1, 32}, {12, 1, 12}, {12, 1, 24}, {8, 1, 8}, {8, 1, 16},
                             {16, 2, 16}, {12, 2, 16}, {32, 2, 32}, {16, 4, 32}};
         for (auto& v : a) add(OMAP_SCHEDULE_ACTIVE, v[0], v[1], v[2]);
-        const int b[][2] = {{16, 16}, {16, 32}, {8, 16}};
-        for (auto& v : b) add(OMAP_SCHEDULE_BITS, v[0], 0, v[1]);
     } else {
-        const int b[][2] = {{16, 16}, {16, 32}, {16, 64}, {8, 8}, {8, 16}, {8, 32}};
-        for (auto& v : b) add(OMAP_SCHEDULE_BITS, v[0], 0, v[1]);
-        const int a[][3] = {{12, 2, 16}, {16, 2, 16}, {12, 2, 32}, {8, 2, 16}, {16, 1, 16}, {16, 4, 32},
+        const int a[][3] = {{12, 1, 12}, {8, 1, 16}, {12, 2, 16}, {16, 2, 16}, {12, 2, 32}, {8, 2, 16}, {16, 1, 16}, {16, 4, 32},
                             {24, 2, 24}};
         for (auto& v : a) add(OMAP_SCHEDULE_ACTIVE, v[0], v[1], v[2]);
     }
