@@ -27,7 +27,10 @@
 // buffer; after the last step exactly the tile's 64 rows are left.  A wave whose
 // rows gain no cell in the first layer has nothing to do in any (its rows are
 // settled, and nothing outside them comes near its middle rows in 16 layers);
-// if no wave gains a cell the visit is over.
+// if no wave gains a cell the visit is over.  A wave that gains cells in some of
+// its words only advances those and the words beside them: three, four or six of
+// the six (26,000^2 with 5000 sources 8.49 -> 8.23 ms of propagation, 512 mazes
+// 3.62 -> 3.30, 2000^2 dense 0.665 -> 0.613, 23170^2 1.62 -> 1.525).
 //
 // The registers of the 16 layers of the tile's own words form a unary code of
 // each cell's arrival, turned into 4 bit planes by 11 selects per word; the
@@ -59,6 +62,8 @@
 // per-lane loop to write activity) a batch of 512 mazes takes 9.0 instead of
 // 21.3 ms.
 #pragma once
+
+#include <type_traits>
 
 #include "omap_sweep.h"
 
@@ -124,6 +129,9 @@ __device__ __forceinline__ void front_layer(uint32_t (&r)[NW], const uint32_t (&
 // m ? a : b, bit by bit.
 __device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
 
+template <int N>
+constexpr std::integral_constant<int, N> at{};
+
 // Step k of a visit, rows 16 k + 32 g .. + 63 and words W0 .. W0 + NW - 1 of
 // the region (one wave).  Of the tile's words it takes OWN from T0 on (their
 // arrivals, and in the last step their sets alone).
@@ -155,28 +163,75 @@ __device__ __forceinline__ void front_step(FrontShared& sh, int k, int g, int la
     // The arrivals of 8 layers are coded at a time (fewer registers): after
     // layers 1 .. 8 of a half, in4 = in the set after 4, in2 = after 2 or 6 by
     // in4, in1 = after 1, 3, 5 or 7 by both.
-    uint32_t in8[OWN], in4[2][OWN], in2[2][OWN], in1[2][OWN], before[OWN];
+    uint32_t in8[OWN], in4[2][OWN] = {}, in2[2][OWN] = {}, in1[2][OWN] = {}, before[OWN];
+    // layers 2 .. 16 on words S .. S + N - 1 of the wave's (rolled over the halves:
+    // the code is two thirds as long, and a short propagation fetches it cold)
+    auto layers = [&](auto s_, auto n_) {
+        constexpr int S = decltype(s_)::value, N = decltype(n_)::value;
+        uint32_t q[N], e[N];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        uint32_t h[7][OWN];
-#pragma unroll
-        for (int j = 0; j < 7; ++j) {
-            if (half != 0 || j != 0) front_layer<NW>(r, f);
-#pragma unroll
-            for (int c = 0; c < OWN; ++c) h[j][c] = r[C0 + c];
+        for (int w = 0; w < N; ++w) {
+            q[w] = r[S + w];
+            e[w] = f[S + w];
         }
-        front_layer<NW>(r, f);
+        // (a word of the tile outside S .. keeps its cells)
+        auto own_word = [&](int c) {
+            return C0 + c >= S && C0 + c < S + N ? q[C0 + c >= S && C0 + c < S + N ? C0 + c - S : 0] : r[C0 + c];
+        };
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int c = 0; c < OWN; ++c) {
-            in4[half][c] = h[3][c];
-            in2[half][c] = bit_select(h[3][c], h[1][c], h[5][c]);
-            in1[half][c] = bit_select(in2[half][c], bit_select(h[3][c], h[0][c], h[4][c]),
-                                      bit_select(h[3][c], h[2][c], h[6][c]));
-            if (half == 0) in8[c] = r[C0 + c];
-            else before[c] = h[6][c];
-            // (or the compiler moves the selects down to their use and keeps every h)
-            asm volatile("" : "+v"(in4[half][c]), "+v"(in2[half][c]), "+v"(in1[half][c]));
+            for (int c = 0; c < OWN; ++c) {
+                in8[c] = own_word(c);
+                in4[0][c] = in4[1][c];
+                in2[0][c] = in2[1][c];
+                in1[0][c] = in1[1][c];
+            }
+            uint32_t h[7][OWN];
+#pragma unroll
+            for (int j = 0; j < 7; ++j) {
+                if (j != 0 || half != 0) front_layer<N>(q, e);
+#pragma unroll
+                for (int c = 0; c < OWN; ++c) h[j][c] = own_word(c);
+            }
+            front_layer<N>(q, e);
+#pragma unroll
+            for (int c = 0; c < OWN; ++c) {
+                in4[1][c] = h[3][c];
+                in2[1][c] = bit_select(h[3][c], h[1][c], h[5][c]);
+                in1[1][c] = bit_select(in2[1][c], bit_select(h[3][c], h[0][c], h[4][c]),
+                                       bit_select(h[3][c], h[2][c], h[6][c]));
+                before[c] = h[6][c];
+                // (or the compiler moves the selects down to their use and keeps every h)
+                asm volatile("" : "+v"(in4[1][c]), "+v"(in2[1][c]), "+v"(in1[1][c]));
+            }
         }
+#pragma unroll
+        for (int w = 0; w < N; ++w) r[S + w] = q[w];
+    };
+    // A cell that arrives in these layers lies within 15 columns of one that
+    // arrived in the first, so only the words that gained a cell and the next ones
+    // are advanced (the others hold what the layers would leave).
+    if constexpr (NW == 6) {
+        const uint32_t g01 = (r[0] ^ first[0]) | (r[1] ^ first[1]), g45 = (r[4] ^ first[4]) | (r[5] ^ first[5]);
+        const uint32_t g2 = r[2] ^ first[2], g3 = r[3] ^ first[3];
+        if (__ballot((g45 | g3) != 0) == 0) {
+            if (__ballot(g2 != 0) == 0) layers(at<0>, at<3>);
+            else layers(at<0>, at<4>);
+        } else if (__ballot((g01 | g2) != 0) == 0) {
+            if (__ballot(g3 != 0) == 0) layers(at<3>, at<3>);
+            else layers(at<2>, at<4>);
+        } else if (__ballot((g01 | g45) != 0) == 0) {
+            layers(at<1>, at<4>);
+        } else {
+            layers(at<0>, at<6>);
+        }
+    } else if constexpr (NW == 4) {
+        if (__ballot(((r[2] ^ first[2]) | (r[3] ^ first[3])) != 0) == 0) layers(at<0>, at<3>);
+        else if (__ballot(((r[0] ^ first[0]) | (r[1] ^ first[1])) != 0) == 0) layers(at<1>, at<3>);
+        else layers(at<0>, at<4>);
+    } else {
+        layers(at<0>, at<NW>);
     }
     if (mid) {
 #pragma unroll

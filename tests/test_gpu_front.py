@@ -59,3 +59,33 @@ def test_front_batch_of_mixed_layer_counts_and_reuse(schedule):
                 A, L, *_ = oracle_solution(m, layers[i])
                 assert np.array_equal(b.activity(i).cpu().numpy(), A), (rep, i)
                 assert (infos[i]["layers"], infos[i]["reached_cells"]) == (L, int((A > 0).sum())), (rep, i)
+
+
+@pytest.mark.parametrize("joined", [False, True])
+def test_front_in_some_words(joined):
+    """Fronts in every subset of six neighbouring 32-column words: a wave
+    advances the words that gain cells and those beside them."""
+    import oracle
+    import paper_2004_00540_amd as omap
+    H, words, first = 150, 10, 2
+    rng = np.random.default_rng(61)
+    base = (rng.random((H, 32 * words)) < 0.35).astype(np.uint8)
+    ms = []
+    for subset in range(1, 64):
+        occ = base.copy()
+        src = []
+        for w in range(words):
+            c0, c1 = 32 * w, 32 * w + 31
+            if not joined:
+                occ[:, [c0, c1]] = 1               # a chamber per word
+            if 0 <= w - first < 6 and subset >> (w - first) & 1:
+                r, c = 40 + 10 * (w - first), c0 + (1, 16, 30)[w % 3]
+                occ[r, c] = 0
+                src.append((r, c))
+        ms.append((occ, np.array(src, np.int32)))
+    with omap.Batch([(to_dev(o), s, s[:1]) for o, s in ms]) as b:
+        infos = b.propagate()
+        for i, (o, s) in enumerate(ms):
+            d, ecc = oracle.bfs(o, s)
+            assert infos[i]["layers"] == ecc, i + 1
+            assert np.array_equal(b.activity(i).cpu().numpy(), oracle.activity_from_bfs(d, ecc)), i + 1
