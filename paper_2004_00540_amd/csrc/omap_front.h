@@ -49,18 +49,20 @@
 //
 // What bounds it: on one large maze the chain of rounds (launch gap, list and
 // region loads, four steps, claims), 64 layers per round instead of 16 of the
-// two-wave integer visit it replaced: 23170^2 maze with L* = 7124 per pass
-// (load, propagate, 4096 paths) 6.4 -> 2.2 ms, 4096^2 corridors (L* = 11,000)
-// 12.4 -> 3.3 ms; with fronts everywhere (26,000^2, 5000 sources, 650 layers)
-// VALU issue and the activity writes, 67.7 -> 10.0 ms.  A lone visit takes 10 us:
-// list entry 0.9, region 0.6, steps 2.1 + 1.7 + 1.3 + 1.2, claims and activity
-// 1.3, and 1.6 us pass before the next round's first wave.  Tiles of 64 x 128
-// cells take a third fewer operations per cell but 3 us longer per visit:
-// 26,000^2 propagation 9.0 against 8.6 ms here, corridors 2.85 against 2.30.
-// Against the earlier
-// bit-sliced sweep (one row of 1984 columns per wave, 8 layers per visit, a
-// per-lane loop to write activity) a batch of 512 mazes takes 9.0 instead of
-// 21.3 ms.
+// two-wave integer visit it replaced: 12 us a round; a pass over a 23170^2 map
+// (load, propagate with L* = 7124, 4096 paths) 6.4 -> 2.3 ms, over 4096^2 corridors
+// (L* = 11,178) 12.4 -> 2.9, of which propagation 1.53 and 2.19.
+// With fronts everywhere (26,000^2, 5000 sources, 650 layers) VALU issue, 54 % of
+// the cycles: 485,000 visits of 5,900 VALU and 1,800 scalar instructions; the
+// whole pass 67.7 -> 9.7 ms.  A lone visit takes 10 us: list entry 0.9, region 0.6,
+// steps 2.1 + 1.7 + 1.3 + 1.2, claims and activity 1.3, and 1.6 us pass before the
+// next round's first wave.  Tiles of 64 x 128 cells take a third fewer operations
+// per cell but 3 us longer per visit: 26,000^2 propagation 9.0 against 8.6 ms at the
+// time, corridors 2.85 against 2.30; 32 layers a round take half the operations per
+// layer but twice the visits: 11.3 against 8.5, corridors 2.79 against 2.21, and
+// only 512 mazes gain, 3.41 against 3.55.  Against the earlier bit-sliced sweep (one
+// row of 1984 columns per wave, 8 layers per visit, a per-lane loop to write
+// activity) a batch of 512 mazes takes 7.7 instead of 21.6 ms.
 #pragma once
 
 #include <type_traits>

@@ -1344,13 +1344,13 @@ hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* r
 
 size_t scan_work_bytes(int32_t n) {
     const size_t nb = ((size_t)n + kScanBlock - 1) / kScanBlock;
-    return n <= kScanLengths ? 0 : 8 * nb + 4 * kBuckets * (nb + 1);
+    return n <= kScanOneBlock ? 0 : 8 * nb + 4 * kBuckets * (nb + 1);
 }
 
 hipError_t launch_lengths_offsets(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc, int32_t n_tgt,
                                   int32_t parity, int32_t* len, int64_t* offsets, int32_t* order, void* work,
                                   uint64_t* posted, uint32_t tag, hipStream_t s) {
-    if (n_tgt > kScanLengths && work != nullptr) {
+    if (n_tgt > kScanOneBlock && work != nullptr) {
         const int nb = (n_tgt + kScanBlock - 1) / kScanBlock;
         int64_t* const sums = static_cast<int64_t*>(work);
         int32_t* const counts = reinterpret_cast<int32_t*>(sums + nb);

@@ -2011,7 +2011,7 @@ static omap_status_t retire_begin(omap_engine_s* e) {
         OK_TRY(sv.upload(d_trc, trc.data(), 8 * n));
     }
     HIP_TRY(launch_lengths_offsets(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, d_off, nullptr,
-                                   R.n > kScanLengths ? base + at_work : nullptr, nullptr, 0, sv.stream));
+                                   R.n > kScanOneBlock ? base + at_work : nullptr, nullptr, 0, sv.stream));
     OK_TRY(R.h_lo.reserve(lo_offsets_at(n) + 8 * (n + 1)));
     if (n > 0) HIP_TRY(hipMemcpyAsync(R.h_lo.p, d_len, 4 * n, hipMemcpyDeviceToHost, sv.stream));
     HIP_TRY(hipMemcpyAsync(R.h_lo.p + lo_offsets_at(n), d_off, 8 * (n + 1), hipMemcpyDeviceToHost, sv.stream));

@@ -1,4 +1,4 @@
-"""Offsets and paths of more targets than one block scans (4,096), at the edges of
+"""Offsets and paths of more targets than one block scans (1,024), at the edges of
 the scan's blocks (256 targets) and of the blocks that one block scans (256 of
 them), for each kind of walk and for an engine's retirement."""
 import numpy as np
@@ -10,7 +10,7 @@ from gpu_helpers import to_dev
 
 pytestmark = pytest.mark.gpu
 
-COUNTS = (4095, 4096, 4097, 4352, 4353, 65536, 65537)
+COUNTS = (1024, 1025, 1280, 4095, 4096, 4097, 4352, 4353, 65536, 65537)
 
 
 def _problem(n):
