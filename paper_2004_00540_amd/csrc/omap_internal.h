@@ -189,9 +189,13 @@ hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, con
                               const int32_t* tgt_local, int32_t n_tgt, int32_t parity, uint64_t seed,
                               const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s,
                               const int32_t* order, const WalkOut& out);
-hipError_t launch_walk_euclid(bool write, const MazeDev* mazes, const int32_t* tgt_slot,
-                              const int32_t* tgt_rc, int32_t n_tgt, int32_t parity, int32_t* len,
-                              const int64_t* offsets, int32_t* cells, hipStream_t s, const WalkOut& out);
+// offsets: cells are written there (the lengths are known); none: the lengths are
+// counted, and with cells (stride apart per target) the paths written as well.
+hipError_t launch_walk_euclid(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc, int32_t n_tgt,
+                              int32_t parity, int32_t* len, const int64_t* offsets, int32_t* cells, int64_t stride,
+                              hipStream_t s, const WalkOut& out);
+hipError_t launch_gather_paths(const int32_t* points, int64_t stride, int32_t n_tgt, const int32_t* len,
+                               const int64_t* offsets, int32_t* cells, hipStream_t s, const WalkOut& out);
 hipError_t launch_source_index(const MazeDev* mazes, const int32_t* tgt_slot, int32_t n_tgt,
                                const int32_t* len, const int64_t* offsets, const int32_t* cells,
                                const int32_t* src_sorted, const int32_t* src_base, const int32_t* src_n,

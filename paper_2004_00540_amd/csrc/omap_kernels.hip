@@ -1013,18 +1013,22 @@ __device__ __forceinline__ uint64_t every_other(uint64_t m, bool after_drop) {
     return (on_even & even) | (m & ~on_even & ~even);
 }
 
-template <bool WRITE>
+// COUNT: the path's length goes to len.  WRITE: its cells go to cells, from off[i]
+// on or, where they are counted as well, from i * stride on (at most stride of
+// them); k_gather_paths moves them once the offsets are known, in place of a second
+// walk: 2,048 paths of a 2,048^2 map, asked for and taken, 0.867 -> 0.635 ms.
+template <bool WRITE, bool COUNT>
 __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
     const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot, const int32_t* __restrict__ trc, int32_t n,
     int32_t parity, int32_t* __restrict__ len, const int64_t* __restrict__ off, int32_t* __restrict__ cells,
-    WalkOut out) {
+    int64_t stride, WalkOut out) {
     __shared__ __attribute__((aligned(16))) int32_t win_all[kWalkWaves][kWinRows * kWinCols];
     __shared__ uint16_t seq_all[kWalkWaves][3 * kLanes + 8];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id();
     const int i = blockIdx.x * kWalkWaves + wave;
     if (i >= n) return;
-    if (WRITE) walk_results(out, i, n, len, off);
+    if (!COUNT) walk_results(out, i, n, len, off);
     const int slot = __builtin_amdgcn_readfirstlane(tslot[i]);
     const MazeDev md = mazes[slot];
     const int32_t* __restrict__ V = parity ? md.V[1] : md.V[0];
@@ -1035,11 +1039,12 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
     int c = __builtin_amdgcn_readfirstlane(trc[2 * i + 1]);
     int v = __builtin_amdgcn_readfirstlane(V[(int64_t)r * md.pitch + c]);
     if (v <= 0) {
-        if (!WRITE && lane == 0) len[i] = -1;
+        if (COUNT && lane == 0) len[i] = -1;
         return;
     }
     const int K = md.K, W = md.W;
-    int64_t o = WRITE ? off[i] : 0;
+    int64_t o = COUNT ? (WRITE ? i * stride : 0) : off[i];
+    const int64_t o_end = COUNT ? o + stride : INT64_MAX;
     int count = 1;   // points kept
     if (WRITE && lane == 0) cells[o] = r * W + c;
     ++o;
@@ -1116,8 +1121,8 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
             const uint64_t cand = __ballot(valid && diagonal(seq[valid ? x - 1 : 0], seq[valid ? x + 1 : 0]));
             const uint64_t drop = every_other(cand, dropped);
             const uint64_t keep = __ballot(valid) & ~drop;
-            if (WRITE && (keep >> lane & 1))
-                cells[o + __popcll(keep & ((1ull << lane) - 1))] = (R0 + (here >> 6)) * W + C0 + (here & 63);
+            const int64_t to = o + __popcll(keep & ((1ull << lane) - 1));
+            if (WRITE && (keep >> lane & 1) && to < o_end) cells[to] = (R0 + (here >> 6)) * W + C0 + (here & 63);
             o += __popcll(keep);
             count += __popcll(keep);
             dropped = (drop >> (min(end - x0, kLanes) - 1)) & 1;
@@ -1138,10 +1143,22 @@ __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
         walk_window_sync();
     }
     if (pending) {
-        if (WRITE && lane == 0) cells[o] = pr * W + pc;
+        if (WRITE && lane == 0 && o < o_end) cells[o] = pr * W + pc;
         ++count;
     }
-    if (!WRITE && lane == 0) len[i] = count - 1;
+    if (COUNT && lane == 0) len[i] = count - 1;
+}
+
+// Path i from points[i * stride] on to cells[off[i]] on, a wave each.
+__global__ void k_gather_paths(const int32_t* __restrict__ points, int64_t stride, int32_t n,
+                               const int32_t* __restrict__ len, const int64_t* __restrict__ off,
+                               int32_t* __restrict__ cells, WalkOut out) {
+    const int i = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    if (i >= n) return;
+    walk_results(out, i, n, len, off);
+    const int m = len[i] + 1;
+    const int64_t o = off[i];
+    for (int j = lane_id(); j < m; j += kLanes) cells[o + j] = points[i * stride + j];
 }
 
 // Index (in its maze's source list) of the source each path ends on; -1 if no
@@ -1395,17 +1412,23 @@ hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, con
     return hipGetLastError();
 }
 
-hipError_t launch_walk_euclid(bool write, const MazeDev* mazes, const int32_t* tgt_slot,
-                              const int32_t* tgt_rc, int32_t n_tgt, int32_t parity, int32_t* len,
-                              const int64_t* offsets, int32_t* cells, hipStream_t s, const WalkOut& out) {
+hipError_t launch_walk_euclid(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc, int32_t n_tgt,
+                              int32_t parity, int32_t* len, const int64_t* offsets, int32_t* cells, int64_t stride,
+                              hipStream_t s, const WalkOut& out) {
     if (n_tgt <= 0) return hipSuccess;
     const dim3 grid((n_tgt + kWalkWaves - 1) / kWalkWaves), block(kLanes * kWalkWaves);
-    if (write)
-        hipLaunchKernelGGL(k_walk_euclid<true>, grid, block, 0, s, mazes, tgt_slot, tgt_rc, n_tgt, parity, len,
-                           offsets, cells, out);
-    else
-        hipLaunchKernelGGL(k_walk_euclid<false>, grid, block, 0, s, mazes, tgt_slot, tgt_rc, n_tgt, parity, len,
-                           offsets, cells, out);
+    const auto kernel = offsets != nullptr ? k_walk_euclid<true, false>
+                        : cells != nullptr ? k_walk_euclid<true, true> : k_walk_euclid<false, true>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, mazes, tgt_slot, tgt_rc, n_tgt, parity, len, offsets, cells, stride,
+                       out);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather_paths(const int32_t* points, int64_t stride, int32_t n_tgt, const int32_t* len,
+                               const int64_t* offsets, int32_t* cells, hipStream_t s, const WalkOut& out) {
+    if (n_tgt <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_gather_paths, dim3((n_tgt + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlockThreads), 0, s,
+                       points, stride, n_tgt, len, offsets, cells, out);
     return hipGetLastError();
 }
 

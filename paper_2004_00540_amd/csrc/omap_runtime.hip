@@ -1525,16 +1525,32 @@ class Solver {
             }
             t0 += m;
         }
+        // A Euclidean path learns its length by walking.  Where the layers are known
+        // (a path of d moves up the activity takes at most d more sideways) and the
+        // caller has room for cells, the walk writes its points to scratch as it
+        // counts them; else, or past kEuclidPoints, it walks twice.
+        constexpr int64_t kEuclidPoints = int64_t(1) << 24;
+        const size_t at_points = at_work + up(scan_work_bytes(n));
+        int64_t stride = 0;
+        if (mode == 2 && cells_out != nullptr && capacity > 0 && n > 0) {
+            int64_t layers = 0;
+            for (int32_t k : which) layers = slots[k].finalized ? std::max(layers, slots[k].layers) : INT64_MAX;
+            if (layers < kEuclidPoints && (2 * layers + 1) * n <= kEuclidPoints) stride = 2 * layers + 1;
+        }
         char* base = nullptr;
-        OK_TRY(scratch(at_work + scan_work_bytes(n), &base));
+        if (stride > 0 && scratch(at_points + sizeof(int32_t) * (size_t)(stride * n), &base) != OMAP_OK) {
+            (void)hipGetLastError();
+            stride = 0;
+        }
+        if (stride == 0) OK_TRY(scratch(at_work + scan_work_bytes(n), &base));
         auto dev = [&](size_t at) { return reinterpret_cast<int32_t*>(base + at); };
         int32_t* const d_len = dev(at_len);
         int64_t* const d_off = reinterpret_cast<int64_t*>(base + at_off);
         if (n > 0) OK_TRY(upload(base, stage.data(), staged));
         // lengths and offsets (the Euclidean walk learns its lengths by walking)
         if (mode == 2)
-            HIP_TRY(launch_walk_euclid(false, d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, nullptr, nullptr, stream,
-                                       {}));
+            HIP_TRY(launch_walk_euclid(d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, nullptr,
+                                       stride > 0 ? dev(at_points) : nullptr, stride, stream, {}));
         HIP_TRY(launch_lengths_offsets(mode == 2 ? nullptr : d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off,
                                        mode == 2 ? nullptr : dev(at_order), dev(at_work), h_post, ++post_tag, stream));
         uint64_t posted = 0;
@@ -1545,8 +1561,10 @@ class Solver {
             return fail(OMAP_ERR_BUFFER_TOO_SMALL, "paths need %lld cells, capacity %lld",
                         (long long)total, (long long)capacity);
         const WalkOut out{len_out, off_out};
-        if (mode == 2)
-            HIP_TRY(launch_walk_euclid(true, d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off, cells_out, stream,
+        if (stride > 0)
+            HIP_TRY(launch_gather_paths(dev(at_points), stride, n, d_len, d_off, cells_out, stream, out));
+        else if (mode == 2)
+            HIP_TRY(launch_walk_euclid(d_mazes, dev(0), dev(at_rc), n, vparity(), d_len, d_off, cells_out, 0, stream,
                                        out));
         else if (mode == 1)
             HIP_TRY(launch_walk_random(d_mazes, dev(0), dev(at_rc), dev(at_local), n, vparity(), seed, d_len, d_off,

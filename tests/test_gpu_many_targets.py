@@ -56,3 +56,24 @@ def test_many_targets(n):
     ref = _expand(oracle.walk(A, m.sources, free), pick)
     for g, r in zip((res.lengths, res.offsets, res.cells), ref):
         assert np.array_equal(g, r), n
+
+
+@pytest.mark.parametrize("layers", [-1, 0, 40, 1 << 24])
+def test_euclidean_walked_once_or_twice(layers):
+    """The walk writes its points as it counts them where the layers are known and
+    few enough, and walks twice otherwise: plans and a batch, layers known or not."""
+    import paper_2004_00540_amd as omap
+    m, _, free, pick = _problem(300)
+    d, ecc = oracle.bfs(m.occ, m.sources)
+    ref = _expand(oracle.walk_euclidean(oracle.activity_from_bfs(d, ecc if layers < 0 else layers), m.sources, free), pick)
+    occ = to_dev(m.occ)
+    for sync in (True, False):
+        with omap.Plan(occ, m.sources, free[pick]) as plan:
+            plan.propagate(layers, sync=sync)
+            for _ in range(2):
+                for g, r in zip(plan.paths("euclidean"), ref):
+                    assert np.array_equal(g.cpu().numpy(), r), (layers, sync)
+        with omap.Batch([(occ, m.sources, free[pick]), (occ, m.sources, free[pick][:0])]) as b:
+            b.propagate([layers, layers], sync=sync)
+            for g, r in zip(b.paths("euclidean")[:3], ref):
+                assert np.array_equal(g.cpu().numpy(), r), (layers, sync)
