@@ -391,9 +391,10 @@ typedef struct omap_tune_result {
  * activity maps and layer counts equal the defaults' bit for bit (any tile
  * schedule reaches the same fixpoint; a difference fails the call with
  * OMAP_ERR_HIP).  With the environment variable OMAP_TUNE_CACHE naming a
- * file, choices are appended to it keyed by device, use, number of mazes and
- * median maze size (powers of two), and a later call for the same key reads
- * them back without timing anything.  Synchronous; needs device memory for
+ * file, choices are appended to it keyed by device, use, number of mazes,
+ * median maze size (powers of two) and the kernels of the library's build, and
+ * a later call for the same key reads them back without timing anything
+ * (choices made with other kernels are not used).  Synchronous; needs device memory for
  * two copies of the sample's activity maps.  Errors: INVALID_ARG, those of
  * the create calls, OUT_OF_MEMORY, HIP. */
 omap_status_t omap_tune(const omap_maze_desc *mazes, int32_t n_mazes, int32_t use,

@@ -6,6 +6,7 @@ selection disabled (the kernels are integer-only, so nothing is lost).
 from __future__ import annotations
 
 import concurrent.futures
+import hashlib
 import os
 import re
 import subprocess
@@ -40,11 +41,25 @@ def variants() -> list:
     return [(int(t), int(c)) for t, c in re.findall(r"X\((\d+),\s*(\d+)\)", body)]
 
 
+def kernel_tag() -> str:
+    """Identifies the kernels of a build: a hash over csrc/ (the autotuner's saved
+    choices are valid for the kernels they were timed with)."""
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith((".h", ".hip")):
+            h.update(open(os.path.join(CSRC, name), "rb").read())
+    return h.hexdigest()[:12]
+
+
+def _defines(src: str) -> list:
+    return [f'-DOMAP_KERNEL_TAG="{kernel_tag()}"'] if src == "omap_tune.hip" else []
+
+
 def _compile_jobs(build_dir):
     jobs = []
     for src in SOURCES:
         obj = os.path.join(build_dir, src.replace(".hip", ".o"))
-        jobs.append(([os.path.join(CSRC, src)], obj))
+        jobs.append(([*_defines(src), os.path.join(CSRC, src)], obj))
     for t, c in variants():
         obj = os.path.join(build_dir, f"sweep_T{t}_C{c}.o")
         jobs.append(([f"-DOMAP_T={t}", f"-DOMAP_C={c}", os.path.join(CSRC, "omap_sweep_variant.hip")], obj))
@@ -91,7 +106,7 @@ def assembly(src: str = "omap_kernels.hip", defines=()) -> str:
     tag = "".join("_" + d.replace("=", "") for d in defines)
     out = os.path.join(HERE, "_build", src.replace(".hip", tag + ".s"))
     os.makedirs(os.path.dirname(out), exist_ok=True)
-    subprocess.check_call([HIPCC, *FLAGS, *("-D" + d for d in defines), "-I", INCLUDE, "-I", CSRC,
+    subprocess.check_call([HIPCC, *FLAGS, *_defines(src), *("-D" + d for d in defines), "-I", INCLUDE, "-I", CSRC,
                            "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", out])
     return out
 

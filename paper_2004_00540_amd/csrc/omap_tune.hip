@@ -5,7 +5,7 @@
 // defaults) -- the update is monotone and bounded by its fixpoint, so every
 // tile schedule must reach the same bits, and a difference is a defect, not a
 // tuning outcome -- and returns the fastest.  Choices are kept in a text
-// cache keyed by device, use and workload shape class.
+// cache keyed by device, use, workload shape class and the kernels timed.
 
 #include <algorithm>
 #include <cmath>
@@ -22,6 +22,10 @@
 
 #include "omap.h"
 #include "omap_internal.h"
+
+#ifndef OMAP_KERNEL_TAG
+#error "define OMAP_KERNEL_TAG (the build's hash of the kernel sources)"
+#endif
 
 namespace {
 
@@ -64,7 +68,9 @@ std::vector<Candidate> candidates(int32_t use) {
 }
 
 // Shape class of a workload: use, number of mazes and median cells per maze
-// (both in powers of two), and the device.
+// (both in powers of two), the device, and the kernels of this build: an option
+// set that was the fastest on other kernels need not be on these, and a saved
+// choice is taken without timing anything.
 std::string shape_key(const omap_maze_desc* m, int32_t n, int32_t use) {
     std::vector<double> cells(n);
     for (int32_t i = 0; i < n; ++i) cells[i] = (double)m[i].height * m[i].width;
@@ -78,7 +84,7 @@ std::string shape_key(const omap_maze_desc* m, int32_t n, int32_t use) {
     for (char& ch : arch)
         if (ch == ' ' || ch == ':') ch = '_';
     std::ostringstream k;
-    k << arch << " use" << use << " n2^" << nb << " cells2^" << cb;
+    k << arch << " use" << use << " n2^" << nb << " cells2^" << cb << " kernels=" OMAP_KERNEL_TAG;
     return k.str();
 }
 
