@@ -485,9 +485,10 @@ static Geometry make_geometry(int32_t H, int32_t W, const Options& o) {
     g.tiles_y = (H + o.TH - 1) / o.TH;
     g.v_bytes = (int64_t)g.pitch * H * 4;
     g.front = o.front != 0;
-    // strips start on 64-byte lines
+    // strips start on 64-byte lines, but for mazes so low that this would take more
+    // than the second activity buffer the integer sweeps have
     g.mrow = g.front ? 1 : g.mpitch;
-    g.mcol = g.front ? (H + 15) / 16 * 16 : 1;
+    g.mcol = !g.front ? 1 : (H < 16 ? H : (H + 15) / 16 * 16);
     g.m_bytes = (int64_t)g.mpitch * (g.front ? g.mcol : H) * 4;
     return g;
 }
@@ -1812,11 +1813,12 @@ static int64_t query_bytes(const Query& q, const Options& o) {
 }
 
 // The size by which a query counts as larger than the budget: two activity
-// buffers whatever the kernel keeps, so that the limit is the same for every
-// option set.
+// buffers and unpadded masks whatever the kernel keeps, which is never less, so
+// that the limit does not depend on it.
 static int64_t query_budget_bytes(const Query& q, const Options& o) {
     const Geometry g = make_geometry(q.H, q.W, o);
-    return query_bytes(q, o) + (g.front ? g.v_bytes : 0);
+    const int64_t held = maze_device_bytes(q.H, q.W, o), masks = o.asked.schedule == OMAP_SCHEDULE_BITS ? 3 : 1;
+    return query_bytes(q, o) - held + 2 * g.v_bytes + masks * g.mpitch * (int64_t)q.H * 4 + 4096;
 }
 
 static void query_release_occ(omap_engine_s* e, Query& q) {
