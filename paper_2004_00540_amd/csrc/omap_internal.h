@@ -189,6 +189,19 @@ hipError_t launch_walk_random(const MazeDev* mazes, const int32_t* tgt_slot, con
                               const int32_t* tgt_local, int32_t n_tgt, int32_t parity, uint64_t seed,
                               const int32_t* len, const int64_t* offsets, int32_t* cells, hipStream_t s,
                               const int32_t* order, const WalkOut& out);
+// Above these numbers of targets the random-tie and the Euclidean walks take a
+// lane per target, below a wave.  The wave's time grows with all the moves, the
+// lanes' stays that of the longest path until they fill the chip.  Both forms, us
+// for asking and taking the paths of a plan, lane / wave:
+//   random     49,152  950 / 863 (empty 1000^2, 227 moves)  861 / 507 (2048^2, 96)
+//             131,072 1610 / 2138                          1317 / 1202
+//           1,048,576 10.8 / 16.1 ms                        7.4 / 8.7 ms
+//   Euclidean  16,384 1887 / 1622                          1665 / 640
+//              24,000 1969 / 2190                          1723 / 1129
+//              65,536 2328 / 5344                          2150 / 2718
+//           1,048,576 19.4 / 80.1 ms                       14.1 / 39.5 ms
+// The lines lie where the wave form first loses to a lane per target on either.
+constexpr int kRandomLaneTargets = 65536, kEuclidLaneTargets = 20480;
 // offsets: cells are written there (the lengths are known); none: the lengths are
 // counted, and with cells (stride apart per target) the paths written as well.
 hipError_t launch_walk_euclid(const MazeDev* mazes, const int32_t* tgt_slot, const int32_t* tgt_rc, int32_t n_tgt,

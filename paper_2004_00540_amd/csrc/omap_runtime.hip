@@ -1533,7 +1533,7 @@ class Solver {
         constexpr int64_t kEuclidPoints = int64_t(1) << 24;
         const size_t at_points = at_work + up(scan_work_bytes(n));
         int64_t stride = 0;
-        if (mode == 2 && cells_out != nullptr && capacity > 0 && n > 0) {
+        if (mode == 2 && cells_out != nullptr && capacity > 0 && n > 0 && n <= kEuclidLaneTargets) {
             int64_t layers = 0;
             for (int32_t k : which) layers = slots[k].finalized ? std::max(layers, slots[k].layers) : INT64_MAX;
             if (layers < kEuclidPoints && (2 * layers + 1) * n <= kEuclidPoints) stride = 2 * layers + 1;
