@@ -117,9 +117,9 @@ hipError_t launch_fill(int32_t* p, int64_t n_elems, int32_t value, hipStream_t s
 hipError_t launch_seed(const RoundArgs& a, int32_t slot, const int32_t* src_rc, const int32_t* src_slot,
                        int32_t n_src, int32_t* bad_count, hipStream_t s);
 // posted (a word of pinned host memory, or null): the number of sources on
-// obstacles, with the tag in the upper 16 bits.
-hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, uint64_t* posted,
-                                uint32_t tag, hipStream_t s);
+// obstacles, with the tag in the upper 16 bits.  sum: two words, zero before and after.
+hipError_t launch_check_sources(const MazeDev& md, const int32_t* src_rc, int32_t n_src, int32_t* sum,
+                                uint64_t* posted, uint32_t tag, hipStream_t s);
 bool sweep_supported(int T, int C);
 // e0 / e1 (optional, both or neither): events that record the kernel's own
 // start and end (hipExtLaunchKernel), for profiling.

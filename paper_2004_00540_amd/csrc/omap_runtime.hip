@@ -572,6 +572,7 @@ class Solver {
     int32_t* d_min = nullptr;
     unsigned long long* d_reached = nullptr;
     int32_t* d_bad = nullptr;
+    int32_t* d_check = nullptr;               // [2] sums of a source check over several blocks
     int32_t* d_sel = nullptr;
     int32_t* h_pinned = nullptr;              // 64 int32 of pinned host scratch
     uint64_t* h_posted = nullptr;             // pinned, [kPosted]: counts posted by the rounds
@@ -690,6 +691,7 @@ class Solver {
             table(&d_layer_copies, S * kSpread);
             table(&d_touched, N);
             table(&d_bad, 1);
+            table(&d_check, 2);
             zeroed = at;
             table(&d_mazes, S);
             table(&d_tile_maze, N);          // (written for the tile ids that are handed out)
@@ -910,7 +912,7 @@ class Solver {
             s.d_src = static_cast<int32_t*>(mem->alloc(sizeof(int32_t) * 2 * n_src));
             if (!s.d_src) return fail(OMAP_ERR_OUT_OF_MEMORY, "source list (%d sources)", n_src);
             OK_TRY(upload(s.d_src, s.src.data(), sizeof(int32_t) * 2 * n_src));
-            HIP_TRY(launch_check_sources(h_mazes[k], s.d_src, n_src, h_post, ++post_tag, stream));
+            HIP_TRY(launch_check_sources(h_mazes[k], s.d_src, n_src, d_check, h_post, ++post_tag, stream));
         }
         s.started = s.finalized = false;
         s.layers = -1;

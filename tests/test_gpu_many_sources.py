@@ -1,0 +1,40 @@
+"""Source checks and starts with more sources than one block looks at (1,024) and
+more than the check's blocks look at at once (1,048,576): how many lie on obstacles,
+and the map of the free ones."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import to_dev
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = (1, 64, 256, 257, 1024, 1025, 2048, 5000, 70001, 1048576, 1048577)
+
+
+@pytest.mark.parametrize("n", COUNTS)
+def test_sources_on_obstacles_are_counted(n):
+    import paper_2004_00540_amd as omap
+    rng = np.random.default_rng(n)
+    occ = (rng.random((300, 417)) < 0.3).astype(np.uint8)
+    free = np.argwhere(occ == 0).astype(np.int32)
+    wall = np.argwhere(occ != 0).astype(np.int32)
+    src = free[rng.integers(0, len(free), n)]
+    dev = to_dev(occ)
+    with omap.Plan(dev, src, src[:1]) as plan:
+        for bad in sorted({1, n // 3, n}):
+            if bad < 1:
+                continue
+            mixed = src.copy()
+            mixed[rng.permutation(n)[:bad]] = wall[rng.integers(0, len(wall), bad)]
+            with pytest.raises(omap.OmapError, match=f" {bad} source") as e:
+                plan.load(dev, mixed, src[:1])
+            assert e.value.name == "OMAP_ERR_SOURCE_ON_OBSTACLE"
+            with pytest.raises(omap.OmapError, match=f" {bad} source"):
+                omap.Plan(dev, mixed, src[:1])
+        plan.load(dev, src, src[:1])
+        info = plan.propagate()
+        d, ecc = oracle.bfs(occ, src)
+        A = oracle.activity_from_bfs(d, ecc)
+        assert info["layers"] == ecc and info["reached_cells"] == int((A > 0).sum())
+        assert np.array_equal(plan.activity().cpu().numpy(), A)
