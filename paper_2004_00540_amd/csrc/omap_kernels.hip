@@ -238,9 +238,11 @@ __device__ __forceinline__ void clear_tile(const MazeDev& md, int ty, int tx, in
 // What a start needs before its seeds, in one launch.  The first blocks take a
 // tile id in [tile_begin, + n_tiles) per wave: the tile of a selected maze is
 // zeroed if it was written since the last time (select 2: always).  The next
-// n_zero_blocks blocks zero n_zero words (the schedule's tables), the last one
-// copies the descriptors to their table and resets the started slots' counters
-// (last round = r - 1).
+// n_zero_blocks blocks zero n_zero words (the schedule's tables), the others copy
+// the descriptors to their table and reset the started slots' counters (last round
+// = r - 1): 1,024 words a block, since one block took 0.9 ms for 20,000 mazes.
+constexpr int kStartWords = 1024;
+
 __global__ __launch_bounds__(kBlockThreads) void k_start(RoundArgs a, StartArgs st) {
     const int nb = (st.n_tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     int b = blockIdx.x;
@@ -263,11 +265,15 @@ __global__ __launch_bounds__(kBlockThreads) void k_start(RoundArgs a, StartArgs 
             st.zero[i] = 0;
         return;
     }
+    b -= st.n_zero_blocks;
+    const int64_t first = (int64_t)b * kBlockThreads + threadIdx.x;
+    const int64_t step = ((int64_t)gridDim.x - nb - st.n_zero_blocks) * kBlockThreads;
     const uint32_t* from = reinterpret_cast<const uint32_t*>(st.staged);
     uint32_t* to = reinterpret_cast<uint32_t*>(st.mazes_out);
-    for (int i = threadIdx.x; i < (int)(sizeof(MazeDev) / 4) * a.n_slots; i += kBlockThreads) to[i] = from[i];
-    for (int i = threadIdx.x; i < st.n_started * kSpread; i += kBlockThreads) {
-        const int slot = st.started[i / kSpread], x = slot * kSpread + i % kSpread;
+    for (int64_t i = first; i < (int64_t)(sizeof(MazeDev) / 4) * a.n_slots; i += step) to[i] = from[i];
+    for (int64_t i = first; i < (int64_t)st.n_started * kSpread; i += step) {
+        const int slot = st.started[i / kSpread];
+        const int64_t x = (int64_t)slot * kSpread + i % kSpread;
         if (i % kSpread == 0) a.maze_last_round[slot] = a.round_id - 1;
         a.maze_visits[x] = 0;
         a.maze_cell_visits[x] = 0;
@@ -1445,7 +1451,9 @@ hipError_t launch_seed(const RoundArgs& a, int32_t slot, const int32_t* src_rc, 
 hipError_t launch_start(const RoundArgs& a, StartArgs st, hipStream_t s) {
     const int64_t zero_blocks = (st.n_zero + 4 * kBlockThreads - 1) / (4 * kBlockThreads);
     st.n_zero_blocks = (int32_t)(zero_blocks < 1024 ? zero_blocks : 1024);
-    const int blocks = (st.n_tiles + kWavesPerBlock - 1) / kWavesPerBlock + st.n_zero_blocks + 1;
+    const int64_t words = (int64_t)(sizeof(MazeDev) / 4) * a.n_slots + (int64_t)st.n_started * kSpread;
+    const int blocks = (st.n_tiles + kWavesPerBlock - 1) / kWavesPerBlock + st.n_zero_blocks +
+                       grid_for(words, kStartWords, 1024);
     hipLaunchKernelGGL(k_start, dim3(blocks), dim3(kBlockThreads), 0, s, a, st);
     return hipGetLastError();
 }
