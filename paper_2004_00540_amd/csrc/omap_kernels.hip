@@ -11,60 +11,81 @@ namespace omap {
 // ingest: occupancy bytes -> obstacle bit mask
 // ---------------------------------------------------------------------------
 
-// A block packs 32 rows x 1024 columns: a wave reads eight rows, 16 bytes a lane
+// A block packs 1,024 words, as many rows as the maze's width and height make
+// sensible (pack_rows: 32 rows x 1024 columns of most mazes).  A lane reads 16 bytes
 // with every load issued before the first is used, turns each byte into a bit
-// (nonzero bytes to 0x01, four of them to a nibble by a dot product with 1, 2, 4,
-// 8) and two lanes' bits into a word; the block's words go through LDS to the
-// mask's layout, 128 contiguous bytes of a strip or of a row.  One job per maze,
-// blocks in job order.  Bound by the read of the occupancy: 3.8 TB/s on
-// 26,000^2 cells (0.179 ms) and 4.0 on 23,170^2 (0.133); a thread per word, 32
-// byte loads each, took 0.19 ms.  512 mazes of up to 2,048^2 cells take 0.095 ms;
-// with a thread per word, each searching its job, 0.46.
-constexpr int kPackRows = 32, kPackWords = 32, kPackGrid = 65536;
+// (nonzero bytes to 0x01, four of them to a nibble by a dot product with 1, 2, 4, 8)
+// and two lanes' bits into a word; the block's words go through LDS to the mask's
+// layout, contiguous down a strip or along a row.  One job per maze, blocks in job
+// order.  Bound by the read of the occupancy: 3.8 TB/s on 26,000^2 cells (0.179 ms)
+// and 4.0 on 23,170^2 (0.133); a thread per word, 32 byte loads each, took 0.19 ms.
+// 512 mazes of up to 2,048^2 cells take 0.095 ms; with a thread per word, each
+// searching its job, 0.46.
+constexpr int kPackWords = 1024, kPackThreads = 256, kPackGrid = 65536;
 typedef uint32_t v4u32_bytes __attribute__((ext_vector_type(4), aligned(1)));
 
-__global__ __launch_bounds__(256) void k_pack_mask(PackJob one, const PackJob* __restrict__ jobs, int32_t n_jobs,
-                                                   int64_t blocks) {
-    __shared__ uint32_t tile[kPackWords][kPackRows + 1];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
+// Log2 of the rows a block packs: its 1,024 words are as wide as the maze up to 32
+// words, and wider only where the maze has fewer than 32 rows (blocks of 32 x 32
+// words left most lanes without a column: loading 4,000,000 x 8 cells 196 us, now 74;
+// with a thread per word 100).
+__host__ __device__ __forceinline__ int pack_rows_log2(int32_t H, int32_t mpitch) {
+    int rows = 10;
+    while (rows > 5 && mpitch > kPackWords >> rows) --rows;
+    while (rows > 0 && H <= 1 << (rows - 1)) --rows;
+    return rows;
+}
+
+__global__ __launch_bounds__(kPackThreads) void k_pack_mask(PackJob one, const PackJob* __restrict__ jobs,
+                                                            int32_t n_jobs, int64_t blocks) {
+    __shared__ uint32_t tile[2 * kPackWords];   // word w of row r at w * (rows + 1) + r
+    const int t = threadIdx.x;
     for (int64_t q = blockIdx.x; q < blocks; q += gridDim.x) {
         PackJob jb = one;
         if (n_jobs > 1) {
-            int lo = 0, hi = n_jobs - 1;   // the last job with block_begin <= q
-            while (lo < hi) {
-                const int m = (lo + hi + 1) >> 1;
-                if (jobs[m].block_begin <= q) lo = m;
-                else hi = m - 1;
+            int lo = 0, hi = n_jobs;   // the last job with block_begin <= q, 64 looked at at a time
+            while (hi - lo > 1) {
+                const int step = (hi - lo + kLanes - 1) / kLanes, j = lo + lane_id() * step;
+                const int below = __popcll(__ballot(j < hi && jobs[min(j, n_jobs - 1)].block_begin <= q));
+                lo += (below - 1) * step;
+                hi = min(hi, lo + step);
             }
             jb = jobs[lo];
         }
-        const int32_t col_tiles = (jb.mpitch + kPackWords - 1) / kPackWords;
+        const int log_rows = pack_rows_log2(jb.H, jb.mpitch), log_words = 10 - log_rows;
+        const int rows = 1 << log_rows, words = 1 << log_words;
+        const int32_t col_tiles = (jb.mpitch + words - 1) >> log_words;
         const int64_t b = q - jb.block_begin;
         const int32_t rt = (int32_t)(b / col_tiles), ct = (int32_t)(b - (int64_t)rt * col_tiles);
-        const int64_t row0 = (int64_t)rt * kPackRows;
+        const int64_t row0 = (int64_t)rt << log_rows;
+        const int32_t w0 = ct << log_words;
         const auto occ = (const __attribute__((address_space(1))) uint8_t*)jb.occ;
         if (jb.W < 16) {   // narrower than a lane's load; columns past the row are obstacles
-            for (int t = threadIdx.x; t < kPackWords * kPackRows; t += 256) {
+            for (int u = t; u < kPackWords; u += kPackThreads) {
+                const int w = u >> log_rows, r = u & (rows - 1);
                 uint32_t word = ~0u;
-                const int64_t r = min(row0 + t % kPackRows, (int64_t)jb.H - 1);
-                if (t < kPackRows) {
+                if (w0 + w == 0) {
+                    const int64_t at = min(row0 + r, (int64_t)jb.H - 1) * jb.W;
                     for (int e = 0; e < jb.W; ++e)
-                        if (occ[r * jb.W + e] == 0) word &= ~(1u << e);
+                        if (occ[at + e] == 0) word &= ~(1u << e);
                 }
-                tile[t / kPackRows][t % kPackRows] = word;
+                tile[w * (rows + 1) + r] = word;
             }
         } else {
-            // (a lane past the row's last 16 bytes reads those and shifts its bits)
-            const int32_t c = ct * (32 * kPackWords) + 16 * lane;
-            const int32_t at = min(c, jb.W - 16), past = min(c - at, 16);
-            v4u32_bytes v[8];
+            // half words 256 k + t of the tile, row by row (a lane past the row's last 16
+            // bytes reads those and shifts its bits)
+            constexpr int kPer = 2 * kPackWords / kPackThreads;
+            v4u32_bytes v[kPer];
+            int32_t past[kPer];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int64_t r = min(row0 + 8 * wave + k, (int64_t)jb.H - 1);
+            for (int k = 0; k < kPer; ++k) {
+                const int u = kPackThreads * k + t;
+                const int32_t c = 16 * min(2 * w0 + (u & (2 * words - 1)), 2 * jb.mpitch - 1), at = min(c, jb.W - 16);
+                const int64_t r = min(row0 + (u >> (log_words + 1)), (int64_t)jb.H - 1);
+                past[k] = min(c - at, 16);
                 v[k] = *(const __attribute__((address_space(1))) v4u32_bytes*)(occ + r * jb.W + at);
             }
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < kPer; ++k) {
                 uint32_t bits = 0;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -77,23 +98,18 @@ __global__ __launch_bounds__(256) void k_pack_mask(PackJob one, const PackJob* _
                     const uint32_t low = __builtin_amdgcn_udot4(y[0], 0x08040201u, 0, false);
                     bits |= __builtin_amdgcn_udot4(y[1], 0x80402010u, low, false) << (8 * h);
                 }
-                bits = (bits | 0xffff0000u) >> past & 0xffffu;
+                bits = (bits | 0xffff0000u) >> past[k] & 0xffffu;
                 const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, 0xF5, 0xF, 0xF, true);   // quad_perm [1, 1, 3, 3]
-                if ((lane & 1) == 0) tile[lane >> 1][8 * wave + k] = bits | next << 16;
+                const int u = kPackThreads * k + t;
+                if ((t & 1) == 0) tile[((u & (2 * words - 1)) >> 1) * (rows + 1) + (u >> (log_words + 1))] = bits | next << 16;
             }
         }
         __syncthreads();
-        const int32_t w0 = ct * kPackWords;
-        if (jb.mrow == 1) {   // strips
-            for (int t = threadIdx.x; t < kPackWords * kPackRows; t += 256) {
-                const int w = t / kPackRows, r = t % kPackRows;
-                if (w0 + w < jb.mpitch && row0 + r < jb.H) jb.mask[(int64_t)(w0 + w) * jb.mcol + row0 + r] = tile[w][r];
-            }
-        } else {
-            for (int t = threadIdx.x; t < kPackWords * kPackRows; t += 256) {
-                const int r = t / kPackWords, w = t % kPackWords;
-                if (w0 + w < jb.mpitch && row0 + r < jb.H) jb.mask[(row0 + r) * jb.mrow + w0 + w] = tile[w][r];
-            }
+        const bool strips = jb.mrow == 1;
+        for (int u = t; u < kPackWords; u += kPackThreads) {
+            const int w = strips ? u >> log_rows : u & (words - 1), r = strips ? u & (rows - 1) : u >> log_words;
+            if (w0 + w < jb.mpitch && row0 + r < jb.H)
+                jb.mask[(row0 + r) * jb.mrow + (int64_t)(w0 + w) * jb.mcol] = tile[w * (rows + 1) + r];
         }
         __syncthreads();   // the next tile overwrites the words
     }
@@ -1416,13 +1432,14 @@ static int grid_for(int64_t n, int block, int cap = 1 << 20) {
 }
 
 int64_t pack_blocks(int32_t H, int32_t mpitch) {
-    return (int64_t)((H + kPackRows - 1) / kPackRows) * ((mpitch + kPackWords - 1) / kPackWords);
+    const int log_rows = pack_rows_log2(H, mpitch), log_words = 10 - log_rows;
+    return (((int64_t)H + (1 << log_rows) - 1) >> log_rows) * (((int64_t)mpitch + (1 << log_words) - 1) >> log_words);
 }
 
 hipError_t launch_pack_mask(const uint8_t* occ, const MazeDev& md, uint32_t* mask, hipStream_t s) {
     const PackJob jb{occ, mask, md.H, md.W, md.mpitch, md.mrow, md.mcol, 0};
     const int64_t blocks = pack_blocks(md.H, md.mpitch);
-    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(blocks, 1, kPackGrid)), dim3(256), 0, s, jb, nullptr, 1, blocks);
+    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(blocks, 1, kPackGrid)), dim3(kPackThreads), 0, s, jb, nullptr, 1, blocks);
     return hipGetLastError();
 }
 
@@ -1461,7 +1478,7 @@ hipError_t launch_start(const RoundArgs& a, StartArgs st, hipStream_t s) {
 hipError_t launch_pack_mask_many(const PackJob& first, const PackJob* jobs, int32_t n_jobs, int64_t blocks,
                                  hipStream_t s) {
     if (n_jobs <= 0 || blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(blocks, 1, kPackGrid)), dim3(256), 0, s, first, jobs, n_jobs, blocks);
+    hipLaunchKernelGGL(k_pack_mask, dim3(grid_for(blocks, 1, kPackGrid)), dim3(kPackThreads), 0, s, first, jobs, n_jobs, blocks);
     return hipGetLastError();
 }
 
