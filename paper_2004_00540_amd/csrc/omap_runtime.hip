@@ -531,7 +531,6 @@ struct Slot {
     int32_t* V[2] = {nullptr, nullptr};
     uint32_t* mask = nullptr;
     uint32_t* R[2] = {nullptr, nullptr};   // front propagation only
-    int32_t* d_src = nullptr;
     std::vector<int32_t> src, tgt;
     int32_t K = 0;
     int64_t L_req = 0;
@@ -581,7 +580,7 @@ class Solver {
     uint16_t post_tag = 0;                    // tag of the value awaited
     void* d_scratch = nullptr;                // grow-only path scratch
     size_t scratch_bytes = 0;
-    int32_t* d_start_ = nullptr;              // grow-only staging of start_many
+    int32_t* d_start_ = nullptr;              // grow-only staging of starts and source checks
     size_t start_cap_ = 0;
     PinnedPool pin;                           // pinned staging of host-to-device copies
 
@@ -788,13 +787,11 @@ class Solver {
         mem->release(s.V[0]);
         if (s.V[1]) mem->release(s.V[1]);
         mem->release(s.mask);
-        mem->release(s.d_src);
         if (s.R[0]) mem->release(s.R[0]);
         if (s.R[1]) mem->release(s.R[1]);
         s.V[0] = s.V[1] = nullptr;
         s.R[0] = s.R[1] = nullptr;
         s.mask = nullptr;
-        s.d_src = nullptr;
     }
 
     // Activity, mask and (front propagation) reached-set buffers of a slot;
@@ -834,8 +831,14 @@ class Solver {
         md.tiles_x_inv = s.g.tiles_x > 1 ? (uint32_t)((uint64_t(1) << 32) / (uint32_t)s.g.tiles_x) : 0xffffffffu;
     }
 
-    // Grow-only device staging of start_many (synchronizes only to grow; the
-    // next start's upload is ordered after this start's kernels on the stream).
+    // Words that start_many stages: descriptors | selection | slot list | seed (r, c)
+    // pairs | seed slots.
+    size_t start_words(size_t n_which, size_t n_seed) const {
+        return sizeof(MazeDev) / 4 * (size_t)cap_slots + cap_slots + n_which + 3 * n_seed;
+    }
+
+    // Grow-only device staging of start_many and of source checks (synchronizes
+    // only to grow; the next upload is ordered after this one's kernels on the stream).
     omap_status_t start_scratch(size_t n_int32, int32_t** out) {
         if (n_int32 > start_cap_) {
             HIP_TRY(hipStreamSynchronize(stream));
@@ -908,11 +911,10 @@ class Solver {
         set_desc(k);
         HIP_TRY(launch_pack_mask(occ_dev, h_mazes[k], s.mask, stream));
         if (check_sources) {
-            mem->release(s.d_src);
-            s.d_src = static_cast<int32_t*>(mem->alloc(sizeof(int32_t) * 2 * n_src));
-            if (!s.d_src) return fail(OMAP_ERR_OUT_OF_MEMORY, "source list (%d sources)", n_src);
-            OK_TRY(upload(s.d_src, s.src.data(), sizeof(int32_t) * 2 * n_src));
-            HIP_TRY(launch_check_sources(h_mazes[k], s.d_src, n_src, d_check, h_post, ++post_tag, stream));
+            int32_t* d_src = nullptr;   // (room for the start that follows: a reload allocates nothing)
+            OK_TRY(start_scratch(start_words(1, n_src), &d_src));
+            OK_TRY(upload(d_src, s.src.data(), sizeof(int32_t) * 2 * n_src));
+            HIP_TRY(launch_check_sources(h_mazes[k], d_src, n_src, d_check, h_post, ++post_tag, stream));
         }
         s.started = s.finalized = false;
         s.layers = -1;
@@ -1086,10 +1088,9 @@ class Solver {
             }
         }
         const RoundArgs a = round_args(true);
-        // staging: descriptors | selection | slot list | seed (r, c) pairs | seed slots
         const int32_t n_which = (int32_t)which.size();
         const size_t desc_words = sizeof(MazeDev) / 4 * (size_t)cap_slots;
-        std::vector<int32_t> stage(desc_words + cap_slots + n_which + 3 * (size_t)n_seed, 0);
+        std::vector<int32_t> stage(start_words(n_which, n_seed), 0);
         std::memcpy(stage.data(), h_mazes.data(), sizeof(MazeDev) * cap_slots);
         int32_t* const sel = stage.data() + desc_words;
         int32_t* const slot_list = sel + cap_slots;
