@@ -70,7 +70,6 @@ struct RoundArgs {
     int32_t* maze_last_round;     // per slot: last round with a tile visited
     uint8_t* touched;             // per tile id: written since its maze's buffers were last cleared
     int64_t* maze_visits;         // [slot][kSpread]: tile visits
-    int64_t* maze_cell_visits;    // [slot][kSpread]: interior cells of visited tiles (integer sweeps)
     unsigned long long* total_cells;  // [kSpread], all slots: interior cells of visited tiles (front
                                   // propagation: once per step of 16 layers)
     unsigned long long* maze_reached; // front propagation, [slot][kSpread]: cells reached

@@ -292,7 +292,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_start(RoundArgs a, StartArgs 
         const int64_t x = (int64_t)slot * kSpread + i % kSpread;
         if (i % kSpread == 0) a.maze_last_round[slot] = a.round_id - 1;
         a.maze_visits[x] = 0;
-        a.maze_cell_visits[x] = 0;
         a.maze_reached[x] = 0;
         a.maze_layer[x] = 0;
     }

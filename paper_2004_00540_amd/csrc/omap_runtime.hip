@@ -560,7 +560,7 @@ class Solver {
     int32_t* d_dchg = nullptr;                // [3][cap_slots] dense: changed, by round mod 3
     int32_t* d_last_round = nullptr;          // per slot
     uint8_t* d_touched = nullptr;             // per tile id
-    int64_t *d_visits = nullptr, *d_cell_visits = nullptr;
+    int64_t* d_visits = nullptr;
     unsigned long long* d_total_cells = nullptr;
     unsigned long long* d_reached_copies = nullptr;   // front propagation: [cap_slots][kSpread] ...
     int32_t* d_layer_copies = nullptr;                // ... cells reached and last layer
@@ -684,7 +684,6 @@ class Solver {
             table(&d_last_round, S);
             table(&d_bad_slot, S);
             table(&d_visits, S * kSpread);
-            table(&d_cell_visits, S * kSpread);
             table(&d_total_cells, kSpread);
             table(&d_reached_copies, S * kSpread);
             table(&d_layer_copies, S * kSpread);
@@ -767,7 +766,6 @@ class Solver {
         a.maze_last_round = d_last_round;
         a.touched = d_touched;
         a.maze_visits = d_visits;
-        a.maze_cell_visits = d_cell_visits;
         a.total_cells = d_total_cells;
         a.maze_reached = d_reached_copies;
         a.maze_layer = d_layer_copies;
@@ -1432,18 +1430,15 @@ class Solver {
 
     // Host copies of every slot's visit counters (read_counters, synchronous).
     std::vector<int32_t> h_last_round;
-    std::vector<int64_t> h_visits, h_cell_visits;
+    std::vector<int64_t> h_visits;
 
     omap_status_t read_counters() {
         h_last_round.resize(cap_slots);
         h_visits.resize((size_t)cap_slots * kSpread);
-        h_cell_visits.resize((size_t)cap_slots * kSpread);
         HIP_TRY(hipMemcpyAsync(h_last_round.data(), d_last_round, sizeof(int32_t) * cap_slots, hipMemcpyDeviceToHost,
                                stream));
         HIP_TRY(hipMemcpyAsync(h_visits.data(), d_visits, sizeof(int64_t) * h_visits.size(), hipMemcpyDeviceToHost,
                                stream));
-        HIP_TRY(hipMemcpyAsync(h_cell_visits.data(), d_cell_visits, sizeof(int64_t) * h_cell_visits.size(),
-                               hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         return OMAP_OK;
     }
@@ -2074,11 +2069,11 @@ static omap_status_t retire_paths(omap_engine_s* e) {
     }
     if (n > 0 && R.total > 0)
         HIP_TRY(launch_walk(sv.d_mazes, d_tslot, d_trc, R.n, sv.vparity(), d_len, d_off, R.d_cells, R.total, xs));
-    // host layout: last_round | visits | cell visits | cells | activity maps
+    // host layout: last_round | visits | cells | activity maps
     const size_t b_lr = up(4 * (size_t)sv.cap_slots), b_v = up(8 * (size_t)sv.cap_slots * kSpread);
     size_t act_bytes = 0;
     R.act_off.assign(R.ids.size(), -1);
-    const size_t cells_at = b_lr + 2 * b_v, act_at = cells_at + up(4 * (size_t)R.total);
+    const size_t cells_at = b_lr + b_v, act_at = cells_at + up(4 * (size_t)R.total);
     for (size_t i = 0; i < R.ids.size(); ++i) {
         const Query& q = e->queries[R.ids[i]];
         if (!(q.flags & OMAP_QUERY_KEEP_ACTIVITY)) continue;
@@ -2091,8 +2086,6 @@ static omap_status_t retire_paths(omap_engine_s* e) {
     HIP_TRY(hipMemcpyAsync(R.h_out.p, sv.d_last_round, 4 * (size_t)sv.cap_slots, hipMemcpyDeviceToHost, xs));
     HIP_TRY(hipMemcpyAsync(R.h_out.p + b_lr, sv.d_visits, 8 * (size_t)sv.cap_slots * kSpread, hipMemcpyDeviceToHost,
                            xs));
-    HIP_TRY(hipMemcpyAsync(R.h_out.p + b_lr + b_v, sv.d_cell_visits, 8 * (size_t)sv.cap_slots * kSpread,
-                           hipMemcpyDeviceToHost, xs));
     // each query's cells straight into a block of the result pool that
     // omap_engine_fetch copies out and frees (else into h_out)
     R.cells_block.assign(R.ids.size(), nullptr);
@@ -2139,13 +2132,11 @@ static omap_status_t retire_finish(omap_engine_s* e) {
     const size_t b_lr = up(4 * (size_t)sv.cap_slots), b_v = up(8 * (size_t)sv.cap_slots * kSpread);
     const int32_t* h_len = reinterpret_cast<const int32_t*>(R.h_lo.p);
     const int64_t* h_off = reinterpret_cast<const int64_t*>(R.h_lo.p + lo_offsets_at(n));
-    const int32_t* h_cells = reinterpret_cast<const int32_t*>(R.h_out.p + b_lr + 2 * b_v);
+    const int32_t* h_cells = reinterpret_cast<const int32_t*>(R.h_out.p + b_lr + b_v);
     const int32_t* h_lr = reinterpret_cast<const int32_t*>(R.h_out.p);
     const int64_t* h_v = reinterpret_cast<const int64_t*>(R.h_out.p + b_lr);
-    const int64_t* h_cv = reinterpret_cast<const int64_t*>(R.h_out.p + b_lr + b_v);
     sv.h_last_round.assign(h_lr, h_lr + sv.cap_slots);
     sv.h_visits.assign(h_v, h_v + (size_t)sv.cap_slots * kSpread);
-    sv.h_cell_visits.assign(h_cv, h_cv + (size_t)sv.cap_slots * kSpread);
     int64_t t0 = 0;
     for (size_t i = 0; i < R.ids.size(); ++i) {
         Query& q = e->queries[R.ids[i]];

@@ -330,7 +330,6 @@ __device__ __forceinline__ void visit_bookkeeping(const RoundArgs& a, int g, int
     const unsigned long long cells = (unsigned long long)tile_cells(md, ty, tx, a.tile_rows, a.tile_cols);
     const int sp = blockIdx.x & (kSpread - 1);
     atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_visits[slot * kSpread + sp]), 1ull);
-    atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[slot * kSpread + sp]), cells);
     atomicAdd(a.total_cells + sp, cells);
     a.touched[g] = 1;
     // every visiting wave of the round stores the same value (a test of the
@@ -349,19 +348,14 @@ __device__ __forceinline__ void visit_bookkeeping_active(const RoundArgs& a, int
     a.touched[g] = 1;
     a.maze_last_round[slot] = a.round_id;
     const long long short_by = (long long)a.tile_rows * a.tile_cols - tile_cells(md, ty, tx, a.tile_rows, a.tile_cols);
-    if (short_by != 0) {
-        const int sp = blockIdx.x & (kSpread - 1);
-        atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[slot * kSpread + sp]),
-                  (unsigned long long)(-short_by));
-        atomicAdd(a.total_cells + sp, (unsigned long long)(-short_by));
-    }
+    if (short_by != 0) atomicAdd(a.total_cells + (blockIdx.x & (kSpread - 1)), (unsigned long long)(-short_by));
 }
 
 // Work of the first block of a round launch, which visits no tile: it clears
 // the buffers round r+2 will fill and (listed schedules) counts round r's
 // visits from the list: per maze, its scheduled tiles (the whole list with
 // one maze) as visits of full tiles, corrected by the visits of edge tiles.
-// This replaces three same-address atomics per visit by one per maze and
+// This replaces two same-address atomics per visit by one per maze and
 // round, off the visiting waves' path.  FRONT_T (front propagation, its layers
 // per visit): a maze whose rounds have covered its layers below K visits
 // nothing, and the visits count the cells they update themselves.
@@ -389,10 +383,7 @@ __device__ __forceinline__ void round_accounting(const RoundArgs& a) {
             const unsigned long long v = (unsigned long long)*a.count_in;
             if (v > 0 && live(a.md0)) {
                 atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_visits[0]), v);
-                if (FRONT_T == 0) {
-                    atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[0]), v * full);
-                    atomicAdd(a.total_cells, v * full);
-                }
+                if (FRONT_T == 0) atomicAdd(a.total_cells, v * full);
             }
         }
         return;
@@ -402,7 +393,6 @@ __device__ __forceinline__ void round_accounting(const RoundArgs& a) {
         const unsigned long long v = (unsigned long long)a.sched_in[m];
         if (v > 0 && live(a.mazes[m])) {
             atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_visits[m * kSpread]), v);
-            if (FRONT_T == 0) atomicAdd(reinterpret_cast<unsigned long long*>(&a.maze_cell_visits[m * kSpread]), v * full);
             mine += v;
         }
     }
