@@ -1302,11 +1302,10 @@ class Solver {
     }
 
     // Rounds in flight ahead of the last posted count: a launch takes the host
-    // about 4 us and an empty round about 3, a round with tiles 10 or more.
-    #ifndef KA
-#define KA 3
-#endif
-    static constexpr int kAhead = KA;
+    // about 4 us and an empty round about 3, a round with tiles 10 or more (an empty
+    // 2000^2 map: 2, 4 and 5 rounds 433, 445 and 449 us, 3 rounds 416).
+    static constexpr int kAhead = 3;
+    static_assert(kAhead < kPosted, "a count is read before its place in the ring is written again");
 
     // Waits until seen() holds for what a kernel on the stream stores in pinned
     // host memory.  A stream that has drained (or failed) without storing it is
