@@ -198,8 +198,9 @@ def tune(mazes, use: int = USE_BATCH, stream=None) -> dict:
 
 
 def resolve_options(**options) -> dict:
-    """The options a plan / batch / engine created with these keyword options
-    runs with (defaults filled in); host only."""
+    """The options of a plan created with these keyword options, defaults filled
+    in, as the create call takes them (where they stand for the bit-packed kernel
+    it runs its own tile shape and depth); host only."""
     out = Options()
     _check(lib().omap_resolve_options(ctypes.byref(_options(**options)), ctypes.byref(out)))
     return {f: getattr(out, f) for f, _ in Options._fields_}

@@ -165,8 +165,8 @@ hipError_t launch_front_report(const MazeDev* mazes, const unsigned long long* r
 // (optional) receives the targets by path length, longest first; posted (a word
 // of pinned host memory, or null) the number of path cells, tagged as above.
 // Up to kScanLengths targets the scan's one block computes the lengths too, at
-// most four gathers per thread in place of a launch and its gap (5 us).  From
-// kScanOneBlock on targets are scanned by many blocks if there is `work`
+// most four gathers per thread in place of a launch and its gap (5 us).  Above
+// kScanOneBlock targets are scanned by many blocks if there is `work`
 // (scan_work_bytes(n), 8-byte aligned): the extraction of 4,096 targets takes 9 us
 // less (the one block 23 us), of 2,048 10 us, but of 512 3 us more.
 constexpr int kScanLengths = 4096, kScanOneBlock = 1024;

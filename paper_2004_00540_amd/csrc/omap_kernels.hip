@@ -391,7 +391,7 @@ __global__ void k_front_report(const MazeDev* __restrict__ mazes, const unsigned
 }
 
 // ---------------------------------------------------------------------------
-// paths: lengths, offsets, gradient walk (one lane per target)
+// paths: lengths, offsets, gradient walk
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ int path_length(const MazeDev& md, int r, int c, int parity) {
@@ -406,10 +406,6 @@ __global__ void k_path_lengths(const MazeDev* __restrict__ mazes, const int32_t*
     if (i < n) len[i] = path_length(mazes[tslot[i]], trc[2 * i], trc[2 * i + 1], parity);
 }
 
-// Offsets of the paths (exclusive scan of length + 1 over reached targets),
-// and optionally an order of the targets by path length, longest first (by
-// the length's bit width: a bucket order, not a full sort), so that the walk
-// starts the paths that take longest before the others.
 // Takes a slot in bucket k for every lane with k >= 0 (wave-uniform call):
 // one LDS atomic per distinct key in the wave, the lanes of a key numbered in
 // lane order.  Returns the lane's slot, or -1 for k < 0.
@@ -430,6 +426,10 @@ __device__ __forceinline__ int wave_bucket_slot(int* bucket, int k) {
     return slot;
 }
 
+// Offsets of the paths (exclusive scan of length + 1 over reached targets),
+// and optionally an order of the targets by path length, longest first (by
+// the length's bit width: a bucket order, not a full sort), so that the walk
+// starts the paths that take longest before the others.
 // (lengths: computed here first, for up to kScanLengths targets; posted: the
 // number of path cells goes to the host as soon as it is known)
 __global__ __launch_bounds__(1024) void k_scan(const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot,
@@ -877,7 +877,7 @@ constexpr int kTileWalkPitch = 18;   // dwords of a row of classes: 16 and one o
 struct TileWalkShared {
     int32_t v[64 * 64];
     uint32_t cls[66 * kTileWalkPitch];
-    uint16_t next[kTileWalkLevels + 1][64 * 64];   // the cell 1, 2, 4, 8, 16 moves on
+    uint16_t next[kTileWalkLevels + 1][64 * 64];   // the cell 1, 2, 4, 8 moves on
 };
 
 __global__ __launch_bounds__(kTileWalkThreads) void k_walk_tile(
@@ -1030,8 +1030,6 @@ __device__ __forceinline__ uint32_t tie_remainders(uint64_t seed, uint64_t targe
 // sideways move to an equal 4-neighbour per activity level, and otherwise
 // takes the first maximal 8-neighbour; the straightening pass (drop a point
 // whose predecessor and successor are diagonal neighbours) runs on the fly.
-// WRITE = false counts the final points (len = points - 1, -1 if no path);
-// WRITE = true writes them at off[i].
 //
 // One wave per target, from the same windows and 8 x 8 blocks as k_walk: a
 // block serves three moves, with ballots of the cells holding v .. v + 3 (a
@@ -1062,10 +1060,10 @@ __device__ __forceinline__ uint64_t every_other(uint64_t m, bool after_drop) {
     return (on_even & even) | (m & ~on_even & ~even);
 }
 
-// COUNT: the path's length goes to len.  WRITE: its cells go to cells, from off[i]
-// on or, where they are counted as well, from i * stride on (at most stride of
-// them); k_gather_paths moves them once the offsets are known, in place of a second
-// walk: 2,048 paths of a 2,048^2 map, asked for and taken, 0.867 -> 0.635 ms.
+// COUNT: the path's length (its points less one, -1 for no path) goes to len.
+// WRITE: its cells go to cells, from off[i] on or, where they are counted as well,
+// from i * stride on (at most stride of them); k_gather_paths moves them once the
+// offsets are known, in place of a second walk: 2,048 paths of a 2,048^2 map, asked for and taken, 0.867 -> 0.635 ms.
 template <bool WRITE, bool COUNT>
 __global__ __launch_bounds__(kLanes * kWalkWaves) void k_walk_euclid(
     const MazeDev* __restrict__ mazes, const int32_t* __restrict__ tslot, const int32_t* __restrict__ trc, int32_t n,

@@ -2574,7 +2574,10 @@ omap_status_t omap_engine_create(omap_engine_t* out, int64_t memory_budget_bytes
     e->budget = memory_budget_bytes;
     e->max_slots = max_slots;
     // tile ids: enough for the whole budget filled with mazes of a strip's
-    // height or more (front tiles: of 16 rows or more, 31 tiles to 1984 columns)
+    // height or more (front tiles: of 16 rows or more, 31 tiles to 1984 columns).
+    // The tables hold 29 bytes a tile id beside the budget: 0.35 % of it for the
+    // front propagation (0.23 GB of 64 GB), 0.01 % with the tiles of 16 x 1984 that
+    // the factor of 31 keeps low and wide queries admitted for.
     const int64_t per_tile = o.front ? 16 * 1984 * 8 : (int64_t)o.TH * o.TW * 8;
     int64_t cap_tiles = (memory_budget_bytes / per_tile + 4 * (int64_t)max_slots + 64) * (o.front ? 31 : 1);
     if (cap_tiles > (int64_t(1) << 28)) cap_tiles = int64_t(1) << 28;
