@@ -39,11 +39,6 @@ HBM_PEAK_GBS = 8000.0                  # MI355X HBM3E
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_front_c3_traffic.json")
 KERNEL_SOURCES = ("omap_front.h", "omap_front.hip", "omap_sweep.h", "omap_internal.h")
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # 256 CUs x 4 SIMD x 16 lanes x 2.4 GHz, 32-bit ops
-# integer sweep: int32 read + int32 write + 1 mask bit; bit-packed front: reached
-# set in and out and mask, 1 bit each (plus 4 B per reached cell once)
-BYTES_PER_CELL_UPDATE, FRONT_BYTES_PER_CELL_UPDATE = 8.125, 0.375
-# VALU operations per cell-update: integer sweep 4.5; front 6 per word of 32 cells
-OPS_PER_CELL_UPDATE, FRONT_OPS_PER_CELL_UPDATE = 4.5, 6 / 32
 LDS_FILE = os.path.join(ROOT, "profiles", "lds_c3_23170.json")
 LDS_SOURCES = KERNEL_SOURCES + ("omap_kernels.hip",)
 # LDS: 256 CUs x 128 B per clock (32 banks of 4 B) x 2.4 GHz
@@ -349,6 +344,7 @@ def bench_plain(args):
     import torch
     import paper_2004_00540_amd as omap
     import workloads
+    from bench_forms import propagation_work, runs_front
 
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
@@ -419,16 +415,13 @@ def bench_plain(args):
     resolved = omap.resolve_options(**opts)
     executed = prof["cell_updates"]            # per propagation = per step
     gcups = executed / step_s / 1e9
-    # the bit-packed front runs the default active shape and the bit-sliced schedule
-    front = resolved["schedule"] == omap.SCHEDULE_BITS or (
-        resolved["schedule"], resolved["temporal_depth"], resolved["tile_rows"], resolved["lane_columns"]) == (
-        omap.SCHEDULE_ACTIVE, 16, 16, 1)
-    alg_bytes = (prof["cell_updates"] * FRONT_BYTES_PER_CELL_UPDATE + 4 * info["reached_cells"] if front
-                 else prof["cell_updates"] * BYTES_PER_CELL_UPDATE)
+    work = propagation_work(runs_front(opts, many=False), prof["cell_updates"], info["tile_visits"],
+                            info["reached_cells"])
+    alg_bytes = work["bytes"]
     kern_s = prof["ms"] / 1e3
     launches = max(prof["launches"], 1)
     achieved = alg_bytes / kern_s / 1e9 if kern_s > 0 else 0.0
-    ops_per_cell = FRONT_OPS_PER_CELL_UPDATE if front else OPS_PER_CELL_UPDATE
+    ops_per_cell = work["ops_per_cell_update"]
     alu_tops = prof["cell_updates"] * ops_per_cell / kern_s / 1e12 if kern_s > 0 else 0.0
     traffic = measured_traffic(m.name, resolved)
     out = {
@@ -456,6 +449,7 @@ def bench_plain(args):
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
+                     "algorithmic_bytes": work["bytes_are"],
                      "algorithmic_bytes_per_launch": round(alg_bytes / launches),
                      "avg_launch_us": round(prof["ms"] * 1e3 / launches, 2),
                      "measured_hbm_gbs": round(traffic / (kern_s / launches) / 1e9, 1) if traffic and kern_s > 0

@@ -24,6 +24,37 @@ def _log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
+def runs_front(options: dict, many: bool) -> bool:
+    """Whether a plan (or, with many, a batch or engine) created with these options
+    propagates on the bit-packed kernel (k_front) or on the integer sweep: the
+    library's choice (the bit-sliced schedule, and the default shapes of a plan's
+    active and of the dense schedule)."""
+    import paper_2004_00540_amd as omap
+    schedule = options.get("schedule", 0)
+    if many and schedule == omap.SCHEDULE_DEFAULT:
+        bits = not options.get("lane_columns", 0) and options.get("temporal_depth", 0) in (0, 8, 16)
+        schedule = omap.SCHEDULE_BITS if bits else omap.SCHEDULE_ACTIVE
+    if schedule == omap.SCHEDULE_BITS:
+        return True
+    r = omap.resolve_options(**{**options, "schedule": schedule})
+    shape = (r["temporal_depth"], r["tile_rows"], r["lane_columns"])
+    if schedule == omap.SCHEDULE_DENSE:
+        return shape == (16, 256, 4)
+    return not many and shape == (16, 16, 1)
+
+
+def propagation_work(front: bool, cell_updates: int, tile_visits: int, reached: int) -> dict:
+    """HBM bytes and VALU operations that a propagation cannot do without.  Integer
+    sweep: int32 in and out and a mask bit per cell-update, 4.5 operations.  Bit-packed
+    front: a bit of the reached set in and out and of the mask per cell of a visited
+    64 x 64 tile (whatever number of layers it gets in LDS and registers), 4 B once
+    per reached cell, 6 operations per word of 32 cells and layer."""
+    if front:
+        return {"bytes": tile_visits * 64 * 64 * 0.375 + 4 * reached, "ops_per_cell_update": 6 / 32,
+                "bytes_are": "3 bits per cell of a visited tile + 4 B per reached cell"}
+    return {"bytes": cell_updates * 8.125, "ops_per_cell_update": 4.5, "bytes_are": "8.125 B per cell-update"}
+
+
 def _gen_config4(n):
     import workloads
     params = workloads.config4_params()
@@ -103,15 +134,13 @@ def bench_batch(args):
         torch.cuda.synchronize()
         t_plain = time.perf_counter() - t0
     eff = sum(m.H * m.W * (i["layers"] + 1) for m, i in zip(mazes, infos))
-    # roofline of the batch's sweep kernel on its own algorithmic bytes: the
-    # integer sweep 8.125 B per cell-update; the bit-sliced one 3 bits per
-    # cell and layer (reached set in and out, mask) + 4 B per reached cell
+    # roofline of the batch's propagation kernel on its own algorithmic bytes
     resolved = omap.resolve_options(**opts)
-    bits = resolved["schedule"] == omap.SCHEDULE_BITS
+    front = runs_front(opts, many=True)
     reached = sum(i["reached_cells"] for i in infos)
-    alg = prof["cell_updates"] * (0.375 if bits else 8.125) + (4 * reached if bits else 0)
+    work = propagation_work(front, prof["cell_updates"], sum(i["tile_visits"] for i in infos), reached)
     k_s = prof["ms"] / 1e3
-    achieved = alg / k_s / 1e9 if k_s > 0 else 0.0
+    achieved = work["bytes"] / k_s / 1e9 if k_s > 0 else 0.0
     return {
         "metric": "mazes/s", "value": round(n / t_batch, 2), "unit": "mazes/s", "n_gpus": 1,
         "steps": reps, "warmup": 1, "ms_per_step": round(t_batch * 1e3, 3), "higher_is_better": True,
@@ -122,15 +151,14 @@ def bench_batch(args):
         "speedup_vs_plain_loop": round(t_plain / t_batch, 2) if t_plain else None,
         "effective_gcell_updates_per_s": round(eff / t_batch / 1e9, 1),
         "paths_per_s": round(n_tgt / t_batch, 1),
-        "sweep_kernel": {"kernel": "k_front" if bits else
+        "sweep_kernel": {"kernel": "k_front" if front else
                          f"k_sweep<{resolved['temporal_depth']},{resolved['lane_columns']}>",
                          "launches": prof["launches"], "ms_total": round(prof["ms"], 3),
                          "avg_us": round(prof["ms"] * 1e3 / max(prof["launches"], 1), 2),
                          "cell_updates": prof["cell_updates"], "reached_cells": reached},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": 8000.0, "unit": "GB/s",
                      "frac": round(achieved / 8000.0, 4),
-                     "algorithmic_bytes": "0.375 B per cell-layer + 4 B per reached cell" if bits
-                     else "8.125 B per cell-update"},
+                     "algorithmic_bytes": work["bytes_are"]},
         "options": resolved if tuned is None else tuned["options"],
         "options_source": ("command line or built-in defaults" if tuned is None else
                            "autotuner" if any(tuned["options"].values()) else
