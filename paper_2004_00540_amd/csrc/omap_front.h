@@ -52,11 +52,13 @@
 // two-wave integer visit it replaced: 12 us a round; a pass over a 23170^2 map
 // (load, propagate with L* = 7124, 4096 paths) 6.4 -> 2.3 ms, over 4096^2 corridors
 // (L* = 11,178) 12.4 -> 2.9, of which propagation 1.53 and 2.19.
-// With fronts everywhere (26,000^2, 5000 sources, 650 layers) VALU issue, 54 % of
-// the cycles: 485,000 visits of 5,900 VALU and 1,800 scalar instructions; the
-// whole pass 67.7 -> 9.7 ms.  A lone visit takes 10 us: list entry 0.9, region 0.6,
-// steps 2.1 + 1.7 + 1.3 + 1.2, claims and activity 1.3, and 1.6 us pass before the
-// next round's first wave.  Tiles of 64 x 128 cells take a third fewer operations
+// With fronts everywhere (26,000^2, 5000 sources, 650 layers) VALU issue, 51 % of
+// the cycles: 485,000 visits of 5,000 VALU and 1,900 scalar instructions; the
+// whole pass 67.7 -> 9.7 ms.  The dense schedule on 2000^2 (1,024 tiles a round on
+// 768 resident blocks: two visits one after another) is latency again, 16 to 21 us
+// a round with VALU issue in 13 % of the cycles.  A lone visit takes 10 us: list
+// entry 0.9, region 0.6, steps 2.1 + 1.7 + 1.3 + 1.2, claims and activity 1.3, and
+// 1.6 us pass before the next round's first wave.  Tiles of 64 x 128 cells take a third fewer operations
 // per cell but 3 us longer per visit: 26,000^2 propagation 9.0 against 8.6 ms at the
 // time, corridors 2.85 against 2.30; 32 layers a round take half the operations per
 // layer but twice the visits: 11.3 against 8.5, corridors 2.79 against 2.21, and

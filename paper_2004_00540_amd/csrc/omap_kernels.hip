@@ -173,10 +173,14 @@ __global__ __launch_bounds__(kCheckBlock) void k_check_sources(MazeDev md, const
 }
 
 // Seed V := K at the sources (both buffers) and, when `schedule` is set,
-// schedule the tiles whose interior or halo holds a source.  Bound by atomics on
-// the same addresses when there are many sources to a tile: 2,000,000 on 4096^2
-// took 3.0 ms with an exchange per tile and an addition per source, 0.39 with the
-// flags read first and an addition per wave.
+// schedule the tiles whose interior or halo holds a source.  Bound by the chain of a
+// source's nine exchanges (10 us), with many sources to a tile by atomics on the same
+// addresses: 2,000,000 on 4096^2 took 3.0 ms with an exchange per tile and an addition
+// per source, 0.39 with the flags read first and an addition per wave.  Reading the
+// flags makes the chain 3 to 7 us longer, so few sources do without: 5,000 on 4096^2
+// 10.7 us (16.3 with), 20,000 on 1000^2 23 us with (87 without).
+constexpr int kSeedMany = 8192;
+
 __global__ void k_seed(RoundArgs a, int32_t slot0, const int32_t* __restrict__ src,
                        const int32_t* __restrict__ src_slot, int32_t n, int32_t schedule,
                        int32_t* __restrict__ bad) {
@@ -218,8 +222,8 @@ __global__ void k_seed(RoundArgs a, int32_t slot0, const int32_t* __restrict__ s
             const int ny = ty + dy, nx = tx + dx;
             if (ny < 0 || ny >= md.tiles_y || nx < 0 || nx >= md.tiles_x) continue;
             // (a tile that is flagged already needs no exchange)
-            if (__hip_atomic_load(&a.flags_out[md.tile_base + ny * md.tiles_x + nx], __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT) == 0)
+            const int g = md.tile_base + ny * md.tiles_x + nx;
+            if (n <= kSeedMany || __hip_atomic_load(&a.flags_out[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
                 schedule_tile(a, md, slot, ny, nx);
         }
 }

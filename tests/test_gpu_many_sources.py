@@ -1,6 +1,6 @@
-"""Source checks and starts with more sources than one block looks at (1,024) and
-more than the check's blocks look at at once (262,144): how many lie on obstacles,
-and the map of the free ones."""
+"""Source checks and starts with more sources than one block looks at (1,024), than
+a start exchanges flags for unread (8,192) and than the check's blocks look at at
+once (262,144): how many lie on obstacles, and the map of the free ones."""
 import numpy as np
 import pytest
 
@@ -9,7 +9,7 @@ from gpu_helpers import to_dev
 
 pytestmark = pytest.mark.gpu
 
-COUNTS = (1, 64, 256, 257, 1024, 1025, 2048, 5000, 70001, 262144, 262145, 1048576)
+COUNTS = (1, 64, 256, 257, 1024, 1025, 2048, 8192, 8193, 70001, 262144, 262145, 1048576)
 
 
 @pytest.mark.parametrize("n", COUNTS)
