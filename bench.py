@@ -415,8 +415,8 @@ def bench_plain(args):
     resolved = omap.resolve_options(**opts)
     executed = prof["cell_updates"]            # per propagation = per step
     gcups = executed / step_s / 1e9
-    work = propagation_work(runs_front(opts, many=False), prof["cell_updates"], info["tile_visits"],
-                            info["reached_cells"])
+    front = runs_front(opts, many=False)
+    work = propagation_work(front, prof["cell_updates"], info["tile_visits"], info["reached_cells"])
     alg_bytes = work["bytes"]
     kern_s = prof["ms"] / 1e3
     launches = max(prof["launches"], 1)
@@ -442,7 +442,9 @@ def bench_plain(args):
         "path_cells": int(cells0.numel()),
         "phase_ms": {"ingest": round(t_load, 3), "propagate": round(t_prop, 3), "extract": round(t_ext, 3)},
         "event_ms_per_step": round(ms, 3),
-        "sweep_kernel": {"launches": prof["launches"], "ms_total": round(prof["ms"], 3),
+        "sweep_kernel": {"kernel": "k_front (64 layers on tiles of 64 x 64 cells)" if front else
+                         f"k_sweep<{resolved['temporal_depth']},{resolved['lane_columns']}>",
+                         "launches": prof["launches"], "ms_total": round(prof["ms"], 3),
                          "avg_us": round(prof["ms"] * 1e3 / max(prof["launches"], 1), 2),
                          "cell_updates": prof["cell_updates"],
                          "dense_cell_updates": N * S_J},
