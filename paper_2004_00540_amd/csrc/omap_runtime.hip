@@ -77,7 +77,7 @@ public:
         }
         Batch b;
         b.left = (int)chunks - 1;
-        const size_t per = (n / chunks + 63) & ~size_t(63);
+        const size_t per = ((n + chunks - 1) / chunks + 63) & ~size_t(63);   // chunks of these cover n
         {
             std::lock_guard<std::mutex> lk(m_);
             for (size_t k = 1; k < chunks; ++k) {
