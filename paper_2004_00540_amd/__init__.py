@@ -88,6 +88,7 @@ def lib() -> ctypes.CDLL:
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it with "
                           "`python -c 'import __graft_entry__ as g; g.build()'`")
+    import torch  # noqa: F401  (its HIP runtime has to be loaded before the library's: a process has one)
     L = ctypes.CDLL(LIB_PATH)
     P, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
     PP = ctypes.POINTER(ctypes.c_void_p)
