@@ -839,8 +839,10 @@ class Solver {
     // only to grow; the next upload is ordered after this one's kernels on the stream).
     omap_status_t start_scratch(size_t n_int32, int32_t** out) {
         if (n_int32 > start_cap_) {
-            HIP_TRY(hipStreamSynchronize(stream));
-            if (d_start_) (void)hipFree(d_start_);
+            if (d_start_) {   // (the first time nothing reads it, and a wait costs a small plan 10 us)
+                HIP_TRY(hipStreamSynchronize(stream));
+                (void)hipFree(d_start_);
+            }
             d_start_ = nullptr;
             start_cap_ = 0;
             const size_t want = std::max<size_t>(n_int32, 1024);
